@@ -400,12 +400,16 @@ int fl_gn_step(fl_ctx* ctx, const double* g, const double* H, double lambda, dou
  * the candidate exp(d_i) S_i, which is taken if F decreases (lambda / 10,
  * at least 1e-12) and refused otherwise (lambda x 10, at most 1e12; the
  * linearisation is kept).  lambda = 0 takes every Gauss-Newton step.  The
- * solve is one of two (`solver`):
+ * solve is one of three (`solver`):
  *  - direct: the free nodes are renumbered by reverse Cuthill-McKee on the
  *    host; when no edge then spans more than FL_PGO_MAX_BAND_NODES - 1
- *    positions, the banded H is factored by float64 Cholesky in one
- *    workgroup and solved exactly (cg_used = 0; a pivot that is not
- *    positive reports -1 and refuses that iteration's candidate).  A band
+ *    positions, the banded H is factored by float64 Cholesky and solved
+ *    exactly (cg_used = 0; a pivot that is not positive reports -1 and
+ *    refuses that iteration's candidate).  FL_PGO_SOLVER_AUTO factors bands
+ *    of at most 37 keyframes by block cyclic reduction (a nested-dissection
+ *    order) over the whole GPU;
+ *  - the band solves, one workgroup (wider bands, graphs of fewer than 4 or
+ *    more than about 87,000 free keyframes, and FL_PGO_SOLVER_DIRECT[_WIDE]).  A band
  *    of at most 12 keyframes is factored through a window of rows in LDS,
  *    a wider one (several loops, for instance) with the band itself in
  *    device memory as the window; both take the same floating-point steps
@@ -424,8 +428,8 @@ int fl_gn_step(fl_ctx* ctx, const double* g, const double* H, double lambda, dou
 #define FL_PGO_MAX_BAND_NODES 64   /* widest band of the direct solver, in keyframes */
 #define FL_PGO_SOLVER_AUTO 0       /* direct when the band fits, else conjugate gradients */
 #define FL_PGO_SOLVER_CG 1
-#define FL_PGO_SOLVER_DIRECT 2     /* FL_ERANGE when the band does not fit */
-#define FL_PGO_SOLVER_DIRECT_WIDE 3   /* direct, with the device-memory window at every band width
+#define FL_PGO_SOLVER_DIRECT 2     /* the band solve; FL_ERANGE when the band does not fit */
+#define FL_PGO_SOLVER_DIRECT_WIDE 3   /* the band solve, with the device-memory window at every band width
                                          (FL_ERANGE when the band does not fit) */
 typedef struct {
     int32_t n_nodes;

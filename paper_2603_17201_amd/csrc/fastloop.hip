@@ -16,6 +16,7 @@
 #include "fastloop.h"
 #include "fl_internal.h"
 #include "fl_pgo.h"
+#include "fl_pgo_cr.h"
 #include "fl_residual.h"
 #include "fl_search.h"
 
@@ -1467,6 +1468,72 @@ int fl_reproj_residual_bwd_inv(fl_ctx* c, int32_t n, const float* xyz, const flo
     return FL_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The block shape of the cyclic reduction for a graph of nf free keyframes
+// whose edges span at most bw band positions: 16 x 16 tiles a side of a
+// block, 0: the band solves.  Ten iterations, band solve against cyclic
+// reduction: 2 free keyframes 344 / 384 us, 4: 507 / 431, 59 (bands of 4, 13,
+// 18 keyframes) 3.0 / 1.2, 7.4 / 2.8, 6.7 / 2.2 ms, 999 36.5 / 2.3 ms (band
+// of 7) and 97 / 6.7 ms (band of 24).  Blocks of more than 36 keyframes would
+// not fit the registers, and graphs beyond kCrMaxEntries (87,000 keyframes at
+// a band of 7) would take over 1 GiB of workspace.
+int cr_shape(int bw, int nf, CrArgs& cr) {
+    if (nf < 4) return 0;
+    for (const int nt : {3, 4, 6, 8, 11, 14, 16}) {
+        const int B = 16 * nt / 7;
+        if (B < bw) continue;
+        cr.block_pos = B;
+        cr.n_pos = nf;
+        cr.m = 16 * nt;
+        cr.n_blocks = (nf + B - 1) / B;
+        if ((int64_t)cr.n_blocks * cr.m * cr.m > kCrMaxEntries) break;
+        return nt;
+    }
+    cr = CrArgs{};
+    return 0;
+}
+
+template <int NT>
+void launch_cr_levels(const CrArgs& cr, hipStream_t st) {
+    constexpr int G = cr_groups(NT), tasks = NT * (NT + 1) / 2 + NT * NT + NT, waves = kCrUpdBlock / kWave;
+    int n = cr.n_blocks, s = 1;
+    for (; n > 1; n = (n + 1) / 2, s *= 2) {
+        hipLaunchKernelGGL(cr_eliminate_kernel<NT>, dim3(n / 2 * G), dim3(kCrWaves * 64), 0, st, cr, s, n, 0);
+        hipLaunchKernelGGL(cr_update_kernel<NT>, dim3((tasks + waves - 1) / waves, (n + 1) / 2), dim3(kCrUpdBlock), 0,
+                           st, cr, s, n);
+    }
+    hipLaunchKernelGGL(cr_eliminate_kernel<NT>, dim3(G), dim3(kCrWaves * 64), 0, st, cr, s, 1, 1);
+    hipLaunchKernelGGL(cr_back_kernel<NT>, dim3(1), dim3(kCrBackBlock), 0, st, cr, s, 1, 1);
+    for (s /= 2; s >= 1; s /= 2) {
+        n = (cr.n_blocks + s - 1) / s;   // active blocks of the level
+        hipLaunchKernelGGL(cr_back_kernel<NT>, dim3(n / 2), dim3(kCrBackBlock), 0, st, cr, s, n, 0);
+    }
+}
+
+void launch_cr(int nt, const PgoArgs& a, const CrArgs& cr, hipStream_t st) {
+    const int64_t entries = (int64_t)cr.n_blocks * cr.m * cr.m;
+    hipLaunchKernelGGL(cr_fill_kernel, dim3((unsigned)std::min<int64_t>((entries + kCrFillBlock - 1) / kCrFillBlock, 4096)),
+                       dim3(kCrFillBlock), 0, st, cr);
+    hipLaunchKernelGGL(cr_assemble_kernel, dim3((cr.n_pos + 3) / 4), dim3(256), 0, st, a, cr);
+    switch (nt) {
+        case 3: launch_cr_levels<3>(cr, st); break;
+        case 4: launch_cr_levels<4>(cr, st); break;
+        case 6: launch_cr_levels<6>(cr, st); break;
+        case 8: launch_cr_levels<8>(cr, st); break;
+        case 11: launch_cr_levels<11>(cr, st); break;
+        case 14: launch_cr_levels<14>(cr, st); break;
+        default: launch_cr_levels<16>(cr, st); break;
+    }
+    hipLaunchKernelGGL(cr_candidate_kernel, dim3((a.n_nodes + 63) / 64), dim3(64), 0, st, a, cr);
+}
+
+}  // namespace
+
+extern "C" {
+
 int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_params* P, hipStream_t stream) {
     if (!c) return fail(FL_EINVAL, "ctx is NULL");
     if (!G || !P) return fail(FL_EINVAL, "graph or params is NULL");
@@ -1567,6 +1634,14 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     const int band_w = 7 * (bw + 1);
     const int64_t band_vs = 7 * (int64_t)nf;
     const size_t tab_bytes = sizeof(int32_t) * tab.size();
+    // The automatic choice takes the block cyclic reduction where its shape
+    // allows; a solver asked for by name is the band solve.
+    CrArgs cr{};
+    const int cr_nt = direct && P->solver == FL_PGO_SOLVER_AUTO ? cr_shape(bw, nf, cr) : 0;
+    // co-resident solve workgroups: enough threads for every edge and node,
+    // at most one per CU (each grid barrier costs every workgroup a fence)
+    const int solve_grid = (int)std::max<int64_t>(
+        1, std::min<int64_t>(c->n_cu, (std::max(E, N) + (int64_t)kPgoBlock - 1) / kPgoBlock));
     size_t off_b = 0;
     auto take = [&](size_t bytes) {
         const size_t o = off_b;
@@ -1577,21 +1652,20 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     const size_t L_fix = take((size_t)N);
     const size_t L_e = take(sizeof(double) * 7 * (size_t)E);
     const size_t L_J = take(sizeof(double) * 98 * (size_t)E);
-    const size_t L_u = take(sizeof(double) * 7 * (size_t)E);
-    const size_t L_vec = take(sizeof(double) * 6 * 7 * (size_t)N);
-    const size_t L_D = take(sizeof(double) * 49 * (size_t)N);
-    // co-resident solve workgroups: enough threads for every edge and node,
-    // at most one per CU (each grid barrier costs every workgroup a fence)
-    const int solve_grid = (int)std::max<int64_t>(
-        1, std::min<int64_t>(c->n_cu, (std::max(E, N) + (int64_t)kPgoBlock - 1) / kPgoBlock));
+    const size_t L_u = take(direct ? 0 : sizeof(double) * 7 * (size_t)E);
+    const size_t L_vec = take(direct ? 0 : sizeof(double) * 6 * 7 * (size_t)N);
+    const size_t L_D = take(direct ? 0 : sizeof(double) * 49 * (size_t)N);
     const size_t L_bar = take(sizeof(uint32_t));
     const size_t L_red = take(sizeof(double) * 2 * 4 * (size_t)solve_grid);
-    const size_t L_band = take(direct ? sizeof(double) * (size_t)band_vs * band_w : 0);
-    const size_t L_rhs = take(direct ? sizeof(double) * (size_t)band_vs : 0);
-    const size_t L_xs = take(direct ? sizeof(double) * (size_t)band_vs : 0);
     const size_t L_lm = take(sizeof(double) * kLmWords);
     const size_t L_Sc = take(sizeof(double) * 13 * (size_t)N);
     const size_t L_ec = take(sizeof(double) * (size_t)E);
+    const bool band = direct && cr_nt == 0;
+    const size_t L_band = take(band ? sizeof(double) * (size_t)band_vs * band_w : 0);
+    const size_t L_rhs = take(band ? sizeof(double) * (size_t)band_vs : 0);
+    const size_t L_xs = take(band ? sizeof(double) * (size_t)band_vs : 0);
+    const size_t cr_mat = sizeof(double) * (size_t)cr.n_blocks * cr.m * cr.m, cr_vec = sizeof(double) * (size_t)cr.n_blocks * cr.m;
+    const size_t L_cr = take(4 * cr_mat + 2 * cr_vec);
     int rc = c->pgo.ensure(off_b);
     if (rc) return rc;
     char* base = (char*)c->pgo.p;
@@ -1632,6 +1706,18 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     a.band = (double*)(base + L_band);
     a.rhs = (double*)(base + L_rhs);
     a.xs = (double*)(base + L_xs);
+    a.e_q = direct ? 1 : E;
+    a.e_k = direct ? 7 : 1;
+    a.J_q = direct ? 1 : E;
+    a.J_k = direct ? 98 : 1;
+    a.J_s = direct ? 49 : (int64_t)49 * E;
+    cr.D = (double*)(base + L_cr);
+    cr.C = cr.D + cr_mat / sizeof(double);
+    cr.YL = cr.C + cr_mat / sizeof(double);
+    cr.LI = cr.YL + cr_mat / sizeof(double);
+    cr.b = cr.LI + cr_mat / sizeof(double);
+    cr.x = cr.b + cr_vec / sizeof(double);
+    cr.lm = (double*)(base + L_lm);
     a.lm = (double*)(base + L_lm);
     a.S_c = (double*)(base + L_Sc);
     a.ecost = (double*)(base + L_ec);
@@ -1649,7 +1735,9 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     for (int it = 0; it < P->iters; ++it) {
         a.step = it;
         if (E > 0) hipLaunchKernelGGL(pgo_jacobian_kernel, dim3(jac_grid), dim3(kPgoJacBlock), 0, stream, a);
-        if (direct) {
+        if (cr_nt) {
+            launch_cr(cr_nt, a, cr, stream);
+        } else if (direct) {
             hipLaunchKernelGGL(pgo_band_assemble_kernel, dim3((unsigned)((band_vs + kBandBlock - 1) / kBandBlock)),
                                dim3(kBandBlock), 0, stream, a);
             if (wide)

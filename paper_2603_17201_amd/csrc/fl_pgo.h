@@ -16,10 +16,14 @@
 // iteration and never waits.
 //
 // Per iteration pgo_jacobian_kernel runs one thread per edge (it exits at
-// once after a refusal), then one of two solves writes the candidate:
-//  - direct (the paper's is a direct LDL^T): with the free nodes renumbered
+// once after a refusal), then one of three solves writes the candidate:
+//  - direct (the paper's is a direct LDL^T), with the free nodes renumbered
 //    so that every edge spans at most b positions (reverse Cuthill-McKee on
-//    the host), H is a band of W = 7 (b + 1) scalars.  pgo_band_assemble_kernel
+//    the host): block cyclic reduction over the whole GPU (fl_pgo_cr.h), the
+//    automatic choice;
+//  - direct, by band: H is a band of W = 7 (b + 1) scalars, factored in one
+//    workgroup (bands too wide for the cyclic reduction, very long graphs, and
+//    callers that ask for it).  pgo_band_assemble_kernel
 //    writes each band row from its node's incident edges;
 //    pgo_band_solve_kernel, one workgroup, factors the band by Cholesky in
 //    block columns of one keyframe (7 columns) with the forward substitution
@@ -43,7 +47,7 @@
 namespace fl {
 
 constexpr int kPgoBlock = 256;      // threads of a solve workgroup (one per CU, all co-resident)
-constexpr int kPgoJacBlock = 256;   // threads of a Jacobian workgroup
+constexpr int kPgoJacBlock = 64;    // threads (edges) of a Jacobian workgroup: one wave, so that a graph fills more CUs
 constexpr int kBandBlock = 512;     // threads of the band assembly and of the one band-solve workgroup
 constexpr int kBandLdsNodes = 12;   // widest band, in keyframes, whose window the LDS holds
 constexpr int kBandMaxW = 7 * kBandLdsNodes;   // widest band row of the LDS-window solve, in scalars
@@ -69,11 +73,15 @@ struct PgoArgs {
     double cg_tol;
     int32_t step;               // outer step index (cost and count outputs)
     // workspace
-    // Component-major layouts (entry, then edge or node), so that the
-    // threads of a wave, which take consecutive edges or nodes, load
-    // consecutive addresses.
-    double* e;                  // [7][n_edges]
-    double* J;                  // [2][49][n_edges]: J_i then J_j, entry 7 r + c of each
+    // The edge errors and Jacobians (J_i then J_j, entry 7 r + c of each) at
+    // e[r e_q + k e_k] and J[side J_s + q J_q + k J_k] of edge k.  For the
+    // conjugate gradients component-major (entry, then edge; likewise their
+    // vectors below), so that the threads of a wave, which take consecutive
+    // edges or nodes, load consecutive addresses; for the direct solves
+    // edge-major, whose assembly reads one edge's entries together.
+    double* e;
+    double* J;
+    int64_t e_q, e_k, J_q, J_k, J_s;
     double* u;                  // [7][n_edges] conjugate-gradient edge products
     double* vec;                // [6][7][n_nodes]: g, x, r, z, p, q
     double* Dfac;               // [49][n_nodes] LDL^T factors of the preconditioner blocks
@@ -224,9 +232,26 @@ __device__ inline void jl_inv_adjoint(const double* K11, const double* K21, cons
     P[48] = sign;
 }
 
+// One Jacobian (7 x 7 row-major) of edge k, this thread's, into a.J.  The
+// edge-major layout goes through LDS, so that the wave's stores are of
+// consecutive addresses (written by each thread at its own stride they took
+// 23 us against 11 for 3,002 edges).
+__device__ inline void pgo_store_jacobian(const PgoArgs& a, int side, int k, const double* P, double* s_P) {
+    double* J = a.J + side * a.J_s;
+    if (a.J_q != 1) {
+        for (int q = 0; q < 49; ++q) J[q * a.J_q + k * a.J_k] = P[q];
+        return;
+    }
+    for (int q = 0; q < 49; ++q) s_P[threadIdx.x * 49 + q] = P[q];
+    // one wave: its LDS accesses are in order; lanes past the last edge are not here
+    const int k0 = blockIdx.x * kPgoJacBlock, n = min(kPgoJacBlock, a.n_edges - k0);
+    for (int i = threadIdx.x; i < n * 49; i += n) J[(k0 + i / 49) * a.J_k + i % 49] = s_P[i];
+}
+
 // e and the exact J_i, J_j of edge k (one thread per edge); nothing after a
 // refused step (the linearisation at the accepted poses is kept).
 __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
+    __shared__ double s_P[kPgoJacBlock * 49];
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n_edges || a.lm[kLmRelin] == 0.0) return;
     const int i = a.edges[2 * k], j = a.edges[2 * k + 1];
@@ -234,7 +259,7 @@ __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
     const Sim3d Ed = sim3_mul(Minv, sim3_mul(sim3_load(a.S + 13 * (int64_t)j), sim3_inv(sim3_load(a.S + 13 * (int64_t)i))));
     double e[7];
     sim3_log(Ed, e);
-    for (int r = 0; r < 7; ++r) a.e[(int64_t)r * a.n_edges + k] = e[r];
+    for (int r = 0; r < 7; ++r) a.e[r * a.e_q + k * a.e_k] = e[r];
     const LeftJac J = sim3_left_jacobian(e);
     double K11[9], K22[9], K21[9], k23[3], A[9];
     inv33(J.J11, K11);
@@ -245,11 +270,9 @@ __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
     for (int r = 0; r < 3; ++r) k23[r] = -fma(K22[3 * r], J.j23[0], fma(K22[3 * r + 1], J.j23[1], K22[3 * r + 2] * J.j23[2]));
     double P[49];
     jl_inv_adjoint(K11, K21, K22, k23, Ed, -1.0, P);   // J_i = -J_l^-1 Ad(E)
-    double* Ji = a.J + k;
-    for (int q = 0; q < 49; ++q) Ji[(int64_t)q * a.n_edges] = P[q];
+    pgo_store_jacobian(a, 0, k, P, s_P);
     jl_inv_adjoint(K11, K21, K22, k23, Minv, 1.0, P);  // J_j = J_l^-1 Ad(M^-1)
-    double* Jj = a.J + (int64_t)49 * a.n_edges + k;
-    for (int q = 0; q < 49; ++q) Jj[(int64_t)q * a.n_edges] = P[q];
+    pgo_store_jacobian(a, 1, k, P, s_P);
 }
 
 // y += J^T v with J's entry 7 r + c at J[(7 r + c) st] and v's entry r at
@@ -534,7 +557,7 @@ __global__ __launch_bounds__(kPgoBlock) void pgo_solve_kernel(PgoArgs a) {
 __global__ __launch_bounds__(kBandBlock) void pgo_band_assemble_kernel(PgoArgs a) {
     const int64_t R = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (R >= a.band_vs) return;
-    const int W = a.band_w, w = W - 1, E = a.n_edges;
+    const int W = a.band_w, w = W - 1;
     const int P = (int)(R / 7), r = (int)(R % 7);
     const int n = a.order[P];
     double* row = a.band + R * W;
@@ -543,16 +566,16 @@ __global__ __launch_bounds__(kBandBlock) void pgo_band_assemble_kernel(PgoArgs a
     for (int t = a.adj_off[n]; t < a.adj_off[n + 1]; ++t) {
         const int k = a.adj[t] >> 1, side = a.adj[t] & 1;
         const int m = a.edges[2 * k + 1 - side];
-        const double* Ja = a.J + (int64_t)49 * side * E + k;
-        const double* Jb = a.J + (int64_t)49 * (1 - side) * E + k;
+        const double* Ja = a.J + 98 * (int64_t)k + 49 * side;
+        const double* Jb = a.J + 98 * (int64_t)k + 49 * (1 - side);
         double ja[7];
         for (int rr = 0; rr < 7; ++rr) {
-            ja[rr] = Ja[(int64_t)(7 * rr + r) * E];
-            gr = fma(ja[rr], a.e[(int64_t)rr * E + k], gr);
+            ja[rr] = Ja[7 * rr + r];
+            gr = fma(ja[rr], a.e[7 * (int64_t)k + rr], gr);
         }
         for (int c = 0; c <= r; ++c) {
             double v = 0.0;
-            for (int rr = 0; rr < 7; ++rr) v = fma(ja[rr], Ja[(int64_t)(7 * rr + c) * E], v);
+            for (int rr = 0; rr < 7; ++rr) v = fma(ja[rr], Ja[7 * rr + c], v);
             row[c - r + w] += v;
         }
         const int pm = a.pos[m];
@@ -560,7 +583,7 @@ __global__ __launch_bounds__(kBandBlock) void pgo_band_assemble_kernel(PgoArgs a
         if (pm >= 0 && pm < P && base >= 0) {
             for (int c = 0; c < 7; ++c) {
                 double v = 0.0;
-                for (int rr = 0; rr < 7; ++rr) v = fma(ja[rr], Jb[(int64_t)(7 * rr + c) * E], v);
+                for (int rr = 0; rr < 7; ++rr) v = fma(ja[rr], Jb[7 * rr + c], v);
                 row[base + c] += v;
             }
         }

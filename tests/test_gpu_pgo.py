@@ -280,3 +280,33 @@ def test_loop_of_200_keyframes_direct_step_matches_oracle(ctx):
     assert np.array_equal(acc, acc_ref)
     assert _err(S, S_ref) < 1e-9, _err(S, S_ref)
     assert np.max(np.abs(cost - h) / h) < 1e-9
+
+
+@pytest.mark.parametrize("n,covis", [
+    (5, 3), (7, 6), (8, 6), (19, 6), (20, 7), (37, 9), (22, 10), (27, 13), (28, 14), (55, 18), (40, 19), (51, 25),
+    (54, 26), (66, 32), (70, 33), (73, 36), (75, 37),
+])
+def test_cyclic_reduction_block_shapes_match_oracle(ctx, n, covis):
+    """The automatic solve at the edges of its block shapes (the narrowest and
+    the widest band of each tile count, one to four blocks, last blocks full
+    and nearly empty, and the first band that goes to the band solve):
+    the oracle's poses and costs, to the bounds of the other direct solves."""
+    d = synth.gen_pose_graph(n=n, seed=37, covis=covis, n_loops=0)
+    S_ref, h, lams_ref, acc_ref = _oracle(d, iters=2)
+    S, cost, used, lams, acc = _run(ctx, d, iters=2)
+    assert all(u == 0 for u in used)
+    assert np.array_equal(acc, acc_ref) and np.array_equal(lams, lams_ref)
+    assert _err(S, S_ref) < 1e-9, _err(S, S_ref)
+    assert np.max(np.abs(cost - h) / h) < 1e-9
+
+
+def test_cyclic_reduction_reports_a_failed_pivot(ctx):
+    """A measurement that is not a number: no positive pivot, so the
+    iteration reports -1 and leaves the poses, as the band solve does."""
+    d = synth.gen_pose_graph(n=40, seed=31, n_loops=3)
+    d["M"] = d["M"].copy()
+    d["M"][20, 0] = np.nan
+    for solver in (0, DIRECT):
+        S, _, used, _, acc = _run(ctx, d, iters=1, solver=solver)
+        assert list(used) == [-1] and list(acc) == [0]
+        assert np.array_equal(S, d["S0"])
