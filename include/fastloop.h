@@ -377,6 +377,23 @@ int fl_sim3_exp_mul(fl_ctx* ctx, const double* xi, const double* S_in, double* S
 int fl_sim3_grad_xi(fl_ctx* ctx, const double* xi, const double* g, const double* scale, double* out,
                     hipStream_t stream);
 
+/* The loss as a function of the tangent coordinates xi, in one launch each
+ * way (Sec. IV-F): the forward composes S = exp(xi) S0, as fl_sim3_exp_mul
+ * does, and evaluates the loss at its float32 form, which it writes to
+ * S32_out; the backward takes that form and writes grad_xi = scale *
+ * J_l(xi)^T g with g as fl_reproj_residual_bwd computes it and J_l, scale as
+ * in fl_sim3_grad_xi.  xi [7], S0 [13], S32_out, loss [1], scale [1] or NULL
+ * and grad_xi [7] are device pointers; the rest, and the errors, as
+ * fl_reproj_residual_fwd. */
+int fl_sim3_residual_fwd(fl_ctx* ctx, int32_t n, const float* xyz, const float* uv, const int32_t* kf_idx,
+                         int32_t n_kf, const float* kf_T, const double* xi, const double* S0,
+                         const fl_pinhole* K /* host */, float huber_delta, fl_sim3* S32_out, double* loss,
+                         hipStream_t stream);
+int fl_sim3_residual_bwd(fl_ctx* ctx, int32_t n, const float* xyz, const float* uv, const int32_t* kf_idx,
+                         int32_t n_kf, const float* kf_T, const fl_sim3* S32, const fl_pinhole* K /* host */,
+                         float huber_delta, const double* xi, const double* scale, double* grad_xi,
+                         hipStream_t stream);
+
 /* One Gauss-Newton / Levenberg-Marquardt step of the Sim3 refinement
  * (Sec. IV-C; the paper's pose optimisation is Levenberg-Marquardt, Sec. VI):
  * solve (H + lambda diag(H)) d = -g

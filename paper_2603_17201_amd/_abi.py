@@ -128,6 +128,10 @@ SIGNATURES = [
     ("fl_reproj_residual_bwd_inv", c_int32, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_void_p,
                                              c_void_p, ctypes.POINTER(Pinhole), c_float, c_double, c_void_p,
                                              c_void_p, c_void_p]),
+    ("fl_sim3_residual_fwd", c_int32, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_void_p, c_void_p,
+                                       c_void_p, ctypes.POINTER(Pinhole), c_float, c_void_p, c_void_p, c_void_p]),
+    ("fl_sim3_residual_bwd", c_int32, [c_void_p, c_int32, c_void_p, c_void_p, c_void_p, c_int32, c_void_p, c_void_p,
+                                       ctypes.POINTER(Pinhole), c_float, c_void_p, c_void_p, c_void_p, c_void_p]),
     ("fl_pose_graph_optimize", c_int32, [c_void_p, ctypes.POINTER(PoseGraph), ctypes.POINTER(PgoParams), c_void_p]),
     ("fl_sim3_inverse", c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]),
     ("fl_sim3_exp_mul", c_int32, [c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_void_p]),

@@ -401,6 +401,29 @@ class Context:
                                         _ptr(H, torch.float64, "H", 8), self._stream(stream)), name)
         return g, H
 
+    def _residual_fwd_xi(self, xi, S0, xyz, uv, kf_idx, kf_T, cam8, delta):
+        """The loss at S = exp(xi) S0 and the float32 form of S, in one launch."""
+        S32 = torch.empty(16, dtype=torch.float32, device=self.device)
+        n, px, pu, pk, nkf, pT, pS = self._res_common(xyz, uv, kf_idx, kf_T, S32)
+        loss = torch.empty(1, dtype=torch.float64, device=self.device)
+        K = pinhole_struct(cam8)
+        _check(self._lib.fl_sim3_residual_fwd(self._h, n, px, pu, pk, nkf, pT, _ptr(xi, torch.float64, "xi", 8),
+                                              _ptr(S0, torch.float64, "S_in", 8), ctypes.byref(K), float(delta), pS,
+                                              _ptr(loss, torch.float64, "loss", 8), self._stream()),
+               "fl_sim3_residual_fwd")
+        return S32, loss
+
+    def _residual_bwd_xi(self, xi, scale, xyz, uv, kf_idx, kf_T, S32, cam8, delta):
+        """scale * J_l(xi)^T g of the residual at S32 = exp(xi) S0, in one launch."""
+        n, px, pu, pk, nkf, pT, pS = self._res_common(xyz, uv, kf_idx, kf_T, S32)
+        out = torch.empty(7, dtype=torch.float64, device=self.device)
+        K = pinhole_struct(cam8)
+        _check(self._lib.fl_sim3_residual_bwd(self._h, n, px, pu, pk, nkf, pT, pS, ctypes.byref(K), float(delta),
+                                              _ptr(xi, torch.float64, "xi", 8), _ptr(scale, torch.float64, "scale", 8),
+                                              _ptr(out, torch.float64, "out", 8), self._stream()),
+               "fl_sim3_residual_bwd")
+        return out
+
     def pose_graph_optimize(self, S, M, edges, fixed=None, iters: int = 10, cg_iters: int = 500, lam: float = 1e-4,
                             cg_tol: float = 1e-10, solver: int = 0, history: bool = False, stream=None):
         """Essential-graph optimisation in place (Levenberg-Marquardt from
@@ -554,17 +577,15 @@ class Sim3Residual(torch.autograd.Function):
     """loss = sum_i Huber(|pi(T_k exp(xi) S0 X_i) - uv_i|).
 
     forward(xi [7] f64, S0 [13] f64, xyz, uv, kf_idx, kf_T, cam8, delta, ctx)
-    The backward is the hand-written kernel pair: the residual backward
-    gives g, the gradient with respect to a left perturbation of
-    S = exp(xi) S0, and fl_sim3_grad_xi turns it into dL/dxi =
-    grad_out * J_l(xi)^T g (J_l the Sim3 left Jacobian; the identity at
-    xi = 0)."""
+    The backward is hand-written: one launch sums g, the gradient with
+    respect to a left perturbation of S = exp(xi) S0, and turns it into
+    dL/dxi = grad_out * J_l(xi)^T g (J_l the Sim3 left Jacobian; the identity
+    at xi = 0)."""
 
     @staticmethod
     def forward(fctx, xi, S0, xyz, uv, kf_idx, kf_T, cam8, delta, flctx: Context):
         xi = xi.detach().contiguous()
-        S, S32 = flctx.sim3_exp_mul(xi, S0.contiguous())
-        _, _, loss = flctx.residual_fwd(xyz, uv, kf_idx, kf_T, S32, cam8, delta, want_r=False)
+        S32, loss = flctx._residual_fwd_xi(xi, S0.contiguous(), xyz, uv, kf_idx, kf_T, cam8, delta)
         fctx.save_for_backward(xyz, uv, S32, xi)
         fctx.kf_idx = kf_idx
         fctx.kf_T = kf_T
@@ -576,8 +597,6 @@ class Sim3Residual(torch.autograd.Function):
     @staticmethod
     def backward(fctx, grad_out):
         xyz, uv, S32, xi = fctx.saved_tensors
-        g, _ = fctx.flctx.residual_bwd(xyz, uv, fctx.kf_idx, fctx.kf_T, S32, fctx.cam8, fctx.delta, 1.0,
-                                       want_H=False)
         scale = grad_out.detach().to(torch.float64).contiguous().reshape(1)
-        gx = fctx.flctx.sim3_grad_xi(xi, g, scale)
+        gx = fctx.flctx._residual_bwd_xi(xi, scale, xyz, uv, fctx.kf_idx, fctx.kf_T, S32, fctx.cam8, fctx.delta)
         return (gx, None, None, None, None, None, None, None, None)

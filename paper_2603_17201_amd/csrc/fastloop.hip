@@ -1468,6 +1468,39 @@ int fl_reproj_residual_bwd_inv(fl_ctx* c, int32_t n, const float* xyz, const flo
     return FL_OK;
 }
 
+int fl_sim3_residual_fwd(fl_ctx* c, int32_t n, const float* xyz, const float* uv, const int32_t* kf_idx, int32_t n_kf,
+                         const float* kf_T, const double* xi, const double* S0, const fl_pinhole* K,
+                         float huber_delta, fl_sim3* S32_out, double* loss, hipStream_t stream) {
+    ResArgs a;
+    int grid = 1;
+    const int rc = residual_args(c, n, xyz, uv, kf_idx, n_kf, kf_T, S32_out, K, huber_delta, a, grid);
+    if (rc) return rc;
+    if (!xi || !S0 || !loss) return fail(FL_EINVAL, "xi, S0 and loss must not be NULL");
+    a.xi = xi;
+    a.S0 = S0;
+    a.S_out = S32_out;
+    a.loss = loss;
+    hipLaunchKernelGGL(residual_fwd_kernel, dim3(grid), dim3(kResBlock), 0, stream, a);
+    FL_HIP(hipGetLastError());
+    return FL_OK;
+}
+
+int fl_sim3_residual_bwd(fl_ctx* c, int32_t n, const float* xyz, const float* uv, const int32_t* kf_idx, int32_t n_kf,
+                         const float* kf_T, const fl_sim3* S32, const fl_pinhole* K, float huber_delta,
+                         const double* xi, const double* scale, double* grad_xi, hipStream_t stream) {
+    ResArgs a;
+    int grid = 1;
+    const int rc = residual_args(c, n, xyz, uv, kf_idx, n_kf, kf_T, S32, K, huber_delta, a, grid);
+    if (rc) return rc;
+    if (!xi || !grad_xi) return fail(FL_EINVAL, "xi and grad_xi must not be NULL");
+    a.xi = xi;
+    a.scale = scale;
+    a.gxi = grad_xi;
+    hipLaunchKernelGGL(residual_bwd_kernel<false>, dim3(grid), dim3(kResBlock), 0, stream, a);
+    FL_HIP(hipGetLastError());
+    return FL_OK;
+}
+
 }  // extern "C"
 
 namespace {

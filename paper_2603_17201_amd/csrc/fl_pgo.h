@@ -616,14 +616,6 @@ __host__ __device__ constexpr size_t band_solve_lds_bytes(int W) {
     return sizeof(double) * ((size_t)W * band_win_stride(W) + (W + 1) + 7 * (size_t)W + 7);
 }
 
-// A float64 value of lane l (l wave-uniform).
-__device__ __forceinline__ double readlane_f64(double x, int l) {
-    const long long v = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)v, l);
-    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // The candidate poses of a direct solve: S_n <- exp(x_n) S_n for every free
 // node (x in a.xs, by band position), held nodes copied.
 __device__ inline void band_candidate_poses(const PgoArgs& a) {

@@ -439,36 +439,67 @@ __device__ __forceinline__ void accumulate(const PairTerm& t, double* acc) {
         for (int j = i; j < 7; ++j) acc[k++] += (double)(w * fmaf(t.J[0][i], t.J[0][j], t.J[1][i] * t.J[1][j]));
 }
 
+// A float64 value of lane l (l wave-uniform).
+__device__ __forceinline__ double readlane_f64(double x, int l) {
+    const long long v = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)v, l);
+    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// The value of lane l ^ H (H: a power of two), by lane permutations inside a
+// row of 16 (quad_perm, row_ror:8, and for 4 row_half_mirror after the
+// quads' reversal) and through LDS across rows.
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const long long v = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xf, 0xf, false);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+template <int H>
+__device__ __forceinline__ double lane_xor_f64(double x) {
+    if constexpr (H == 1) return dpp_f64<0xB1>(x);                       // quad_perm [1, 0, 3, 2]
+    else if constexpr (H == 2) return dpp_f64<0x4E>(x);                  // quad_perm [2, 3, 0, 1]
+    else if constexpr (H == 4) return dpp_f64<0x141>(dpp_f64<0x1B>(x));  // quad_perm [3, 2, 1, 0], row_half_mirror
+    else if constexpr (H == 8) return dpp_f64<0x128>(x);                 // row_ror:8
+    else return __shfl_xor(x, H);
+}
+
+// One step of the reduce-scatter below: lanes whose bit H is set keep the
+// upper half of the 2 N values, the others the lower half.
+template <int N, int H>
+__device__ __forceinline__ void reduce_scatter_step(double* w) {
+    const bool up = (wave_lane() & H) != 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) w[i] = (up ? w[i + N] : w[i]) + lane_xor_f64<H>(up ? w[i] : w[i + N]);
+}
+
 // Block reduction of NV <= 64 doubles per thread, fixed order.  Inside a
 // wave a butterfly reduce-scatter halves the values a lane carries at every
-// step (63 exchanges for any NV instead of 6 * NV), leaving the wave total of
-// value l in lane l; the block then adds the wave totals in wave order.
-// Result in s_out[0..NV) after the call.
+// step (63 exchanges for any NV instead of 6 NV), the steps with the most
+// exchanges between lanes of one quad or row, which need no LDS (all of them
+// through LDS took the backward of 50,000 pairs 3 us longer); the block then
+// adds the wave totals in wave order.  Result in s_out[0..NV).
 template <int NV>
-__device__ __forceinline__ void block_reduce(double* v, double* s_red, double* s_out) {
+__device__ __forceinline__ void block_reduce(const double* v, double* s_red, double* s_out) {
     static_assert(NV <= 64, "at most 64 values");
     const int lane = wave_lane();
     const int wid = threadIdx.x / kWave;
     const int nw = blockDim.x / kWave;
-    double w[32];
+    double w[64];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
-        const double lo = i < NV ? v[i] : 0.0;
-        const double hi = i + 32 < NV ? v[i + 32] : 0.0;
-        const bool up = (lane & 32) != 0;
-        const double send = up ? lo : hi;
-        w[i] = (up ? hi : lo) + __shfl_xor(send, 32);
-    }
-#pragma unroll
-    for (int h = 16; h >= 1; h >>= 1) {
-        const bool up = (lane & h) != 0;
-#pragma unroll
-        for (int i = 0; i < h; ++i) {
-            const double send = up ? w[i] : w[i + h];
-            w[i] = (up ? w[i + h] : w[i]) + __shfl_xor(send, h);
-        }
-    }
-    if (lane < NV) s_red[wid * NV + lane] = w[0];
+    for (int i = 0; i < 64; ++i) w[i] = i < NV ? v[i] : 0.0;
+    reduce_scatter_step<32, 1>(w);
+    reduce_scatter_step<16, 2>(w);
+    reduce_scatter_step<8, 8>(w);
+    reduce_scatter_step<4, 4>(w);
+    reduce_scatter_step<2, 16>(w);
+    reduce_scatter_step<1, 32>(w);
+    // this lane's value
+    const int i = (lane & 1) * 32 + (lane >> 1 & 1) * 16 + (lane >> 3 & 1) * 8 + (lane >> 2 & 1) * 4 +
+                  (lane >> 4 & 1) * 2 + (lane >> 5);
+    if (i < NV) s_red[wid * NV + i] = w[0];
     __syncthreads();
     if ((int)threadIdx.x < NV) {
         double s = 0.0;
@@ -558,6 +589,19 @@ __device__ __forceinline__ void block_reduce_quad(const float* v, float* s_t, do
     __syncthreads();
 }
 
+// Fixed-order float64 sum over the block: a wave butterfly (every lane ends
+// with the same value: each stage adds the same two numbers in both lanes),
+// then the wave totals in wave order.  s_w holds one double per wave.
+__device__ __forceinline__ double block_sum_f64(double v, double* s_w) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (wave_lane() == 0) s_w[threadIdx.x / kWave] = v;
+    __syncthreads();
+    double sum = 0.0;
+    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) sum += s_w[w];
+    return sum;
+}
+
 struct ResArgs {
     int32_t n;
     int32_t n_kf;
@@ -566,6 +610,11 @@ struct ResArgs {
     const int32_t* kf_idx;
     const float* kf_T;
     const fl_sim3* S;
+    const double* xi;     // forward: S = exp(xi) S0 (S is then an output); backward: gradient with respect to xi
+    const double* S0;
+    fl_sim3* S_out;
+    const double* scale;  // backward with xi: device factor of the gradient, may be null
+    double* gxi;          // backward with xi: [7]
     float fx, fy, cx, cy;
     float delta;
     double grad_scale;
@@ -596,47 +645,87 @@ __device__ __forceinline__ bool load_pair(const ResArgs& a, int i, float& x, flo
     return true;
 }
 
-// Last-block-done: true in the one block that finishes last (all blocks'
-// partials are then visible to it).
-__device__ __forceinline__ bool last_block(uint32_t* done, unsigned n_blocks) {
+// The block's NV sums (s_out) join the launch's: they go to the block's row
+// of partials, and in the block that finishes last (true is returned there,
+// in every thread) the rows are added into s_out, thread (c, seg) taking rows
+// seg, seg + SEG, ... of value c and the segments in order.  The partials are
+// stored and loaded at device scope and each block counts itself once its
+// stores are complete, so no cache is written back or invalidated: a release
+// fence per block wrote back the L2's dirty lines, the pairs' outputs among
+// them.  s_seg holds kResBlock doubles.
+template <int NV>
+__device__ __forceinline__ bool finish_sums(const ResArgs& a, double* s_out, double* s_seg) {
     __shared__ int s_last;
-    __syncthreads();   // every wave's partial is written before thread 0 releases
-    if (threadIdx.x == 0) {
-        __threadfence();
-        s_last = atomicAdd(done, 1u) == n_blocks - 1;
-        if (s_last) __threadfence();   // acquire: see every block's partial (L2s of other XCDs)
-    }
-    __syncthreads();
-    return s_last != 0;
-}
-
-// Sum `rows` partials of NV doubles (row stride kNAcc) in row order into
-// s_out[0..NV): rows are staged through LDS in chunks by the whole block so
-// the loads are issued in parallel, then column i is summed by thread i.
-template <int NV, int MAXR>
-__device__ __forceinline__ void sum_partials(const double* part, int rows, double* s_chunk, double* s_out) {
-    double acc = 0.0;
-    for (int r0 = 0; r0 < rows; r0 += MAXR) {
-        const int nr = min(MAXR, rows - r0);
-        for (int i = threadIdx.x; i < nr * NV; i += blockDim.x) {
-            const int r = i / NV, c = i - r * NV;
-            s_chunk[i] = part[(int64_t)(r0 + r) * kNAcc + c];
+    const int tid = threadIdx.x, nb = gridDim.x;
+    if (nb > 1) {
+        if (tid < NV)
+            __hip_atomic_store(&a.partial[(int64_t)blockIdx.x * kNAcc + tid], s_out[tid], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's partials have arrived
+        __syncthreads();
+        if (tid == 0)
+            s_last = __hip_atomic_fetch_add(a.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb - 1;
+        __syncthreads();
+        if (!s_last) return false;
+        constexpr int SEG = kResBlock / NV;
+        const int c = tid % NV, seg = tid / NV;
+        if (seg < SEG) {
+            double v = 0.0;
+            const double* p = a.partial + c;
+            int r = seg;
+            for (; r + 7 * SEG < nb; r += 8 * SEG) {
+                double x[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    x[q] = __hip_atomic_load(p + (int64_t)(r + q * SEG) * kNAcc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v += x[q];
+            }
+            double x[7];
+#pragma unroll
+            for (int q = 0; q < 7; ++q)
+                x[q] = r + q * SEG < nb ? __hip_atomic_load(p + (int64_t)(r + q * SEG) * kNAcc, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT) : 0.0;
+#pragma unroll
+            for (int q = 0; q < 7; ++q) v += x[q];
+            s_seg[seg * NV + c] = v;
         }
         __syncthreads();
-        if ((int)threadIdx.x < NV)
-            for (int r = 0; r < nr; ++r) acc += s_chunk[r * NV + threadIdx.x];
+        if constexpr (NV == 1) {
+            if (tid < kWave) {   // 256 segments
+                double v = (s_seg[tid] + s_seg[tid + 64]) + (s_seg[tid + 128] + s_seg[tid + 192]);
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+                if (tid == 0) s_out[0] = v;
+            }
+        } else if (tid < NV) {
+            double v = 0.0;
+#pragma unroll
+            for (int q = 0; q < SEG; ++q) v += s_seg[q * NV + tid];
+            s_out[tid] = v;
+        }
+        if (tid == 0) *a.done = 0;
         __syncthreads();
     }
-    if ((int)threadIdx.x < NV) s_out[threadIdx.x] = acc;
-    __syncthreads();
+    return true;
 }
 
 __global__ __launch_bounds__(kResBlock) void residual_fwd_kernel(ResArgs a) {
-    __shared__ double s_red[(kResBlock / kWave) * 1];
+    __shared__ double s_wave[kResBlock / kWave];
     __shared__ double s_out[1];
-    __shared__ double s_chunk[32 * 1];
-    const fl_sim3 S = *a.S;
-    double acc[1] = {0.0};
+    __shared__ double s_seg[kResBlock];
+    __shared__ fl_sim3 s_S;
+    if (a.xi) {   // every block composes S for itself; block 0 hands it out
+        if (threadIdx.x == 0) {
+            sim3_to_f32(sim3_mul(sim3_exp(a.xi), sim3_load(a.S0)), &s_S);
+            if (blockIdx.x == 0) *a.S_out = s_S;
+        }
+    } else if (threadIdx.x == 0) {
+        s_S = *a.S;
+    }
+    __syncthreads();
+    const fl_sim3 S = s_S;
+    double loss = 0.0;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < a.n; i += gridDim.x * blockDim.x) {
         float x, y, z, uo, vo;
         const float* T;
@@ -652,24 +741,22 @@ __global__ __launch_bounds__(kResBlock) void residual_fwd_kernel(ResArgs a) {
             a.r[2 * (int64_t)i + 1] = t.r1;
         }
         if (a.w) a.w[i] = t.w;
-        acc[0] += (double)t.rho;
+        loss += (double)t.rho;
     }
-    block_reduce<1>(acc, s_red, s_out);
-    if (threadIdx.x == 0) a.partial[blockIdx.x * kNAcc] = s_out[0];
-    if (last_block(a.done, gridDim.x)) {
-        sum_partials<1, 32>(a.partial, gridDim.x, s_chunk, s_out);
-        if (threadIdx.x == 0) {
-            *a.loss = s_out[0];
-            *a.done = 0;
-        }
-    }
+    const double sum = block_sum_f64(loss, s_wave);
+    if (threadIdx.x == 0) s_out[0] = sum;
+    __syncthreads();
+    if (finish_sums<1>(a, s_out, s_seg) && threadIdx.x == 0) *a.loss = s_out[0];
 }
+
+// scale J_l(xi)^T g by one wave (the definition at sim3_grad_xi_kernel below).
+__device__ __forceinline__ void sim3_grad_xi_wave(const double* xi, const double* g, const double* scale, double* out);
 
 template <bool INV>
 __global__ __launch_bounds__(kResBlock) void residual_bwd_kernel(ResArgs a) {
     __shared__ double s_red[(kResBlock / kWave) * 35];
     __shared__ double s_out[35];
-    __shared__ double s_chunk[32 * 35];
+    __shared__ double s_seg[kResBlock];
     const fl_sim3 S = *a.S;
     double acc[35];
 #pragma unroll
@@ -683,13 +770,13 @@ __global__ __launch_bounds__(kResBlock) void residual_bwd_kernel(ResArgs a) {
         if (t.valid) accumulate(t, acc);
     }
     block_reduce<35>(acc, s_red, s_out);
-    if ((int)threadIdx.x < 35) a.partial[blockIdx.x * kNAcc + threadIdx.x] = s_out[threadIdx.x];
-    if (last_block(a.done, gridDim.x)) {
-        sum_partials<35, 32>(a.partial, gridDim.x, s_chunk, s_out);
-        if (threadIdx.x < 7) a.g[threadIdx.x] = a.grad_scale * s_out[threadIdx.x];
-        else if ((int)threadIdx.x < 35 && a.H) a.H[threadIdx.x - 7] = s_out[threadIdx.x];
-        if (threadIdx.x == 0) *a.done = 0;
+    if (!finish_sums<35>(a, s_out, s_seg)) return;
+    if (a.gxi) {
+        if (threadIdx.x < kWave) sim3_grad_xi_wave(a.xi, s_out, a.scale, a.gxi);
+        return;
     }
+    if (threadIdx.x < 7) a.g[threadIdx.x] = a.grad_scale * s_out[threadIdx.x];
+    else if ((int)threadIdx.x < 35 && a.H) a.H[threadIdx.x - 7] = s_out[threadIdx.x];
 }
 
 __global__ void sim3_exp_mul_kernel(const double* __restrict__ xi, const double* __restrict__ S_in,
@@ -710,56 +797,61 @@ __global__ void sim3_exp_mul_kernel(const double* __restrict__ xi, const double*
 //   ad(xi) = [ [w]x        0          0 ]
 //            [ [u]x   [w]x + sig I   -u ]
 //            [ 0           0          0 ].
-// The series is summed in float64 until a term's largest entry falls below
-// 1e-18 of the sum's (at most 64 terms; |w| <= pi and |sig| of order one
-// converge in about 25).  out = scale * J_l^T g (scale: device, may be null).
-__global__ void sim3_grad_xi_kernel(const double* __restrict__ xi, const double* __restrict__ g,
-                                    const double* __restrict__ scale, double* __restrict__ out) {
-    if (threadIdx.x != 0) return;
-    double A[49];
-    for (int i = 0; i < 49; ++i) A[i] = 0.0;
-    const double w0 = xi[0], w1 = xi[1], w2 = xi[2], u0 = xi[3], u1 = xi[4], u2 = xi[5], sg = xi[6];
-    auto set_hat = [&](int r, int c, double a0, double a1, double a2) {   // [a]x at block (r, c)
-        A[(r + 0) * 7 + c + 1] = -a2;
-        A[(r + 0) * 7 + c + 2] = a1;
-        A[(r + 1) * 7 + c + 0] = a2;
-        A[(r + 1) * 7 + c + 2] = -a0;
-        A[(r + 2) * 7 + c + 0] = -a1;
-        A[(r + 2) * 7 + c + 1] = a0;
+// Only J_l^T g is wanted, so the series runs on the vector: v_0 = g, v_k =
+// ad(xi)^T v_{k-1} / (k + 1), 49 products a term where the matrix took 343.
+// It is summed in float64 until a term's largest entry falls below 1e-18 of
+// the sum's and the terms can only shrink from there (at most 64 terms; |w|
+// <= pi and |sig| of order one converge in about 25).  out = scale * J_l^T g
+// (scale: device, may be null).  One wave: lane c < 7 holds column c of
+// ad(xi) and entry c of v (one lane with the matrices in scratch memory took
+// 60 us; this takes 2).
+__device__ __forceinline__ void sim3_grad_xi_wave(const double* xi, const double* g, const double* scale, double* out) {
+    const int c = min(wave_lane(), 7);   // lanes past 6 carry zeros
+    double x[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) x[i] = xi[i];
+    // column c of ad(xi), by its row blocks: [w]x column, then [u]x column
+    // (c < 3) or [w]x column + sig I (c < 6) or -u (c = 6), then 0
+    auto hat_col = [](double a0, double a1, double a2, int j, double* h) {
+        h[0] = j == 1 ? -a2 : j == 2 ? a1 : 0.0;
+        h[1] = j == 0 ? a2 : j == 2 ? -a0 : 0.0;
+        h[2] = j == 0 ? -a1 : j == 1 ? a0 : 0.0;
     };
-    set_hat(0, 0, w0, w1, w2);
-    set_hat(3, 0, u0, u1, u2);
-    set_hat(3, 3, w0, w1, w2);
-    for (int i = 3; i < 6; ++i) A[i * 7 + i] += sg;
-    A[3 * 7 + 6] = -u0;
-    A[4 * 7 + 6] = -u1;
-    A[5 * 7 + 6] = -u2;
-    // J = sum_k T_k with T_0 = I, T_k = A T_{k-1} / (k + 1)
-    double T[49], J[49], N[49];
-    for (int i = 0; i < 49; ++i) T[i] = J[i] = (i % 8 == 0) ? 1.0 : 0.0;
+    double W[3], U[3], A[6];
+    hat_col(x[0], x[1], x[2], c < 3 ? c : c - 3, W);
+    hat_col(x[3], x[4], x[5], c, U);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        A[i] = c < 3 ? W[i] : 0.0;
+        A[3 + i] = c < 3 ? U[i] : c < 6 ? W[i] + (c - 3 == i ? x[6] : 0.0) : c == 6 ? -x[3 + i] : 0.0;
+    }
+    double v = c < 7 ? g[c] : 0.0, sum = v;
+    // a bound of every |ad(xi)^T v| / |v|, largest entries: its largest column sum
+    double norm = 0.0;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) norm += fabs(A[i]);
+#pragma unroll
+    for (int off = 4; off > 0; off >>= 1) norm = fmax(norm, __shfl_xor(norm, off));
     for (int k = 1; k < 64; ++k) {
-        double tmax = 0.0, jmax = 0.0;
-        const double f = 1.0 / (double)(k + 1);
-        for (int r = 0; r < 7; ++r)
-            for (int c = 0; c < 7; ++c) {
-                double v = 0.0;
-                for (int m = 0; m < 7; ++m) v = fma(A[r * 7 + m], T[m * 7 + c], v);
-                N[r * 7 + c] = v * f;
-            }
-        for (int i = 0; i < 49; ++i) {
-            T[i] = N[i];
-            J[i] += N[i];
-            tmax = fmax(tmax, fabs(N[i]));
-            jmax = fmax(jmax, fabs(J[i]));
+        double n = 0.0;
+#pragma unroll
+        for (int r = 0; r < 6; ++r) n = fma(A[r], readlane_f64(v, r), n);   // row 6 of ad(xi) is 0
+        v = n * (1.0 / (double)(k + 1));
+        sum += v;
+        double tmax = fabs(v), smax = fabs(sum);
+#pragma unroll
+        for (int off = 4; off > 0; off >>= 1) {
+            tmax = fmax(tmax, __shfl_xor(tmax, off));
+            smax = fmax(smax, __shfl_xor(smax, off));
         }
-        if (tmax <= 1e-18 * jmax) break;
+        if (readlane_f64(tmax, 0) <= 1e-18 * readlane_f64(smax, 0) && readlane_f64(norm, 0) < (double)(k + 2)) break;
     }
-    const double sc = scale ? *scale : 1.0;
-    for (int c = 0; c < 7; ++c) {
-        double v = 0.0;
-        for (int r = 0; r < 7; ++r) v = fma(J[r * 7 + c], g[r], v);
-        out[c] = sc * v;
-    }
+    if (wave_lane() < 7) out[wave_lane()] = (scale ? *scale : 1.0) * sum;
+}
+
+__global__ __launch_bounds__(64) void sim3_grad_xi_kernel(const double* __restrict__ xi, const double* g,
+                                                          const double* __restrict__ scale, double* out) {
+    sim3_grad_xi_wave(xi, g, scale, out);   // out may be g
 }
 
 // S_inv = S^-1 = (R^T, -R^T t / s, 1 / s) in float64, and its float32 form.
@@ -870,19 +962,6 @@ __device__ __forceinline__ bool pair_error64(const double* S, const float* T, fl
 
 __device__ __forceinline__ double huber64(double e, double delta) {
     return e <= delta ? 0.5 * e * e : delta * e - 0.5 * delta * delta;
-}
-
-// Fixed-order float64 sum over the block: a wave butterfly (every lane ends
-// with the same value: each stage adds the same two numbers in both lanes),
-// then the wave totals in wave order.  s_w holds one double per wave.
-__device__ __forceinline__ double block_sum_f64(double v, double* s_w) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (wave_lane() == 0) s_w[threadIdx.x / kWave] = v;
-    __syncthreads();
-    double sum = 0.0;
-    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) sum += s_w[w];
-    return sum;
 }
 
 // S <- exp(d) S by the lanes of one wave: every lane holds the same step d

@@ -713,3 +713,35 @@ def test_two_sided_refinement_rejects_bad_arguments(ctx):
         with pytest.raises(fl.FlError) as ei:
             ctx.search_fuse_batched(b, ev.params, refine=ref)
         assert ei.value.code == code, (off, rounds, lm, ei.value)
+
+
+@pytest.mark.parametrize("n", [0, 1, 63, 256, 257, 2049, 14337, 262144, 262145])
+def test_residual_sums_over_every_grid_shape(ctx, n):
+    """One block and many, blocks with a few pairs, more rows of partials than
+    one round of loads takes, the largest grid and pairs beyond it: loss, g
+    and H against float64 to the bound of the other residual tests, and the
+    one-launch form of the autograd function against the separate calls: the
+    same float32 Sim3 to the bit and sums that differ by their float64 order
+    at most."""
+    d = synth.gen_c4(n=max(n, 1))
+    xyz, uv = d["xyz"][:n], d["uv"][:n]
+    xi, S_true = d["xi0"], d["S_true"]
+    S0, S32 = ctx.sim3_exp_mul(t(xi), t(S_true))
+    _, _, loss = ctx.residual_fwd(t(xyz), t(uv), None, None, S32, d["cam"], 2.45)
+    g, H = ctx.residual_bwd(t(xyz), t(uv), None, None, S32, d["cam"], 2.45)
+    if n:
+        S64 = S0.cpu().numpy()
+        L64 = R.forward(S64, xyz, uv, None, None, d["cam"], 2.45)[2]
+        g64, H64, _ = R.grad_hess(S64, xyz, uv, None, None, d["cam"], 2.45)
+        assert abs(loss.item() - L64) / L64 < REL
+        assert rel(g.cpu().numpy(), g64) < REL
+        assert rel(H.cpu().numpy(), R.H_upper(H64)) < REL
+    else:
+        assert loss.item() == 0.0 and not g.any() and not H.any()
+    scale = t(np.array([1.7]))
+    gx = ctx.sim3_grad_xi(t(xi), g, scale).cpu().numpy()
+    one32, one = ctx._residual_fwd_xi(t(xi), t(S_true), t(xyz), t(uv), None, None, d["cam"], 2.45)
+    gone = ctx._residual_bwd_xi(t(xi), scale, t(xyz), t(uv), None, None, S32, d["cam"], 2.45).cpu().numpy()
+    assert torch.equal(one32, S32)
+    assert abs(one.item() - loss.item()) <= 1e-14 * loss.item()
+    assert np.max(np.abs(gone - gx)) <= 1e-13 * np.max(np.abs(gx))
