@@ -246,8 +246,9 @@ class Context:
             pass
 
     def _stream(self, stream=None):
-        s = stream if stream is not None else torch.cuda.current_stream(self.device)
-        return ctypes.c_void_p(s.cuda_stream)
+        if stream is None:   # the handle itself: a Stream object costs 2 us to make
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(self.device.index))
+        return ctypes.c_void_p(stream.cuda_stream)
 
     # -- grid ------------------------------------------------------------
     def build_grid(self, kp_xy: torch.Tensor, cam8, params, stream=None):
