@@ -177,7 +177,7 @@ struct alignas(16) BatchHdr {
     double* event_S;            // [n_events][13] caller's, in/out
     fl_sim3* event_S32_out;     // caller's (may be null)
     int32_t* event_n_matched;   // caller's (may be null)
-    unsigned long long* refine_rows;   // [2][n_events * refine_blocks][2 * kNAccPad] tagged partial-sum words
+    unsigned long long* refine_rows;   // [2][n_events * refine_blocks][kRefWords] tagged partial-sum words
     // two-sided refinement (caller's; null without it): points of the other
     // side observed through S^-1 in keyframes of their own
     const float* inv_xyz;       // [n][3]

@@ -67,12 +67,12 @@ constexpr int64_t kCrMaxEntries = 1 << 25;   // entries of one of the four block
 constexpr int cr_rows(int nt) { return nt >= 14 ? 2 : nt >= 11 ? 4 : 5; }
 constexpr int cr_groups(int nt) { return (3 * nt + 1 + cr_rows(nt) - 1) / cr_rows(nt); }
 
-// 1 / sqrt(d) from the hardware estimate and two Newton steps.
+// 1 / sqrt(d) from the hardware estimate r (relative error below 2^-22) and
+// one step of third order, r (1 + e / 2 + 3 e^2 / 8) with e = 1 - d r^2.
 __device__ __forceinline__ double cr_rsqrt(double d) {
-    double r = __builtin_amdgcn_rsq(d);
-#pragma unroll
-    for (int it = 0; it < 2; ++it) r = fma(0.5 * r, fma(-d * r, r, 1.0), r);
-    return r;
+    const double r = __builtin_amdgcn_rsq(d);
+    const double e = fma(-d * r, r, 1.0);
+    return fma(r * e, fma(0.375, e, 0.5), r);
 }
 
 // Cholesky of the 16 x 16 tile c (accumulator layout) by one wave, four

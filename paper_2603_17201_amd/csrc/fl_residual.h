@@ -38,15 +38,14 @@ struct RecipTable {
 };
 __device__ constexpr RecipTable kRecip{};
 
-// 1/x to within about one ulp: the hardware estimate refined by two Newton
-// steps (cheaper on the serial path of a step than a correctly rounded
-// division).
+// 1/x to within about one ulp: the hardware estimate r (relative error below
+// 2^-22) and one step of third order, r (1 + e + e^2) with e = 1 - x r
+// (cheaper on the serial path of a step than a correctly rounded division or
+// two Newton steps).
 __device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
 }
 
 // The first NT terms of e^sigma = sum_k sigma^k / k! and of
@@ -466,21 +465,41 @@ __device__ __forceinline__ double lane_xor_f64(double x) {
     else return __shfl_xor(x, H);
 }
 
-// One step of the reduce-scatter below: lanes whose bit H is set keep the
-// upper half of the 2 N values, the others the lower half.
+// lo + its value in lane l ^ H in lanes whose bit H is clear, hi + its value
+// there in the others.  Across rows the swap instructions of gfx950 hand both
+// sums' operands over without a select (three instructions); inside a row the
+// operands are selected and one permuted.
+template <int H>
+__device__ __forceinline__ double scatter_add(double lo, double hi) {
+    if constexpr (H == 16 || H == 32) {
+        const long long a = __double_as_longlong(lo), b = __double_as_longlong(hi);
+        const auto swap = [](uint32_t x, uint32_t y) {
+            if constexpr (H == 16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        };
+        const auto l = swap((uint32_t)a, (uint32_t)b), h = swap((uint32_t)(a >> 32), (uint32_t)(b >> 32));
+        return __longlong_as_double(((long long)h[0] << 32) | (long long)l[0]) +
+               __longlong_as_double(((long long)h[1] << 32) | (long long)l[1]);
+    } else {
+        const bool up = (wave_lane() & H) != 0;
+        return (up ? hi : lo) + lane_xor_f64<H>(up ? lo : hi);
+    }
+}
+
+// One step of a reduce-scatter: of N values, lanes whose bit H is set keep the
+// last N / 2, the others the first (N + 1) / 2 (w padded with a zero).
 template <int N, int H>
 __device__ __forceinline__ void reduce_scatter_step(double* w) {
-    const bool up = (wave_lane() & H) != 0;
+    constexpr int K = (N + 1) / 2;
 #pragma unroll
-    for (int i = 0; i < N; ++i) w[i] = (up ? w[i + N] : w[i]) + lane_xor_f64<H>(up ? w[i] : w[i + N]);
+    for (int i = 0; i < K; ++i) w[i] = scatter_add<H>(w[i], K + i < N ? w[K + i] : 0.0);
 }
 
 // Block reduction of NV <= 64 doubles per thread, fixed order.  Inside a
 // wave a butterfly reduce-scatter halves the values a lane carries at every
-// step (63 exchanges for any NV instead of 6 NV), the steps with the most
-// exchanges between lanes of one quad or row, which need no LDS (all of them
-// through LDS took the backward of 50,000 pairs 3 us longer); the block then
-// adds the wave totals in wave order.  Result in s_out[0..NV).
+// step (63 exchanges for any NV instead of 6 NV), none of them through LDS,
+// the cheapest first; the block then adds the wave totals in wave order.
+// Result in s_out[0..NV).
 template <int NV>
 __device__ __forceinline__ void block_reduce(const double* v, double* s_red, double* s_out) {
     static_assert(NV <= 64, "at most 64 values");
@@ -490,15 +509,15 @@ __device__ __forceinline__ void block_reduce(const double* v, double* s_red, dou
     double w[64];
 #pragma unroll
     for (int i = 0; i < 64; ++i) w[i] = i < NV ? v[i] : 0.0;
-    reduce_scatter_step<32, 1>(w);
-    reduce_scatter_step<16, 2>(w);
-    reduce_scatter_step<8, 8>(w);
-    reduce_scatter_step<4, 4>(w);
-    reduce_scatter_step<2, 16>(w);
-    reduce_scatter_step<1, 32>(w);
+    reduce_scatter_step<64, 16>(w);
+    reduce_scatter_step<32, 32>(w);
+    reduce_scatter_step<16, 1>(w);
+    reduce_scatter_step<8, 2>(w);
+    reduce_scatter_step<4, 8>(w);
+    reduce_scatter_step<2, 4>(w);
     // this lane's value
-    const int i = (lane & 1) * 32 + (lane >> 1 & 1) * 16 + (lane >> 3 & 1) * 8 + (lane >> 2 & 1) * 4 +
-                  (lane >> 4 & 1) * 2 + (lane >> 5);
+    const int i = (lane >> 4 & 1) * 32 + (lane >> 5) * 16 + (lane & 1) * 8 + (lane >> 1 & 1) * 4 + (lane >> 3 & 1) * 2 +
+                  (lane >> 2 & 1);
     if (i < NV) s_red[wid * NV + i] = w[0];
     __syncthreads();
     if ((int)threadIdx.x < NV) {
@@ -509,84 +528,61 @@ __device__ __forceinline__ void block_reduce(const double* v, double* s_red, dou
     __syncthreads();
 }
 
-// The same sums in float32, for a thread's few register-held pairs (it adds
-// at most two terms before they are widened to float64).
-__device__ __forceinline__ void accumulate_f32(const PairTerm& t, float* acc) {
-    const float w = t.w, r0 = t.r0, r1 = t.r1;
-#pragma unroll
-    for (int i = 0; i < 7; ++i) acc[i] += w * fmaf(t.J[0][i], r0, t.J[1][i] * r1);
-    int k = 7;
-#pragma unroll
-    for (int i = 0; i < 7; ++i)
-#pragma unroll
-        for (int j = i; j < 7; ++j) acc[k++] += w * fmaf(t.J[0][i], t.J[0][j], t.J[1][i] * t.J[1][j]);
-}
-
-// Fixed-order block reduction for the refinement.  The four lanes of each
-// quad first add their values pairwise in float32 (DPP quad permutations:
-// lanes 2i and 2i + 1 swap halves and add, then lanes 4i + {0, 1} and
-// 4i + {2, 3} swap quarters and add), so each lane keeps NV / 4 of the quad's
-// sums.  Those go through LDS column-major (column stride NT / 4 + 1), kSeg
-// NV threads each add one of kSeg segments of a column in float64 and NV
-// threads add the segments pairwise.  s_t holds NV (NT / 4 + 1) floats, s_q
-// kSeg NV doubles; the block has NT threads (whole waves), a multiple of
-// 4 kSeg and at least kSeg NV; NV is a multiple of 4.  Result in
-// s_out[0..NV) after the call.
+// Fixed-order sums of a wave for the refinement.  The four lanes of each quad
+// first add their NV values pairwise in float32 (DPP quad permutations: lanes
+// 2i and 2i + 1 swap halves and add, then lanes 4i + {0, 1} and 4i + {2, 3}
+// swap quarters and add), so each lane keeps NV / 4 of the quad's sums; those
+// are widened, and a reduce-scatter over the 16 quads adds them in float64.
+// On return value `idx` of the wave's NV sums is v in the lane that got it
+// (idx < 0: none).
 constexpr int kSeg = 8;
-
-static_assert(kSeg == 4 || kSeg == 8, "segments are added as a pairwise tree of 4 or 8");
-
-template <int NV>
-__device__ __forceinline__ double add_segments(const double* s_q, int c) {
-    const double a = (s_q[c] + s_q[NV + c]) + (s_q[2 * NV + c] + s_q[3 * NV + c]);
-    if constexpr (kSeg == 4) return a;
-    else return a + ((s_q[4 * NV + c] + s_q[5 * NV + c]) + (s_q[6 * NV + c] + s_q[7 * NV + c]));
-}
 
 template <int CTRL>
 __device__ __forceinline__ float quad_perm_f32(float x) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, false));
 }
 
-template <int NV, int NT>
-__device__ __forceinline__ void block_reduce_quad(const float* v, float* s_t, double* s_q, double* s_out) {
-    static_assert(NV % 4 == 0 && NT % (4 * kSeg) == 0 && NT >= kSeg * NV && NT % kWave == 0, "block shape");
-    constexpr int H = NV / 2, Q = NV / 4, NQ = NT / 4, ld = NQ + 1, per = NQ / kSeg;
-    const int tid = threadIdx.x;
-    const bool odd = tid & 1, hi = tid & 2;
+template <int NV>
+__device__ __forceinline__ double wave_reduce_quad(const float* v, int& idx) {
+    static_assert(NV == 36, "nine values a lane after the quads");
+    constexpr int H = NV / 2, Q = NV / 4;
+    const int l = wave_lane();
+    const bool odd = l & 1, hi = l & 2;
+    // both lanes' sums of both halves, then the one to keep (a permuted add
+    // each; selecting first costs waits between a select and its permutation)
     float h[H];
 #pragma unroll
     for (int j = 0; j < H; ++j) {
-        const float keep = odd ? v[j + H] : v[j];
-        const float send = odd ? v[j] : v[j + H];
-        h[j] = keep + quad_perm_f32<0xB1>(send);   // quad_perm [1, 0, 3, 2]
+        const float a = v[j] + quad_perm_f32<0xB1>(v[j]);   // quad_perm [1, 0, 3, 2]
+        const float b = v[j + H] + quad_perm_f32<0xB1>(v[j + H]);
+        h[j] = odd ? b : a;
     }
-    float q[Q];
+    double w[Q];
 #pragma unroll
     for (int j = 0; j < Q; ++j) {
-        const float keep = hi ? h[j + Q] : h[j];
-        const float send = hi ? h[j] : h[j + Q];
-        q[j] = keep + quad_perm_f32<0x4E>(send);   // quad_perm [2, 3, 0, 1]
+        const float a = h[j] + quad_perm_f32<0x4E>(h[j]);   // quad_perm [2, 3, 0, 1]
+        const float b = h[j + Q] + quad_perm_f32<0x4E>(h[j + Q]);
+        w[j] = (double)(hi ? b : a);
     }
-    const int base = (odd ? H : 0) + (hi ? Q : 0);
-#pragma unroll
-    for (int j = 0; j < Q; ++j) s_t[(base + j) * ld + (tid >> 2)] = q[j];
-    __syncthreads();
-    if (tid < kSeg * NV) {
-        const int c = tid % NV, sg = tid / NV;
-        const float* col = s_t + c * ld + sg * per;
-        double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-        for (int r = 0; r + 1 < per; r += 2) {
-            a0 += (double)col[r];
-            a1 += (double)col[r + 1];
-        }
-        if (per & 1) a0 += (double)col[per - 1];
-        s_q[sg * NV + c] = a0 + a1;
-    }
-    __syncthreads();
-    if (tid < NV) s_out[tid] = add_segments<NV>(s_q, tid);
-    __syncthreads();
+    reduce_scatter_step<9, 16>(w);   // 5 left (4 in the upper lanes)
+    reduce_scatter_step<5, 32>(w);   // 3 (2)
+    reduce_scatter_step<3, 8>(w);    // 2 (1)
+    reduce_scatter_step<2, 4>(w);    // 1
+    const int n1 = l & 16 ? 4 : 5;                    // this lane's values after each step
+    const int n2 = l & 32 ? n1 - 3 : 3;
+    const int n3 = l & 8 ? n2 - 2 : min(n2, 2);
+    const int at = (l & 16 ? 5 : 0) + (l & 32 ? 3 : 0) + (l & 8 ? 2 : 0) + (l & 4 ? 1 : 0);
+    idx = (l & 4 ? 1 : 0) < n3 ? (odd ? H : 0) + (hi ? Q : 0) + at : -1;
+    return w[0];
+}
+
+// The kSeg segments (or wave totals) of value c, NV values each, added
+// pairwise.
+static_assert(kSeg == 8, "a pairwise tree of 8");
+template <int NV>
+__device__ __forceinline__ double add_segments(const double* s_q, int c) {
+    const double a = (s_q[c] + s_q[NV + c]) + (s_q[2 * NV + c] + s_q[3 * NV + c]);
+    return a + ((s_q[4 * NV + c] + s_q[5 * NV + c]) + (s_q[6 * NV + c] + s_q[7 * NV + c]));
 }
 
 // Fixed-order float64 sum over the block: a wave butterfly (every lane ends
@@ -889,49 +885,79 @@ __global__ void gn_step_kernel(const double* __restrict__ g, const double* __res
 
 constexpr unsigned kSpinLimit = 1u << 22;
 
-// One pair's terms at S (float32), added when the pair is in front of its
-// keyframe; acc[35] counts the pairs added.
-__device__ __forceinline__ void refine_accumulate_f32(const float* T, float fx, float fy, float cx, float cy, float x,
-                                                      float y, float z, float uo, float vo, const fl_sim3& S,
-                                                      float delta, float* acc) {
-    PairTerm t;
-    pair_term(S.sR, S.t, T, fx, fy, cx, cy, x, y, z, uo, vo, delta, true, t);
-    if (t.valid) {
-        accumulate_f32(t, acc);
-        acc[35] += 1.0f;
+// One pair's terms of the refinement at S (its float32 form A, t), added to
+// acc when the pair is in front of its keyframe: acc[0..6] w J^T r, acc[7..34]
+// w J^T J (upper, row by row), acc[35] the pairs added.  The arithmetic of
+// pair_term with fused multiply-adds throughout, the weight from the squared
+// error and w J formed once (150 instructions a pair where separate products
+// and sums took 250: two waves a SIMD issue them for 0.9 us a step instead of
+// 1.3).  INV as in pair_term: A, t are S^-1's, the pair is a point of the
+// current side.
+// No branch: a pair that is not there (has false) or not in front of its
+// keyframe adds zeros.  FIRST: acc is written, not added to.
+template <bool INV, bool FIRST = false>
+__device__ __forceinline__ void refine_pair_f32(const float* A, const float* t, const float* T, float fx, float fy,
+                                                float cx, float cy, float x, float y, float z, float uo, float vo,
+                                                float delta, float* acc, bool has = true) {
+    float p0 = fmaf(A[0], x, fmaf(A[1], y, fmaf(A[2], z, t[0])));
+    float p1 = fmaf(A[3], x, fmaf(A[4], y, fmaf(A[5], z, t[1])));
+    float p2 = fmaf(A[6], x, fmaf(A[7], y, fmaf(A[8], z, t[2])));
+    float q0 = fmaf(T[0], p0, fmaf(T[1], p1, fmaf(T[2], p2, T[9])));
+    float q1 = fmaf(T[3], p0, fmaf(T[4], p1, fmaf(T[5], p2, T[10])));
+    const float q2 = fmaf(T[6], p0, fmaf(T[7], p1, fmaf(T[8], p2, T[11])));
+    const bool in = has && q2 > 0.0f;
+    // zeros in place of a point that is not finite, so that its terms are
+    p0 = in ? p0 : 0.0f;
+    p1 = in ? p1 : 0.0f;
+    p2 = in ? p2 : 0.0f;
+    q0 = in ? q0 : 0.0f;
+    q1 = in ? q1 : 0.0f;
+    const float iz = in ? __builtin_amdgcn_rcpf(q2) : 0.0f;   // within 1 ulp
+    const float a0 = fx * iz, b1 = fy * iz;
+    const float r0 = fmaf(a0, q0, cx) - uo;
+    const float r1 = fmaf(b1, q1, cy) - vo;
+    const float e2 = fmaf(r0, r0, r1 * r1);
+    const float w = !in ? 0.0f : e2 <= delta * delta ? 1.0f : delta * __builtin_amdgcn_rsqf(e2);   // within 1 ulp
+    const float a2 = -a0 * (q0 * iz), b2 = -b1 * (q1 * iz);
+    float J[2][7], W[2][7];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const float d0 = r ? b1 : a0, d2 = r ? b2 : a2;
+        float m0 = fmaf(d2, T[6], d0 * T[3 * r]);
+        float m1 = fmaf(d2, T[7], d0 * T[3 * r + 1]);
+        float m2 = fmaf(d2, T[8], d0 * T[3 * r + 2]);
+        float x0 = p0, x1 = p1, x2 = p2;   // the point the perturbation acts on
+        if (INV) {
+            const float i0 = -fmaf(m0, A[0], fmaf(m1, A[3], m2 * A[6]));
+            const float i1 = -fmaf(m0, A[1], fmaf(m1, A[4], m2 * A[7]));
+            const float i2 = -fmaf(m0, A[2], fmaf(m1, A[5], m2 * A[8]));
+            m0 = i0;
+            m1 = i1;
+            m2 = i2;
+            x0 = in ? x : 0.0f;
+            x1 = in ? y : 0.0f;
+            x2 = in ? z : 0.0f;
+        }
+        J[r][0] = fmaf(x1, m2, -(x2 * m1));
+        J[r][1] = fmaf(x2, m0, -(x0 * m2));
+        J[r][2] = fmaf(x0, m1, -(x1 * m0));
+        J[r][3] = m0;
+        J[r][4] = m1;
+        J[r][5] = m2;
+        J[r][6] = fmaf(m0, x0, fmaf(m1, x1, m2 * x2));
+#pragma unroll
+        for (int i = 0; i < 7; ++i) W[r][i] = w * J[r][i];
     }
-}
-
-// A pair of the other direction (a point of the current side observed in a
-// loop-side keyframe through S^-1, Si = float32 form of S^-1): its terms with
-// respect to the left perturbation of S, added when the point is in front of
-// that keyframe.  The keyframe's pose and intrinsics come from LDS (16 floats
-// per keyframe: T, fx, fy, cx, cy) or from the caller's arrays.
-__device__ __forceinline__ void refine_inverse_f32(const BatchHdr& h, const float* s_ikf, bool lds, int k, float x,
-                                                   float y, float z, float uo, float vo, const fl_sim3& Si,
-                                                   float delta, float* acc) {
-    const float* T;
-    float fx, fy, cx, cy;
-    if (lds) {
-        T = s_ikf + 16 * k;
-        fx = T[12];
-        fy = T[13];
-        cx = T[14];
-        cy = T[15];
-    } else {
-        T = h.inv_T + 12 * (int64_t)k;
-        const float* c = h.inv_cam + 4 * (int64_t)k;
-        fx = c[0];
-        fy = c[1];
-        cx = c[2];
-        cy = c[3];
+    int k = 7;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+        acc[i] = fmaf(W[0][i], r0, FIRST ? W[1][i] * r1 : fmaf(W[1][i], r1, acc[i]));
+#pragma unroll
+        for (int j = i; j < 7; ++j, ++k)
+            acc[k] = fmaf(W[0][i], J[0][j], FIRST ? W[1][i] * J[1][j] : fmaf(W[1][i], J[1][j], acc[k]));
     }
-    PairTerm t;
-    pair_term<true>(Si.sR, Si.t, T, fx, fy, cx, cy, x, y, z, uo, vo, delta, true, t);
-    if (t.valid) {
-        accumulate_f32(t, acc);
-        acc[35] += 1.0f;
-    }
+    const float one = in ? 1.0f : 0.0f;
+    acc[35] = FIRST ? one : acc[35] + one;
 }
 
 // A pair's reprojection error at a float64 Sim3 (13 doubles: R, t, s), in
@@ -964,19 +990,76 @@ __device__ __forceinline__ double huber64(double e, double delta) {
     return e <= delta ? 0.5 * e * e : delta * e - 0.5 * delta * delta;
 }
 
-// S <- exp(d) S by the lanes of one wave: every lane holds the same step d
-// and evaluates the exponential's coefficients; lane l < 13 then computes
-// entry l of the product (R row-major, t, s) from the rows of exp(d)
-// (R_d = I + a W + b W^2 and V = c0 I + c1 W + c2 W^2 with W = [omega]x and
-// W^2 = omega omega^T - |omega|^2 I) and from S in LDS, writes it to S64 and
-// its float32 pose to o32; with inv32 the lanes then write the float32 pose
-// of the product's inverse (R^T / s, -R^T t / s).  S64 is read by every lane
-// before any lane writes it (one wave: its LDS accesses are in order).
-__device__ __forceinline__ void compose_exp_lanes(const double* d, double* S64, fl_sim3* o32, fl_sim3* inv32) {
+// Coefficient tables of the exponential's series, entry k of lane l's
+// polynomial at [16 k + l]: lanes 0..6 I_l(sigma) = sum_k sigma^k / (k! (l + k
+// + 1)), lane 7 e^sigma = sum_k sigma^k / k!, lanes 8 and 9 sin(th) / th and
+// (1 - cos(th)) / th^2 in th^2, other lanes 0.  With |sigma| below 1e-2 and
+// th^2 below 1e-4 nine (four) terms leave less than 0.01^9 / 9! < 3e-24.
+constexpr int kExpTerms = 9;
+struct ExpTable {
+    double v[16 * kExpTerms];
+    constexpr ExpTable() : v() {
+        double f = 1.0;   // 1 / k!
+        for (int k = 0; k < kExpTerms; ++k) {
+            if (k > 0) f = f / (double)k;
+            for (int l = 0; l < 7; ++l) v[16 * k + l] = f / (double)(l + k + 1);
+            v[16 * k + 7] = f;
+        }
+        const double a[4] = {1.0, -1.0 / 6.0, 1.0 / 120.0, -1.0 / 5040.0};
+        const double b[4] = {0.5, -1.0 / 24.0, 1.0 / 720.0, -1.0 / 40320.0};
+        for (int k = 0; k < 4; ++k) {
+            v[16 * k + 8] = a[k];
+            v[16 * k + 9] = b[k];
+        }
+    }
+};
+__device__ constexpr ExpTable kExpTable{};
+
+// S <- exp(d) S by the lanes of one wave, every lane holding the same step d:
+// for the usual Gauss-Newton step (rotation angle and |sigma| below 1e-2) the
+// lanes evaluate one series each (kExpTable, in LDS) and hand the ten values
+// round, for any other step every lane evaluates the full coefficients; lane l < 13 then computes entry l of the
+// product (R row-major, t, s) from the rows of exp(d) (R_d = I + a W + b W^2
+// and V = c0 I + c1 W + c2 W^2 with W = [omega]x and W^2 = omega omega^T -
+// |omega|^2 I) and from B, writes it to S64 (B may be S64) and its
+// float32 pose to o32; with inv32 the lanes then write the float32 pose of the
+// product's inverse (R^T / s, -R^T t / s).  What does not depend on the step
+// is loaded beforehand (compose_inputs), beside the solve for it.
+struct ComposeIn {
+    double cf[kExpTerms], b[3], s;   // this lane's series, its column of B, the scale of B
+};
+__device__ __forceinline__ ComposeIn compose_inputs(const double* cf, const double* B) {
     const int l = wave_lane();
-    const ExpCoef k = sim3_exp_coef(d[0], d[1], d[2], d[6]);
-    const double w0 = d[0], w1 = d[1], w2 = d[2];
+    ComposeIn in;
+#pragma unroll
+    for (int q = 0; q < kExpTerms; ++q) in.cf[q] = cf[16 * q + (l & 15)];
+    const int o = l < 9 ? l % 3 : 9, st = l < 9 ? 3 : 1;   // a column of the rotation, or the translation
+#pragma unroll
+    for (int q = 0; q < 3; ++q) in.b[q] = B[o + st * q];
+    in.s = B[12];
+    return in;
+}
+__device__ __forceinline__ void compose_exp_lanes(const double* d, const ComposeIn& in, double* S64, fl_sim3* o32,
+                                                  fl_sim3* inv32) {
+    const int l = wave_lane();
+    const double w0 = d[0], w1 = d[1], w2 = d[2], sig = d[6];
     const double th2 = w0 * w0 + w1 * w1 + w2 * w2;
+    ExpCoef k;
+    if (th2 < 1e-4 && fabs(sig) < 0.01) {
+        const double x = l < 8 ? sig : th2;
+        double v = in.cf[kExpTerms - 1];
+#pragma unroll
+        for (int q = kExpTerms - 2; q >= 0; --q) v = fma(v, x, in.cf[q]);
+        const double I1 = readlane_f64(v, 1), I2 = readlane_f64(v, 2);
+        k.c0 = readlane_f64(v, 0);
+        k.c1 = fma(th2, fma(th2 * (1.0 / 120.0), readlane_f64(v, 5), (-1.0 / 6.0) * readlane_f64(v, 3)), I1);
+        k.c2 = fma(th2, fma(th2 * (1.0 / 720.0), readlane_f64(v, 6), (-1.0 / 24.0) * readlane_f64(v, 4)), 0.5 * I2);
+        k.es = readlane_f64(v, 7);
+        k.a = readlane_f64(v, 8);
+        k.b = readlane_f64(v, 9);
+    } else {
+        k = sim3_exp_coef_full(w0, w1, w2, sig);
+    }
     // this lane's row i of R_d and V: lanes 0-8 entry (i, j) = (l / 3, l % 3)
     // of the rotation, lanes 9-11 row l - 9 of the translation
     const int i = l < 9 ? l / 3 : (l < 12 ? l - 9 : 0);
@@ -986,31 +1069,26 @@ __device__ __forceinline__ void compose_exp_lanes(const double* d, double* S64, 
     const double W0 = i == 0 ? 0.0 : (i == 1 ? w2 : -w1);
     const double W1 = i == 0 ? -w2 : (i == 1 ? 0.0 : w0);
     const double W2 = i == 0 ? w1 : (i == 1 ? -w0 : 0.0);
-    const double Q0 = wi * w0 - (i == 0 ? th2 : 0.0);   // row i of W^2
-    const double Q1 = wi * w1 - (i == 1 ? th2 : 0.0);
-    const double Q2 = wi * w2 - (i == 2 ? th2 : 0.0);
-    const double R0 = (i == 0 ? 1.0 : 0.0) + k.a * W0 + k.b * Q0;
-    const double R1 = (i == 1 ? 1.0 : 0.0) + k.a * W1 + k.b * Q1;
-    const double R2 = (i == 2 ? 1.0 : 0.0) + k.a * W2 + k.b * Q2;
-    const double s_new = k.es * S64[12];
-    double v;
-    if (l < 9) {
-        v = R0 * S64[j] + R1 * S64[3 + j] + R2 * S64[6 + j];
-    } else if (l < 12) {
-        const double V0 = (i == 0 ? k.c0 : 0.0) + k.c1 * W0 + k.c2 * Q0;
-        const double V1 = (i == 1 ? k.c0 : 0.0) + k.c1 * W1 + k.c2 * Q1;
-        const double V2 = (i == 2 ? k.c0 : 0.0) + k.c1 * W2 + k.c2 * Q2;
-        v = k.es * (R0 * S64[9] + R1 * S64[10] + R2 * S64[11]) + (V0 * d[3] + V1 * d[4] + V2 * d[5]);
-    } else {
-        v = s_new;
-    }
+    const double Q0 = fma(wi, w0, i == 0 ? -th2 : 0.0);   // row i of W^2
+    const double Q1 = fma(wi, w1, i == 1 ? -th2 : 0.0);
+    const double Q2 = fma(wi, w2, i == 2 ? -th2 : 0.0);
+    const double R0 = (i == 0 ? 1.0 : 0.0) + fma(k.b, Q0, k.a * W0);
+    const double R1 = (i == 1 ? 1.0 : 0.0) + fma(k.b, Q1, k.a * W1);
+    const double R2 = (i == 2 ? 1.0 : 0.0) + fma(k.b, Q2, k.a * W2);
+    const double V0 = fma(k.c2, Q0, fma(k.c1, W0, i == 0 ? k.c0 : 0.0));
+    const double V1 = fma(k.c2, Q1, fma(k.c1, W1, i == 1 ? k.c0 : 0.0));
+    const double V2 = fma(k.c2, Q2, fma(k.c1, W2, i == 2 ? k.c0 : 0.0));
+    const double s_new = k.es * in.s;
+    const double rb = fma(R0, in.b[0], fma(R1, in.b[1], R2 * in.b[2]));
+    const double vu = fma(V0, d[3], fma(V1, d[4], V2 * d[5]));
+    const double v = l < 9 ? rb : l < 12 ? fma(k.es, rb, vu) : s_new;
     if (l < 13) S64[l] = v;
     if (l < 9) o32->sR[l] = (float)(s_new * v);
     else if (l < 12) o32->t[l - 9] = (float)v;
-    // the new entries are written before any lane reads them
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
     if (inv32) {
+        // the new entries are written before any lane reads them
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
         const double inv_s = 1.0 / s_new;
         if (l < 9) {
             inv32->sR[l] = (float)(inv_s * S64[3 * j + i]);
@@ -1020,17 +1098,18 @@ __device__ __forceinline__ void compose_exp_lanes(const double* d, double* S64, 
     }
 }
 
-constexpr int kRefCache = 2;     // accepted pairs a thread keeps in registers across the steps
-constexpr int kRefKfLds = 64;    // keyframes of one event whose pose and intrinsics sit in LDS
+constexpr int kRefKfLds = 128;   // keyframes of one event whose pose and intrinsics sit in LDS
 constexpr int kRefMaxB = 64;     // workgroups per event
 constexpr int kRefBlock = 512;   // threads of a refinement workgroup: 64 x 512 pairs at one per thread
-constexpr int kNAccLM = 40;      // the sums plus the Huber loss (slot 36), padded to a multiple of 4
+constexpr int kNAccLM = 37;      // the sums plus the Huber loss (slot 36)
 // Each float64 partial travels as two 64-bit words, (high half << 32 | tag)
 // and (low half << 32 | tag): a word is written and read in one piece, so a
 // reader that sees the tag of the current launch and step in both words has
 // the value, without a separate flag or any cache maintenance.  Rows are
 // laid out for the larger (Levenberg-Marquardt) sum set.
-constexpr int kRefWords = 2 * kNAccLM;
+constexpr int kRefWords = 80;    // 2 kNAccLM, padded
+constexpr int kDeviceScope = 16;   // sc1 of the buffer loads and stores of the exchange
+static_assert(kRefBlock / kWave == kSeg && kRefWords >= 2 * kNAccLM, "wave totals and segments alike, one a wave");
 constexpr double kLmConverged = 1e-6;   // relative loss change that ends a round
 
 // The refinement of each event in rounds.  Round 0 uses every accepted
@@ -1049,16 +1128,18 @@ constexpr double kLmConverged = 1e-6;   // relative loss change that ends a roun
 template <bool LM, bool ROUNDS>
 __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __restrict__ hp) {
     constexpr int NV = LM ? kNAccLM : kNAcc;
-    __shared__ float s_big[NV * (kRefBlock / 4 + 1)];   // the block reduction's transpose
-    __shared__ double s_q[kSeg * NV];
+    constexpr int kRefCache = LM || ROUNDS ? 2 : 3;   // accepted pairs a thread keeps in registers across the steps
+    static_assert(kRefCache == 2 || kRefCache == 3, "the calls below");
+    __shared__ double s_w[kSeg * NV];        // the waves' sums
+    __shared__ double s_q[kSeg * NV];        // segments of the event's rows
     __shared__ double s_out[NV];
+    __shared__ double s_cf[16 * kExpTerms];
     __shared__ float s_kf[kRefKfLds * 16];   // per keyframe: T (12), fx, fy, cx, cy
     __shared__ float s_ikf[(LM || ROUNDS) ? 16 : kRefKfLds * 16];   // the same for the other direction's keyframes
     __shared__ double s_S64[13];
     __shared__ fl_sim3 s_S;
     __shared__ fl_sim3 s_Sinv;               // float32 form of S^-1 (two-sided refinement)
     __shared__ double s_Srs64[13];           // the round's starting Sim3 (inlier tests)
-    __shared__ double s_wsum[kRefBlock / kWave];
     __shared__ double s_acc[kNAcc];          // LM: g, H and count at S_acc
     __shared__ double s_Sacc[13];            // LM: S_acc
     __shared__ double s_lm[2];               // LM: loss at S_acc, lambda
@@ -1073,6 +1154,7 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     const float tau = h.outlier_px;
     const int tid = threadIdx.x;
     const uint32_t epoch = *h.epoch;
+    for (int i = tid; i < 16 * kExpTerms; i += blockDim.x) s_cf[i] = kExpTable.v[i];
     for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
         const int ev = unit / B, b = unit % B;
         const EventDesc ed = h.ev[ev];
@@ -1125,6 +1207,7 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
         for (int r = 0; r < kRefCache; ++r) {
             const int i = b * blockDim.x + tid + r * stride;
             ck_[r] = -1;
+            cx_[r] = cy_[r] = cz_[r] = cu_[r] = cv_[r] = 0.0f;
             in_[r] = true;
             if (use_list && i < (int)cnt) {
                 const MatchRec m = h.match_list[ed.list_off + i];
@@ -1166,41 +1249,41 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
             // thread when the list fits the workgroups, a couple of dozen at
             // most when the event's pairs are scanned); everything across
             // threads and workgroups is summed in float64.
-            float accf[NV];
-#pragma unroll
-            for (int i = 0; i < NV; ++i) accf[i] = 0.0f;
+            float accf[kNAcc];
             double lossd = 0.0;   // LM: the Huber loss of this thread's pairs, float64
             if (use_list) {
-#pragma unroll
-                for (int r = 0; r < kRefCache; ++r) {
-                    if (ck_[r] < 0 || !(in_[r] || classify)) continue;
-                    const float* T;
-                    float fx, fy, px, py;
+                // Straight-line code for the first pair, whose sums are written
+                // rather than added to zeros; the others only where the
+                // workgroup has them (a branch of a whole wave).
+                auto cached = [&](auto R) {
+                    constexpr int r = decltype(R)::value;
+                    bool has = ck_[r] >= 0;
+                    const int k = max(ck_[r], ed.kf_begin);
+                    const float *T, *c;
                     if (kf_lds) {
-                        const float* q = &s_kf[16 * (ck_[r] - ed.kf_begin)];
-                        T = q;
-                        fx = q[12];
-                        fy = q[13];
-                        px = q[14];
-                        py = q[15];
+                        T = &s_kf[16 * (k - ed.kf_begin)];
+                        c = T + 12;
                     } else {
-                        const KfDesc& kd = h.kf[ck_[r]];
-                        T = kd.T;
-                        fx = kd.fx;
-                        fy = kd.fy;
-                        px = kd.cx;
-                        py = kd.cy;
+                        T = h.kf[k].T;
+                        c = &h.kf[k].fx;
                     }
                     double e;
-                    if (classify) {
-                        in_[r] = pair_error64(s_Srs64, T, fx, fy, px, py, cx_[r], cy_[r], cz_[r], cu_[r], cv_[r], e) &&
-                                 e <= (double)tau;
-                        if (!in_[r]) continue;
+                    if (ROUNDS) {
+                        if (classify && has)
+                            in_[r] = pair_error64(s_Srs64, T, c[0], c[1], c[2], c[3], cx_[r], cy_[r], cz_[r], cu_[r],
+                                                  cv_[r], e) && e <= (double)tau;
+                        has = has && in_[r];
                     }
-                    refine_accumulate_f32(T, fx, fy, px, py, cx_[r], cy_[r], cz_[r], cu_[r], cv_[r], S, delta, accf);
-                    if (LM && pair_error64(s_S64, T, fx, fy, px, py, cx_[r], cy_[r], cz_[r], cu_[r], cv_[r], e))
+                    refine_pair_f32<false, r == 0>(S.sR, S.t, T, c[0], c[1], c[2], c[3], cx_[r], cy_[r], cz_[r], cu_[r],
+                                                   cv_[r], delta, accf, has);
+                    if (LM && has &&
+                        pair_error64(s_S64, T, c[0], c[1], c[2], c[3], cx_[r], cy_[r], cz_[r], cu_[r], cv_[r], e))
                         lossd += huber64(e, (double)delta);
-                }
+                };
+                cached(std::integral_constant<int, 0>{});
+                if (kRefCache > 1 && b * (int)blockDim.x + stride < (int)cnt) cached(std::integral_constant<int, 1>{});
+                if (kRefCache > 2 && b * (int)blockDim.x + 2 * stride < (int)cnt)
+                    cached(std::integral_constant<int, kRefCache - 1>{});
                 for (int i = b * blockDim.x + tid + kRefCache * stride; i < (int)cnt; i += stride) {
                     const MatchRec m = h.match_list[ed.list_off + i];
                     const KfDesc& kd = h.kf[m.kf];
@@ -1208,12 +1291,14 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                     if (bounded && !(pair_error64(s_Srs64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v,
                                                   e) && e <= (double)tau))
                         continue;
-                    refine_accumulate_f32(kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v, S, delta, accf);
+                    refine_pair_f32<false>(S.sR, S.t, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v, delta, accf);
                     if (LM && pair_error64(s_S64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v, e))
                         lossd += huber64(e, (double)delta);
                 }
             } else {
                 // no list (or it overflowed): scan the event's pairs keyframe by keyframe
+#pragma unroll
+                for (int i = 0; i < kNAcc; ++i) accf[i] = 0.0f;
                 for (int k = ed.kf_begin; k < ed.kf_end; ++k) {
                     const KfDesc& kd = h.kf[k];
                     for (int64_t jj = b * blockDim.x + tid; jj < kd.n_pairs; jj += stride) {
@@ -1230,7 +1315,7 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                         if (bounded && !(pair_error64(s_Srs64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, x, y, z, uo, vo, e) &&
                                          e <= (double)tau))
                             continue;
-                        refine_accumulate_f32(kd.T, kd.fx, kd.fy, kd.cx, kd.cy, x, y, z, uo, vo, S, delta, accf);
+                        refine_pair_f32<false>(S.sR, S.t, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, x, y, z, uo, vo, delta, accf);
                         if (LM && pair_error64(s_S64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, x, y, z, uo, vo, e))
                             lossd += huber64(e, (double)delta);
                     }
@@ -1238,131 +1323,143 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
             }
             if (n_inv > 0) {
                 const fl_sim3 Si = s_Sinv;
-                if (ik_ >= 0)
-                    refine_inverse_f32(h, s_ikf, ikf_lds, ik_, ix_, iy_, iz_, iu_, iv_, Si, delta, accf);
+                auto add_inverse = [&](int k, float x, float y, float z, float uo, float vo) {
+                    const float* T = ikf_lds ? s_ikf + 16 * k : h.inv_T + 12 * (int64_t)k;
+                    const float* c = ikf_lds ? T + 12 : h.inv_cam + 4 * (int64_t)k;
+                    refine_pair_f32<true>(Si.sR, Si.t, T, c[0], c[1], c[2], c[3], x, y, z, uo, vo, delta, accf);
+                };
+                if (ik_ >= 0) add_inverse(ik_, ix_, iy_, iz_, iu_, iv_);
                 for (int i = b * blockDim.x + tid + stride; i < n_inv; i += stride) {
                     const int64_t g = ed.inv_off + (int64_t)i;
                     const int k = h.inv_kf[g];
                     if (k < 0 || k >= h.inv_n_kf) continue;
-                    refine_inverse_f32(h, s_ikf, ikf_lds, k, h.inv_xyz[3 * g], h.inv_xyz[3 * g + 1],
-                                       h.inv_xyz[3 * g + 2], h.inv_uv[2 * g], h.inv_uv[2 * g + 1], Si, delta, accf);
+                    add_inverse(k, h.inv_xyz[3 * g], h.inv_xyz[3 * g + 1], h.inv_xyz[3 * g + 2], h.inv_uv[2 * g],
+                                h.inv_uv[2 * g + 1]);
                 }
             }
-            // the per-thread float32 sums go through LDS as they are and are
-            // widened as the segments are added
-            block_reduce_quad<NV, kRefBlock>(accf, s_big, s_q, s_out);
-            if (LM) {
-                const double loss = block_sum_f64(lossd, s_wsum);
-                if (tid == 0) s_out[36] = loss;
-                __syncthreads();
+            // the waves' sums, in float64 beyond a quad of threads
+            {
+                int idx;
+                const double v = wave_reduce_quad<kNAcc>(accf, idx);
+                if (idx >= 0) s_w[(tid / kWave) * NV + idx] = v;
+                if (LM) {
+                    double loss = lossd;
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) loss += __shfl_xor(loss, off);
+                    if (wave_lane() == 0) s_w[(tid / kWave) * NV + 36] = loss;
+                }
             }
+            __syncthreads();
             if (Be > 1) {
                 // Exchange of the Be partial sums of this step as tagged words
-                // (device-coherent stores and loads).  Rows alternate between
-                // two buffers by step: a workgroup writes step it + 2 only
-                // after it has read every row of step it + 1, which every
+                // (device-coherent stores and loads of 16 bytes, the two words
+                // of a value; each word carries its own tag).  Rows alternate
+                // between two buffers by step: a workgroup writes step it + 2
+                // only after it has read every row of step it + 1, which every
                 // workgroup writes only after reading all rows of step it.
                 const size_t slot = ((size_t)(seq & 1) * n_units + (size_t)ev * B);   // rows of this step: Be
-                unsigned long long* rows = h.refine_rows + slot * kRefWords;
+                const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+                    uniform_p(h.refine_rows + slot * kRefWords), 0, Be * kRefWords * 8, 0x00020000);
                 const uint32_t tag = refine_tag(epoch, seq);
-                if (tid < 2 * NV) {
-                    const unsigned long long bits = (unsigned long long)__double_as_longlong(s_out[tid >> 1]);
-                    const uint32_t half = (tid & 1) ? (uint32_t)bits : (uint32_t)(bits >> 32);
-                    __hip_atomic_store(&rows[(size_t)b * kRefWords + tid], ((unsigned long long)half << 32) | tag,
-                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int w = __builtin_amdgcn_readfirstlane(tid / kWave), c = wave_lane();
+                if (tid < NV) {
+                    const uint64_t bits = (uint64_t)__double_as_longlong(add_segments<NV>(s_w, tid));
+                    const v4u x = {tag, (uint32_t)(bits >> 32), tag, (uint32_t)bits};
+                    __builtin_amdgcn_raw_buffer_store_b128(x, rows, 16 * tid, b * kRefWords * 8, kDeviceScope);
                 }
-                // Thread (c, q) loads the two words of value c of rows q,
-                // q + kSeg, ... (words whose tag is not yet the current one are
-                // loaded again) and adds those rows in that order; then the
-                // segments are added pairwise.  The order is the same in every
-                // workgroup, so all of them solve for bitwise the same step.
-                if (tid < kSeg * NV) {
-                    const int c = tid % NV, q = tid / NV;
-                    constexpr int kRowsPer = kRefMaxB / kSeg;
-                    unsigned long long wh[kRowsPer], wl[kRowsPer];
-                    uint32_t pending = 0;
+                // Wave w loads rows w, w + kSeg, ..., lane c value c of each (a
+                // row with a tag that is not yet the current one is loaded
+                // again), and adds them in that order; then the segments are
+                // added pairwise.  The order is the same in every workgroup, so
+                // all of them solve for bitwise the same step.
+                constexpr int kRowsPer = kRefMaxB / kSeg;
+                v4u x[kRowsPer];
+                uint32_t pending = 0;   // the same in every lane, like the branches on it
+#pragma unroll
+                for (int jr = 0; jr < kRowsPer; ++jr)
+                    if (w + kSeg * jr < Be) pending |= 1u << jr;
+                unsigned spins = 0;
+                // the rows take about 1,600 cycles to arrive, and a load that
+                // is on its way when they do costs as much again: the first is
+                // sent 900 cycles on (C2's loop event: 9,500 cycles to here a
+                // step without the pause, 8,850 with it)
+                __builtin_amdgcn_s_sleep(14);
+                while (pending) {
+                    asm volatile("" ::: "memory");   // the rows change under this loop
 #pragma unroll
                     for (int jr = 0; jr < kRowsPer; ++jr)
-                        if (q + kSeg * jr < Be) pending |= 1u << jr;
-                    unsigned spins = 0;
-                    while (pending) {
+                        if (pending >> jr & 1u)
+                            x[jr] = __builtin_amdgcn_raw_buffer_load_b128(rows, 16 * min(c, NV - 1),
+                                                                          (w + kSeg * jr) * kRefWords * 8, kDeviceScope);
 #pragma unroll
-                        for (int jr = 0; jr < kRowsPer; ++jr)
-                            if (pending >> jr & 1u) {
-                                const unsigned long long* w = rows + (size_t)(q + kSeg * jr) * kRefWords + 2 * c;
-                                wh[jr] = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                wl[jr] = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                            }
-#pragma unroll
-                        for (int jr = 0; jr < kRowsPer; ++jr)
-                            if ((pending >> jr & 1u) && (uint32_t)wh[jr] == tag && (uint32_t)wl[jr] == tag)
-                                pending &= ~(1u << jr);
-                        if (pending) {
-                            // no back-off: each round is a device-memory round
-                            // trip already, and a pause only delays the last row
-                            if (++spins > kSpinLimit) {
-                                s_fail = 1;
-                                break;
-                            }
-                        }
+                    for (int jr = 0; jr < kRowsPer; ++jr)
+                        if ((pending >> jr & 1u) && __ballot(x[jr].x != tag || x[jr].z != tag) == 0ull)
+                            pending &= ~(1u << jr);
+                    if (pending && ++spins > kSpinLimit) {
+                        s_fail = 1;
+                        break;
                     }
-                    double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-                    for (int jr = 0; jr < kRowsPer; ++jr) {
-                        if (q + kSeg * jr < Be) {
-                            const double x = __longlong_as_double(
-                                (long long)((wh[jr] >> 32 << 32) | (wl[jr] >> 32)));
-                            if (jr & 1) a1 += x; else a0 += x;
-                        }
-                    }
-                    s_q[q * NV + c] = a0 + a1;
                 }
+                double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+                for (int jr = 0; jr < kRowsPer; ++jr) {
+                    if (w + kSeg * jr < Be) {
+                        const double y = __longlong_as_double(((long long)x[jr].y << 32) | (long long)x[jr].w);
+                        if (jr & 1) a1 += y; else a0 += y;
+                    }
+                }
+                if (c < NV) s_q[w * NV + c] = a0 + a1;
                 __syncthreads();
                 if (s_fail) break;
-                if (tid < NV) s_out[tid] = add_segments<NV>(s_q, tid);
-                __syncthreads();
             }
-            if (!LM && tid < kWave) {
-                // Gauss-Newton: every lane of wave 0 solves for the same step,
-                // then the lanes compose it with S together
-                double d[7];
-                if (solve7(s_out, s_out + 7, 0.0, d)) compose_exp_lanes(d, s_S64, &s_S, n_inv > 0 ? &s_Sinv : nullptr);
-            }
-            if (tid == 0) {
+            if (tid < kWave) {
+                // Wave 0, every lane alike: the event's sums, then the step,
+                // which the lanes compose with S together.
+                if (tid < NV) s_out[tid] = add_segments<NV>(Be > 1 ? s_q : s_w, tid);
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
                 bool round_end = j == iters - 1;
-                if (LM) {
+                double d[7];
+                if (!LM) {
+                    const ComposeIn in = compose_inputs(s_cf, s_S64);
+                    if (solve7(s_out, s_out + 7, 0.0, d))
+                        compose_exp_lanes(d, in, s_S64, &s_S, n_inv > 0 ? &s_Sinv : nullptr);
+                } else {
                     // the evaluation just summed was at s_S64: the round's start
                     // (j = 0) or the last candidate
                     bool take = j == 0;
-                    if (j == 0) {
-                        s_lm[1] = (double)h.lm_lambda;
-                    } else {
+                    double lam = j == 0 ? (double)h.lm_lambda : s_lm[1];
+                    if (j > 0) {
                         const double rho = s_lm[0] > 0.0 ? (s_lm[0] - s_out[36]) / s_lm[0] : 0.0;
                         take = rho > kLmConverged;
                         if (!take && rho >= -kLmConverged) round_end = true;   // converged
+                        if (take) lam = fmax(lam * 0.1, 1e-12);
+                        else if (!round_end) lam = fmin(lam * 10.0, 1e16);
                     }
                     if (take) {
-                        for (int i = 0; i < kNAcc; ++i) s_acc[i] = s_out[i];
-                        for (int i = 0; i < 13; ++i) s_Sacc[i] = s_S64[i];
-                        s_lm[0] = s_out[36];
-                        if (j > 0) s_lm[1] = fmax(s_lm[1] * 0.1, 1e-12);
-                    } else if (!round_end) {
-                        s_lm[1] = fmin(s_lm[1] * 10.0, 1e16);
+                        if (tid < kNAcc) s_acc[tid] = s_out[tid];
+                        if (tid < 13) s_Sacc[tid] = s_S64[tid];
                     }
-                    const Sim3d Sa = sim3_load(s_Sacc);
-                    double d[7];
-                    if (!round_end && solve7(s_acc, s_acc + 7, s_lm[1], d)) {
-                        const Sim3d Sd = sim3_mul(sim3_exp(d), Sa);
-                        sim3_store(Sd, s_S64);
-                        sim3_to_f32_pose(Sd, &s_S);
+                    if (tid == 0) {
+                        if (take) s_lm[0] = s_out[36];
+                        s_lm[1] = lam;
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    if (!round_end && solve7(s_acc, s_acc + 7, lam, d)) {
+                        compose_exp_lanes(d, compose_inputs(s_cf, s_Sacc), s_S64, &s_S, nullptr);
                     } else {
-                        sim3_store(Sa, s_S64);
-                        sim3_to_f32_pose(Sa, &s_S);
+                        if (tid < 13) s_S64[tid] = s_Sacc[tid];
+                        if (tid < 9) s_S.sR[tid] = (float)(s_Sacc[12] * s_Sacc[tid]);
+                        else if (tid < 12) s_S.t[tid - 9] = (float)s_Sacc[tid];
                     }
                 }
-                if (round_end)
-                    for (int i = 0; i < 13; ++i) s_Srs64[i] = s_S64[i];   // the next round's starting Sim3
-                s_round_end = round_end;
+                if (round_end) {
+                    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    if (tid < 13) s_Srs64[tid] = s_S64[tid];   // the next round's starting Sim3
+                }
+                if (tid == 0) s_round_end = round_end;
             }
             __syncthreads();
             if (LM && s_round_end) it = (rnd + 1) * iters - 1;   // on to the next round

@@ -745,3 +745,48 @@ def test_residual_sums_over_every_grid_shape(ctx, n):
     assert torch.equal(one32, S32)
     assert abs(one.item() - loss.item()) <= 1e-14 * loss.item()
     assert np.max(np.abs(gone - gx)) <= 1e-13 * np.max(np.abs(gx))
+
+
+@pytest.mark.parametrize("n_kf", [5, 64, 128, 129])
+def test_refinement_at_the_keyframe_table_limit(ctx, n_kf):
+    """Keyframe poses in LDS up to 128 keyframes of an event, from device
+    memory beyond, and two events that hold one, two, three and more accepted
+    pairs a thread between them: the oracle's accepted pairs, and float64
+    Gauss-Newton on them to the bound of the other refinement tests."""
+    import paper_2603_17201_amd as fl
+    few = synth.gen_c2(seed=211, n_kf=n_kf, n_mp=900, n_kp=40)
+    many = synth.gen_c2(seed=212, n_kf=4, n_mp=4000, n_kp=800)
+    B = synth.concat_events([few, many])
+    exp = oracle.search_fuse(B, use_grid=True)
+    S = t(np.stack([ev.S_init for ev in B.events]))
+    nm = torch.zeros(2, dtype=torch.int32, device=dev())
+    got = ctx.search_fuse_batched(fl.DeviceBatch(B, device=dev()), B.params, refine=(6, 2.45, S, None, nm)).numpy()
+    for k in got:
+        assert np.array_equal(got[k], exp[k]), k
+    for e in range(2):
+        S_ref, n_ref = _event_gn(B, exp, e, iters=6)
+        assert nm[e].item() == n_ref
+        assert np.linalg.norm(sim3.log(sim3.compose(S[e].cpu().numpy(), sim3.inverse(S_ref)))) < 1e-6
+
+
+def test_two_sided_pairs_that_are_not_finite_add_nothing(ctx):
+    """Pairs of the other direction whose point or depth is not a number or
+    infinite add nothing, like those behind their keyframe: the same Sim3 as
+    without them (another order of the float32 sums of a quad at most)."""
+    import paper_2603_17201_amd as fl
+    ev = synth.gen_c2(seed=213, n_kf=4, n_mp=2000, n_kp=500)
+    xyz, uv, kf, T = synth.gen_inverse_pairs(ev.S_true, 700, seed=9)
+    bad = np.array([[np.nan, 1, 2], [1, np.inf, 2], [0, 0, -np.inf], [np.nan] * 3], np.float32)
+    cam = t(np.tile(np.array(synth.CAM_752[:4], np.float32), (len(T), 1)))
+    b = fl.DeviceBatch(ev, device=dev())
+    out = []
+    for extra in (0, len(bad)):
+        x = np.concatenate([xyz, bad[:extra]])
+        inv = fl.InversePairs([0, len(x)], t(x), t(np.concatenate([uv, uv[:extra]])), t(np.concatenate([kf, kf[:extra]])),
+                              t(T), cam)
+        S = t(ev.S_init.reshape(1, 13).copy())
+        nm = torch.zeros(1, dtype=torch.int32, device=dev())
+        ctx.search_fuse_batched(b, ev.params, refine=(6, 2.45, S, None, nm, 0, 0.0, 0.0, inv))
+        out.append((S.cpu().numpy()[0], nm.item()))
+    assert out[0][1] == out[1][1]
+    assert np.linalg.norm(sim3.log(sim3.compose(out[1][0], sim3.inverse(out[0][0])))) < 1e-6
