@@ -464,7 +464,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     EventDesc* evd = (EventDesc*)(blob.data() + o_ev);
 
     // keyframes, events, list regions, tiles
-    int64_t hash_total = 0, list_total = 0;
+    int64_t hash_total = 0;
     std::vector<double> tile_cost;    // cost of each keyframe's tiles (per tile)
     tile_cost.resize(n_vk);
     for (int e = 0; e < n_ev; ++e) {
@@ -476,15 +476,10 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
         ed.n_mp = B->event_mp_offset[e + 1] - ed.mp_off;
         ed.pair_begin = B->pair_offset[kb];
         ed.pair_end = B->pair_offset[ke];
-        const int64_t kp_ev = B->kp_offset[ke] - B->kp_offset[kb];
-        int64_t cap = std::min<int64_t>(ed.pair_end - ed.pair_begin, std::max<int64_t>(2 * kp_ev, 4096));
-        if (c->add_cap_override > 0) cap = std::min<int64_t>(cap, c->add_cap_override);
-        ed.list_off = refine ? (int32_t)list_total : 0;
-        ed.list_cap = refine ? (int32_t)cap : 0;
+        ed.list_cap = c->add_cap_override > 0 ? c->add_cap_override : INT32_MAX;
         const fl_refine_inverse* V = refine ? R->inverse : nullptr;
         ed.inv_off = V ? (int32_t)V->event_offset[e] : 0;
         ed.inv_n = V ? (int32_t)(V->event_offset[e + 1] - V->event_offset[e]) : 0;
-        if (refine) list_total += cap;
         for (int k = kb; k < ke; ++k) {
             // the keyframe's global grid and owner hash set serve every pass
             const int n_kp = B->kp_offset[k + 1] - B->kp_offset[k];
@@ -522,7 +517,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     // space of the workgroups' list regions
     int64_t n_virtual = 0;
     for (int v = 0; v < n_vk; ++v) n_virtual += kfd[v].n_pairs;
-    if (n_virtual > INT32_MAX || list_total > INT32_MAX || hash_total > INT32_MAX)
+    if (n_virtual > INT32_MAX || hash_total > INT32_MAX)
         return fail(FL_ERANGE, "batch too large for the workspace indexing");
     // tile order: keyframes in batch order
     int32_t* order = (int32_t*)(blob.data() + o_order);
@@ -600,6 +595,34 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
             const int64_t p0 = tile_pair(t0), p1 = tile_pair(bound[i + 1]);
             g.priv_off = (int32_t)p0;
             g.priv_cap = (int32_t)(p1 - p0);
+            g.chunk = i;
+            g.event = t0 < n_tiles ? kfd[order[slot]].event : -1;
+            g.slot_t0 = prefix[slot];
+            g.slot_t1 = prefix[slot + 1];
+            const KfDesc& kd = kfd[order[slot]];
+            g.pass = kd.pass;
+            g.stage_key = kd.stage_key;
+            g.kp_off = kd.kp_off;
+            g.n_kp = kd.n_kp;
+            g.invw = kd.invw;
+            g.invh = kd.invh;
+        }
+        // each event's chunks: from the one that holds its first tile to the
+        // one that holds its last (an empty chunk between them writes an empty
+        // entry for the event its place in the order lies in, this one)
+        for (int e = 0; e < n_ev; ++e) {
+            EventDesc& ed = evd[e];
+            const int64_t ta = prefix[ed.kf_begin], tz = prefix[ed.kf_end];
+            ed.seg_off = ed.seg_n = 0;
+            if (!refine || ta == tz) continue;
+            const int c0 = (int)(std::upper_bound(bound.begin(), bound.end(), ta) - bound.begin()) - 1;
+            const int c1 = (int)(std::upper_bound(bound.begin(), bound.end(), tz - 1) - bound.begin()) - 1;
+            ed.seg_off = c0 + e;
+            ed.seg_n = c1 - c0 + 1;
+            if (ed.seg_n > kRefBlock) {   // more than the refinement's table holds: from the decisions
+                ed.seg_n = 0;
+                ed.list_cap = -1;
+            }
         }
         for (int i = ge; i < grid; ++i) {
             WgRange& g = wr[i];
@@ -608,6 +631,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
             g.kf = order[0];
             g.priv_off = (int32_t)n_virtual;
             g.priv_cap = 0;
+            g.event = -1;
         }
     }
 
@@ -632,7 +656,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     const size_t L_add = take(sizeof(AddRef) * (size_t)n_virtual);
     const size_t L_add_count = take(sizeof(uint32_t) * (size_t)grid);
     const size_t L_stage = take(refine ? sizeof(MatchRec) * (size_t)n_virtual : 0);
-    const size_t L_match = take(sizeof(MatchRec) * (size_t)list_total);
+    const size_t L_seg = take(sizeof(MatchSeg) * (size_t)(grid + n_ev));
     const int refine_blocks = std::max(1, std::min(kRefMaxB, kRefineGrid / std::max(1, n_ev)));
     const size_t n_rows = 2 * (size_t)n_ev * refine_blocks;
     int rc = c->ws.ensure(off);
@@ -646,7 +670,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     rc = c->claims.ensure(sizeof(unsigned long long) * (size_t)std::max(n_pass * B->n_kp_total, 1), 0xFF);
     if (rc) return rc;
     const void* old_ctrs = c->ctrs.p;
-    rc = c->ctrs.ensure(64 + sizeof(uint32_t) * (size_t)kEvCtrs * n_ev, 0x00);
+    rc = c->ctrs.ensure(64, 0x00);
     if (rc) return rc;
     if (c->ctrs.p != old_ctrs && old_ctrs != nullptr) {
         // a fresh counter block restarts the epoch: every stored claim must be reset too
@@ -716,11 +740,10 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     h.claim = (unsigned long long*)c->claims.p;
     h.stats_out = (unsigned long long*)cb;
     h.epoch = (const uint32_t*)(cb + 32);
-    h.ev_ctr = (uint32_t*)(cb + 64);
     h.add_list = (AddRef*)(base + L_add);
     h.add_count = (uint32_t*)(base + L_add_count);
     h.match_stage = (MatchRec*)(base + L_stage);
-    h.match_list = (MatchRec*)(base + L_match);
+    h.match_seg = (MatchSeg*)(base + L_seg);
     h.refine_blocks = refine_blocks;
     h.refine_scan = refine_scan ? 1 : 0;
     // a refinement that follows a search in the same call resolves its ADD

@@ -61,10 +61,11 @@ struct PassOut {
 struct alignas(16) EventDesc {
     int32_t kf_begin, kf_end;
     int32_t mp_off, n_mp;
-    int32_t list_off, list_cap;    // region of the matched-pair list
+    int32_t seg_off, seg_n;        // the event's entries of the accepted-pair table
     int64_t pair_begin, pair_end;  // pair range (pairs of the event are contiguous)
     int32_t inv_off, inv_n;        // the event's pairs of the other direction (two-sided refinement)
-    int32_t pad0, pad1;
+    int32_t list_cap;              // more accepted pairs than this are taken from the decisions instead
+    int32_t pad0;
 };
 
 // Offsets in the table blob (which starts at the batch header) of the
@@ -89,7 +90,24 @@ struct alignas(16) AddRef {
 // (each pair adds at most one entry to each list).
 struct alignas(16) WgRange {
     int32_t t0, t1, slot, kf;
-    int32_t priv_off, priv_cap, pad0, pad1;
+    int32_t priv_off, priv_cap;
+    int32_t chunk;           // the workgroup's place in the tile order
+    int32_t event;           // event of tile t0
+    // of the first keyframe, so that neither its keypoints' loads nor the
+    // pass's thresholds wait for its descriptor
+    int32_t slot_t0, slot_t1;   // tile_prefix[slot], tile_prefix[slot + 1]
+    int32_t pass, stage_key;
+    int32_t kp_off, n_kp;
+    float invw, invh;
+};
+static_assert(sizeof(WgRange) == 64, "one cache line");
+
+// The accepted pairs one workgroup staged for one event: entries [start,
+// start + count) of the staging list.  Workgroup chunk c and event e meet at
+// index c + e of the table (both rise along the tile order, so no two meetings
+// share an index).
+struct MatchSeg {
+    int32_t start, count;
 };
 
 // Accepted pair kept for refinement: point, observation, keyframe.
@@ -107,12 +125,6 @@ struct alignas(16) KpRec {
     int32_t idx;
     int32_t oct;
 };
-
-// Per-event counters (the accepted-pair count, zero between launches: the
-// refinement that reads the list resets it).  Each event's counters sit on a
-// 128-byte line of their own: device-scope atomics on one line serialise
-// (about 12 ns apiece).
-enum : int { kEvMatch = 0, kEvCtrs = 32 };
 
 enum : int { kModeGlobal = 0, kModeLdsRec = 1, kModeLdsDesc = 2 };
 
@@ -167,11 +179,10 @@ struct alignas(16) BatchHdr {
     int32_t* hash;              // global-grid mode: owner hash tables
     unsigned long long* claim;  // [n_pass * n_kp_total] (epoch << 32 | lowest claiming point)
     const uint32_t* epoch;      // tag of this launch's claims, decremented by the table fetch
-    uint32_t* ev_ctr;           // [n_events * kEvCtrs]
     AddRef* add_list;           // per-workgroup regions (WgRange::priv_off)
     uint32_t* add_count;        // [n_wg] entries of each workgroup's ADD region
-    MatchRec* match_stage;      // per-workgroup regions of accepted pairs, before they join their event's list
-    MatchRec* match_list;       // per-event regions
+    MatchRec* match_stage;      // per-workgroup regions of accepted pairs (WgRange::priv_off)
+    MatchSeg* match_seg;        // [n_wg + n_events] which of them belong to which event
     unsigned long long* stats_out;  // [4]
     // refinement
     double* event_S;            // [n_events][13] caller's, in/out
@@ -201,11 +212,11 @@ __host__ __device__ constexpr size_t blob_kf_offset(int grid) {
 // library is compiled with -ffp-contract=off).
 
 // floor(x * inv) clamped to [0, n): a negative or NaN product gives cell 0.
-// Branch free: fmaxf returns its other operand for a NaN, and floor of a
-// product below n is at most n - 1.
+// Clamped in float first (the median of the product and both ends; of a NaN
+// and the ends it is the lower end), where the conversion's truncation is the
+// floor.
 __device__ __forceinline__ int cell_of(float x, float inv, int n) {
-    const float f = floorf(x * inv);
-    return (int)fminf(fmaxf(f, 0.0f), (float)(n - 1));
+    return (int)__builtin_amdgcn_fmed3f(x * inv, 0.0f, (float)(n - 1));
 }
 
 struct Proj {
@@ -214,21 +225,18 @@ struct Proj {
 };
 
 // Transform by the keyframe's Sim3, pinhole projection and image test:
-// false when the point is not visible; u, v and the metric distance d
-// otherwise.
+// false when the point is not visible (u, v and d are then of no meaning);
+// u, v and the metric distance d otherwise.  Straight-line code: a wave
+// leaves it early only if none of its 64 points is visible.
 __device__ __forceinline__ bool project_uv(const KfDesc& k, float x, float y, float z, Proj& p) {
     const float q0 = fmaf(k.A[2], z, fmaf(k.A[1], y, fmaf(k.A[0], x, k.t[0])));
     const float q1 = fmaf(k.A[5], z, fmaf(k.A[4], y, fmaf(k.A[3], x, k.t[1])));
     const float q2 = fmaf(k.A[8], z, fmaf(k.A[7], y, fmaf(k.A[6], x, k.t[2])));
-    if (!(q2 > 0.0f)) return false;
     const float iz = 1.0f / q2;
-    const float u = fmaf(k.fx, q0 * iz, k.cx);
-    const float v = fmaf(k.fy, q1 * iz, k.cy);
-    if (!(u >= 0.0f && u < k.W && v >= 0.0f && v < k.H)) return false;
-    p.u = u;
-    p.v = v;
+    p.u = fmaf(k.fx, q0 * iz, k.cx);
+    p.v = fmaf(k.fy, q1 * iz, k.cy);
     p.d = sqrtf(fmaf(q0, q0, fmaf(q1, q1, q2 * q2))) * k.inv_s;
-    return true;
+    return (q2 > 0.0f) & (p.u >= 0.0f) & (p.u < k.W) & (p.v >= 0.0f) & (p.v < k.H);
 }
 
 // Transform, projection, image test and predicted octave: the first n with

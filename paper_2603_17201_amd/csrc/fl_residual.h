@@ -1143,6 +1143,9 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     __shared__ double s_acc[kNAcc];          // LM: g, H and count at S_acc
     __shared__ double s_Sacc[13];            // LM: S_acc
     __shared__ double s_lm[2];               // LM: loss at S_acc, lambda
+    __shared__ int s_segx[kRefBlock];        // the event's segments of accepted pairs: the pairs before each,
+    __shared__ int s_segp[kRefBlock];        // and its place in the staging list less those
+    __shared__ int s_segw[kRefBlock / kWave];
     __shared__ int s_fail;
     __shared__ int s_round_end;              // LM: the round converged at this step
     const BatchHdr& h = *hp;
@@ -1158,6 +1161,8 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
         const int ev = unit / B, b = unit % B;
         const EventDesc ed = h.ev[ev];
+        const int seg_n = h.refine_scan ? 0 : ed.seg_n;
+        const MatchSeg sg = tid < seg_n ? h.match_seg[ed.seg_off + tid] : MatchSeg{0, 0};
         const int n_kf_ev = ed.kf_end - ed.kf_begin;
         const bool kf_lds = n_kf_ev <= kRefKfLds;
         if (tid < 13) s_S64[tid] = h.event_S[13 * (int64_t)ev + tid];
@@ -1179,20 +1184,45 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 s_ikf[i] = f < 12 ? h.inv_T[12 * k + f] : h.inv_cam[4 * k + f - 12];
             }
         }
+        // The event's accepted pairs lie in the search workgroups' regions:
+        // pair i is in the last segment with at most i pairs before it (a
+        // segment past the last has all of them before it).  Three rounds of
+        // seven independent reads find it, where a binary search would be a
+        // chain of nine.
+        const int incl = wave_incl_scan(sg.count);
+        if (wave_lane() == kWave - 1) s_segw[tid / kWave] = incl;
         __syncthreads();
-        if (tid == 0) {
-            const Sim3d S0 = sim3_load(s_S64);
-            sim3_to_f32(S0, &s_S);
-            if (n_inv > 0) sim3_to_f32_pose(sim3_inv(S0), &s_Sinv);
+        int cnt = 0;
+        {
+            int before = incl - sg.count;
+#pragma unroll
+            for (int q = 0; q < kRefBlock / kWave; ++q) {
+                before += q < tid / kWave ? s_segw[q] : 0;
+                cnt += s_segw[q];
+            }
+            s_segx[tid] = before;
+            s_segp[tid] = sg.start - before;   // place of pair i: i + this
         }
-        const uint32_t cnt = h.ev_ctr[ev * kEvCtrs + kEvMatch];
-        const bool use_list = !h.refine_scan && cnt <= (uint32_t)ed.list_cap;
+        __syncthreads();
+        auto pair_at = [&](int i) -> const MatchRec& {
+            static_assert(kRefBlock == 512, "three rounds of eight");
+            int lo = 0;
+#pragma unroll
+            for (int step = 64; step >= 1; step /= 8) {
+                int n = 0;
+#pragma unroll
+                for (int q = 1; q < 8; ++q) n += s_segx[lo + q * step] <= i;
+                lo += n * step;
+            }
+            return h.match_stage[s_segp[lo] + i];
+        };
+        const bool use_list = !h.refine_scan && cnt <= ed.list_cap;
         // With the list, the event uses only as many workgroups as give each
         // thread one pair of each direction (every workgroup reads the same
         // counts, so all agree on Be); the others have nothing to add and
         // skip the event.
-        const uint32_t per_dir = max(cnt, (uint32_t)n_inv);
-        const int Be = use_list ? max(1, min(B, (int)((per_dir + blockDim.x - 1) / blockDim.x))) : B;
+        const int per_dir = max(cnt, n_inv);
+        const int Be = use_list ? max(1, min(B, (int)(((uint32_t)per_dir + blockDim.x - 1) / blockDim.x))) : B;
         if (b >= Be) {
             __syncthreads();
             continue;
@@ -1209,8 +1239,8 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
             ck_[r] = -1;
             cx_[r] = cy_[r] = cz_[r] = cu_[r] = cv_[r] = 0.0f;
             in_[r] = true;
-            if (use_list && i < (int)cnt) {
-                const MatchRec m = h.match_list[ed.list_off + i];
+            if (use_list && i < cnt) {
+                const MatchRec m = pair_at(i);
                 cx_[r] = m.x;
                 cy_[r] = m.y;
                 cz_[r] = m.z;
@@ -1231,6 +1261,11 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
             iv_ = h.inv_uv[2 * g + 1];
             const int k = h.inv_kf[g];
             ik_ = (k >= 0 && k < h.inv_n_kf) ? k : -1;
+        }
+        if (tid == 0) {   // (while the pairs arrive)
+            const Sim3d S0 = sim3_load(s_S64);
+            sim3_to_f32(S0, &s_S);
+            if (n_inv > 0) sim3_to_f32_pose(sim3_inv(S0), &s_Sinv);
         }
         __syncthreads();
         // it: evaluation index (round it / iters); seq: exchanges done, which
@@ -1281,11 +1316,11 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                         lossd += huber64(e, (double)delta);
                 };
                 cached(std::integral_constant<int, 0>{});
-                if (kRefCache > 1 && b * (int)blockDim.x + stride < (int)cnt) cached(std::integral_constant<int, 1>{});
-                if (kRefCache > 2 && b * (int)blockDim.x + 2 * stride < (int)cnt)
+                if (kRefCache > 1 && b * (int)blockDim.x + stride < cnt) cached(std::integral_constant<int, 1>{});
+                if (kRefCache > 2 && b * (int)blockDim.x + 2 * stride < cnt)
                     cached(std::integral_constant<int, kRefCache - 1>{});
-                for (int i = b * blockDim.x + tid + kRefCache * stride; i < (int)cnt; i += stride) {
-                    const MatchRec m = h.match_list[ed.list_off + i];
+                for (int i = b * blockDim.x + tid + kRefCache * stride; i < cnt; i += stride) {
+                    const MatchRec m = pair_at(i);
                     const KfDesc& kd = h.kf[m.kf];
                     double e;
                     if (bounded && !(pair_error64(s_Srs64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v,
@@ -1471,7 +1506,6 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
             }
             if (h.event_n_matched)
                 h.event_n_matched[ev] = s_fail ? -1 : (int32_t)(LM ? s_acc[35] : s_out[35]);
-            h.ev_ctr[ev * kEvCtrs + kEvMatch] = 0;   // the event's list is spent
         }
         __syncthreads();
     }

@@ -132,33 +132,62 @@ __device__ void block_exclusive_scan(int32_t* a, int n, int32_t* s_tmp) {
     __syncthreads();
 }
 
-// Workgroup exclusive scan of n_words packed pairs of 16-bit counts in place
-// (low half first): word k becomes (P, P + lo) for P the sum of every count
-// before it.  Every sum must stay below 65536.  Same shape as
-// block_exclusive_scan.
-__device__ void block_exclusive_scan_u16(uint32_t* w, int n, int32_t* s_tmp) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int lane = wave_lane(), wid = tid / kWave, nw = nt / kWave;
-    const int chunk = (n + nt - 1) / nt;
-    const int b = min(tid * chunk, n), e = min(b + chunk, n);
-    int sum = 0;
-    for (int i = b; i < e; ++i) sum += (int)(w[i] & 0xFFFFu) + (int)(w[i] >> 16);
+// 16-byte units of the 16-bit octave-bucket counts in LDS, and the bytes of
+// the bucket starts: those units behind one more, whose last entry is the
+// first start (0).  The counts alone are a whole number of units a thread
+// (64 x 48 cells of 8 groups: 3).
+__host__ __device__ inline int search_cs_units(int cells, int nb) { return (int)(((size_t)cells * nb + 7) / 8); }
+__host__ __device__ inline size_t search_cs_bytes(int cells, int nb) {
+    return 16 * (size_t)(search_cs_units(cells, nb) + 1);
+}
+constexpr int kCsFirst = 7;   // entry of the first start in the leading unit
+
+// Exclusive scan by a workgroup of kSearchBlock threads of n4 groups of four
+// words, each word a packed pair of 16-bit counts, in place (low half first):
+// a word becomes (P, P + lo) for P the sum of every count before it.  Every
+// sum must stay below 65536, so the halves never carry into each other and
+// both are added in one instruction: with four waves on a SIMD the vector
+// instructions bound this scan, one for a word's share of the sum and four
+// for its result.  Each thread takes a run of consecutive groups: with
+// 16-byte accesses at strides of 16, 32 or 48 bytes a wave's lanes share no
+// bank, and the groups of a short run stay in registers between the two
+// passes.  s_tmp needs one int a wave.
+__device__ __forceinline__ void block_exclusive_scan_u16(uint4* w, int n4, int32_t* s_tmp) {
+    constexpr int nt = kSearchBlock;
+    const int tid = threadIdx.x;
+    const int lane = wave_lane(), wid = tid / kWave;
+    const int chunk = (n4 + nt - 1) / nt;
+    const int b = min(tid * chunk, n4), e = min(b + chunk, n4);
+    constexpr int kRun = 3;
+    uint4 v[kRun];
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) v[j] = b + j < e ? w[b + j] : make_uint4(0, 0, 0, 0);
+    uint32_t both = 0;
+#pragma unroll
+    for (int j = 0; j < kRun; ++j) both += (v[j].x + v[j].y) + (v[j].z + v[j].w);
+    for (int i = b + kRun; i < e; ++i) both += (w[i].x + w[i].y) + (w[i].z + w[i].w);
+    const int sum = (int)((both & 0xFFFFu) + (both >> 16));
     const int incl = wave_incl_scan(sum);
     if (lane == kWave - 1) s_tmp[wid] = incl;
     __syncthreads();
-    if (wid == 0) {
-        const int t = lane < nw ? s_tmp[lane] : 0;
-        const int x = wave_incl_scan(t);
-        if (lane < nw) s_tmp[lane] = x - t;
-        if (lane == nw - 1) s_tmp[nw] = x;
-    }
-    __syncthreads();
-    uint32_t run = (uint32_t)(s_tmp[wid] + incl - sum);
-    for (int i = b; i < e; ++i) {
-        const uint32_t x = w[i], lo = x & 0xFFFFu, hi = x >> 16;
-        w[i] = run | ((run + lo) << 16);
-        run += lo + hi;
-    }
+    const int before = __builtin_amdgcn_readlane(wave_incl_scan(lane < wid ? s_tmp[lane] : 0), kWave - 1);
+    uint32_t run = (uint32_t)(before + incl - sum) * 0x10001u;   // in both halves
+    auto put = [&](int i, uint4 x) {
+        auto word = [&](uint32_t& y) {
+            const uint32_t c = y;
+            y = run + (c << 16);
+            run += c + __builtin_amdgcn_alignbit(c, c, 16);
+        };
+        word(x.x);
+        word(x.y);
+        word(x.z);
+        word(x.w);
+        w[i] = x;
+    };
+#pragma unroll
+    for (int j = 0; j < kRun; ++j)
+        if (b + j < e) put(b + j, v[j]);
+    for (int i = b + kRun; i < e; ++i) put(i, w[i]);
     __syncthreads();
 }
 
@@ -197,61 +226,114 @@ __device__ __forceinline__ int u16_fetch_add(uint32_t* w, int j) {
     return (int)((atomicAdd(&w[j >> 1], 1u << sh) >> sh) & 0xFFFFu);
 }
 
-template <bool STAGE_DESC>
-__device__ void stage_keyframe(const BatchHdr& h, const KfDesc& kd, uint16_t* s_cs, KpRec* s_rec, uint4* s_desc,
-                               int32_t* s_hash, int32_t* s_tmp) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const int n = kd.n_kp;
-    const int C = h.grid_cols, R = h.grid_rows, nb = h.oct_buckets;
-    const int entries = R * nb * C + 1;          // cell starts and the end
-    const int words = (entries + 1) / 2;
-    uint32_t* w = reinterpret_cast<uint32_t*>(s_cs);
-    const int hmask = h.lds_hash_mask;
-    const float* xy = h.kp_xy + 2 * (int64_t)kd.kp_off;
-    for (int c = tid; c < words; c += nt) w[c] = 0;
-    for (int s = tid; s <= hmask; s += nt) s_hash[s] = -1;
-    __syncthreads();
-    // cell of group g of keypoint i: (row * nb + g) * C + col
-    for (int i = tid; i < n; i += nt) {
-        const float x = xy[2 * i], y = xy[2 * i + 1];
-        const int base = cell_of(y, kd.invh, R) * nb * C + cell_of(x, kd.invw, C);
-        int ga, gb;
-        groups_of((int)h.kp_oct[kd.kp_off + i], nb, ga, gb);
-        if (ga >= 0) u16_fetch_add(w, base + ga * C + 1);
-        if (gb >= 0) u16_fetch_add(w, base + gb * C + 1);
-        const int32_t o = h.kp_owner[kd.kp_off + i];
-        if (o >= 0) owner_insert(s_hash, hmask, o);
+// The first kStagePre keypoints of a thread are loaded once, before the LDS
+// is cleared and the keyframe's descriptor is there, and kept for the scatter.
+// Clearing and scan move 16 bytes at a time.  At 1,000 keypoints and 64 x 48
+// cells of 8 groups (48 KB of counts) the staging takes 8,800 cycles; with
+// 4-byte accesses and the keypoints loaded where they are used it took 13,000.
+constexpr int kStagePre = 2;
+
+// What the staging needs of a keyframe.
+struct StageKf {
+    int32_t kp_off, n_kp;
+    float invw, invh;
+};
+
+struct StageKp {
+    float x, y;
+    int oct, own;
+    int ca, cb;   // its cells in up to two groups, or -1
+};
+
+// The launch's constants of the staging.
+struct StageEnv {
+    const float* xy;
+    const int8_t* oct;
+    const int32_t* own;
+    const uint8_t* desc;
+    int C, R, nb, hmask;
+    __device__ __forceinline__ StageKp load(const StageKf& k, int i) const {
+        const int64_t g = (int64_t)k.kp_off + i;
+        return {ldg(xy + 2 * g), ldg(xy + 2 * g + 1), (int)ldg(oct + g), ldg(own + g), -1, -1};
     }
+};
+
+__device__ __forceinline__ void stage_load(const StageEnv& env, const StageKf& kd, StageKp* pre) {
+#pragma unroll
+    for (int j = 0; j < kStagePre; ++j) {
+        const int i = (int)threadIdx.x + j * kSearchBlock;
+        if (i < kd.n_kp) pre[j] = env.load(kd, i);
+    }
+}
+
+template <bool STAGE_DESC>
+__device__ __forceinline__ void stage_build(const StageEnv& env, const StageKf& kd, StageKp* pre, uint4* s_cs,
+                                            KpRec* s_rec, uint4* s_desc, int32_t* s_hash, int32_t* s_tmp) {
+    constexpr int nt = kSearchBlock;
+    const int tid = threadIdx.x;
+    const int n = kd.n_kp, C = env.C, R = env.R, nb = env.nb;
+    const int n4 = search_cs_units(R * C, nb);
+    uint4* w4 = s_cs + 1;   // cell j's count, then its first slot, then (the scatter) the next cell's
+    uint32_t* w = reinterpret_cast<uint32_t*>(w4);
+    for (int c = tid; c <= n4; c += nt) s_cs[c] = make_uint4(0, 0, 0, 0);
+    for (int s = tid; s <= env.hmask; s += nt) s_hash[s] = -1;
     __syncthreads();
-    block_exclusive_scan_u16(w, words, s_tmp);   // entry 1 + j = first slot of cell j
-    for (int i = tid; i < n; i += nt) {
-        const float x = xy[2 * i], y = xy[2 * i + 1];
-        const int oct = (int)h.kp_oct[kd.kp_off + i];
-        const int base = cell_of(y, kd.invh, R) * nb * C + cell_of(x, kd.invw, C);
+    // cell of group g: (row * nb + g) * C + col
+    auto cells_of = [&](StageKp& k) {
+        const int base = cell_of(k.y, kd.invh, R) * (nb * C) + cell_of(k.x, kd.invw, C);
         int ga, gb;
-        groups_of(oct, nb, ga, gb);
+        groups_of(k.oct, nb, ga, gb);
+        k.ca = ga >= 0 ? base + ga * C : -1;
+        k.cb = gb >= 0 ? base + gb * C : -1;
+    };
+    auto count = [&](StageKp& k) {
+        cells_of(k);
+        if (k.ca >= 0) u16_fetch_add(w, k.ca);
+        if (k.cb >= 0) u16_fetch_add(w, k.cb);
+    };
+    auto list_owner = [&](const StageKp& k) {
+        if (k.own >= 0) owner_insert(s_hash, env.hmask, k.own);
+    };
+    auto scatter = [&](int i, const StageKp& k) {
         KpRec r;
-        r.x = x;
-        r.y = y;
+        r.x = k.x;
+        r.y = k.y;
         r.idx = i;
-        r.oct = oct;
+        r.oct = k.oct;
         uint4 d0 = make_uint4(0, 0, 0, 0), d1 = d0;
-        if (STAGE_DESC && (ga >= 0 || gb >= 0)) {
-            const uint4* src = reinterpret_cast<const uint4*>(h.kp_desc + 32 * ((int64_t)kd.kp_off + i));
-            d0 = src[0];
-            d1 = src[1];
-        }
+        if (STAGE_DESC && (k.ca >= 0 || k.cb >= 0)) load_desc(env.desc, (int64_t)kd.kp_off + i, d0, d1);
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int g = q ? gb : ga;
-            if (g < 0) continue;
-            const int slot = u16_fetch_add(w, base + g * C + 1);   // ends as the first slot of the next cell
+            const int c = q ? k.cb : k.ca;
+            if (c < 0) continue;
+            const int slot = u16_fetch_add(w, c);
             s_rec[slot] = r;
             if (STAGE_DESC) {
                 s_desc[2 * slot] = d0;
                 s_desc[2 * slot + 1] = d1;
             }
         }
+    };
+#pragma unroll
+    for (int j = 0; j < kStagePre; ++j)
+        if (tid + j * nt < n) count(pre[j]);
+#pragma unroll
+    for (int j = 0; j < kStagePre; ++j)
+        if (tid + j * nt < n) list_owner(pre[j]);
+    for (int i = tid + kStagePre * nt; i < n; i += nt) {
+        StageKp k = env.load(kd, i);
+        count(k);
+        list_owner(k);
+    }
+    __syncthreads();
+    block_exclusive_scan_u16(w4, n4, s_tmp);
+#pragma unroll
+    for (int j = 0; j < kStagePre; ++j)
+        if (tid + j * nt < n) scatter(tid + j * nt, pre[j]);
+    for (int i = tid + kStagePre * nt; i < n; i += nt) {
+        StageKp k = env.load(kd, i);
+        cells_of(k);
+        scatter(i, k);
     }
     __syncthreads();
 }
@@ -383,10 +465,20 @@ __device__ __forceinline__ void wave_append(bool want, uint32_t* counter, T* lis
 // and owner hash set in LDS; then its waves take the segment's pairs in
 // chunks of 64 x PPL (pair j of a chunk on lane j mod 64), each wave on its
 // own, with no barrier between chunks.  Provisional ADDs and accepted pairs
-// go to the workgroup's own list regions through LDS counters; at the end of
-// a segment its accepted pairs join their event's list with one device-scope
-// reservation.  The ADD conflicts are resolved by the next kernel on the
-// stream.
+// go to the workgroup's own list regions through LDS counters; a table says
+// which of its accepted pairs are whose event's, and the refinement reads them
+// where they are (joining the event's list, with a device-scope reservation
+// and a copy, took 6,000 to 8,000 cycles at the end of every workgroup).  The
+// ADD conflicts are resolved by the next kernel on the stream.
+
+// Zero in a vector register the compiler cannot see through: an atomic at
+// such an offset is left as written (at an address known to be uniform it is
+// given a reduction over the wave first, about 25 instructions for one lane).
+__device__ __forceinline__ int opaque_zero() {
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    return z;
+}
 
 struct KfView {
     const int32_t* cs;          // global grid: cell starts (one bucket per cell)
@@ -400,12 +492,6 @@ struct KfView {
     int32_t hash_mask;
     int32_t n_rec;              // records (slots) in rec
 };
-
-// Bytes of the 16-bit octave-bucket starts in LDS (a whole number of 16-byte
-// units).
-__host__ __device__ inline size_t search_cs_bytes(int cells, int nb) {
-    return ((size_t)cells * nb + 2 + 7) / 8 * 16;
-}
 
 // Record slots of a keyframe of kp_cap keypoints in nb octave groups (a
 // keypoint sits in up to two groups when nb > 1).
@@ -431,25 +517,43 @@ struct PairIn {
     uint8_t dec;
 };
 
-__device__ __forceinline__ void load_pair(const BatchHdr& h, const KfDesc& kd, bool dense, int gate, int64_t o,
-                                          int64_t se, PairIn& p) {
-    p.dec = o < se ? kDecUndecided : (uint8_t)0;
+// The launch's point arrays (mp_id may be null; pair_mp is read unless dense).
+struct PointEnv {
+    const int32_t* pair_mp;
+    const int32_t* id;
+    const float* xyz;
+    const float* dmax;
+    bool dense;
+    int gate;
+};
+
+// The pairs [o, o + 64) of a wave, one a lane, n of them (any n) to be
+// searched.  First the point's index in its event (-1: no pair), then the
+// point: two dependent loads, in flight during different chunks.  Addresses
+// are a scalar base and the lane.
+__device__ __forceinline__ int32_t load_index(const PointEnv& env, const KfDesc& kd, int64_t o, int n) {
+    const uint32_t lane = (uint32_t)wave_lane();
+    int32_t lp = -1;
+    if ((int)lane < n) lp = env.dense ? (int32_t)(o - kd.pair_off) + (int32_t)lane : ldg(env.pair_mp + o + lane);
+    return lp;
+}
+
+typedef float v3f __attribute__((ext_vector_type(3), aligned(4)));
+
+__device__ __forceinline__ void load_point(const PointEnv& env, const KfDesc& kd, int32_t lp, int n, PairIn& p) {
+    p.dec = FL_INVALID;
     p.gp = 0;
     p.id = -1;
     p.x = p.y = p.z = p.dm = 0.0f;
-    if (o < se) {
-        const int64_t j = o - kd.pair_off;
-        const int32_t lp = dense ? (int32_t)j : ldg(h.pair_mp + o);
-        if (lp < 0 || lp >= kd.n_mp) {
-            p.dec = FL_INVALID;
-        } else {
-            p.gp = kd.mp_off + lp;
-            p.id = h.mp_id ? ldg(h.mp_id + p.gp) : p.gp;
-            p.x = ldg(h.mp_xyz + 3 * (int64_t)p.gp);
-            p.y = ldg(h.mp_xyz + 3 * (int64_t)p.gp + 1);
-            p.z = ldg(h.mp_xyz + 3 * (int64_t)p.gp + 2);
-            if (gate) p.dm = ldg(h.mp_dmax + p.gp);
-        }
+    if (wave_lane() < n && lp >= 0 && lp < kd.n_mp) {
+        p.dec = kDecUndecided;
+        p.gp = kd.mp_off + lp;
+        p.id = env.id ? ldg(env.id + p.gp) : p.gp;
+        const v3f x = *(const gmem<v3f>*)(env.xyz + 3 * (int64_t)p.gp);
+        p.x = x.x;
+        p.y = x.y;
+        p.z = x.z;
+        if (env.gate) p.dm = ldg(env.dmax + p.gp);
     }
 }
 
@@ -471,24 +575,16 @@ struct OctaveTable {
     float r0;
 };
 
-// The first n with d * sf[n] >= dmax, else N - 1 (the oracle's loop; the
-// first kOctReg tests without branches).
+// The first n with d * sf[n] >= dmax, else N - 1: the first kOctReg tests
+// from the last to the first without branches (entries past N, if any test
+// true, come after every real one and are cut to N - 1).
 __device__ __forceinline__ int predict_octave(const OctaveTable& T, float d, float dmax) {
-    int pred = T.N - 1;
-    bool found = false;
+    int pred = kOctReg;
 #pragma unroll
-    for (int n = 0; n < kOctReg; ++n) {
-        const bool hit = (!found) & (n < T.N) & (d * T.sf[n] >= dmax);
-        pred = hit ? n : pred;
-        found = found | hit;
-    }
-    if (!found)
-        for (int n = kOctReg; n < T.N; ++n)
-            if (d * T.all[n] >= dmax) {
-                pred = n;
-                break;
-            }
-    return pred;
+    for (int n = kOctReg - 1; n >= 0; --n) pred = d * T.sf[n] >= dmax ? n : pred;
+    if (T.N > kOctReg && pred == kOctReg)
+        while (pred < T.N - 1 && !(d * T.all[pred] >= dmax)) ++pred;
+    return min(pred, T.N - 1);
 }
 
 // Window half-width r0 * sf[pred] (sf from LDS: a lane-dependent index into
@@ -549,8 +645,8 @@ __device__ __forceinline__ bool search_front(const KfDesc& kd, const KfView& v, 
         hh = owner_slot(p.id, v.hash_mask);
         hv = v.hash[hh];
     }
-    Proj pr{};
-    const bool vis = p.dec == kDecUndecided && project_uv(kd, p.x, p.y, p.z, pr);
+    Proj pr;
+    const bool vis = project_uv(kd, p.x, p.y, p.z, pr);
     q.pred = gate ? predict_octave(T, pr.d, p.dm) : T.N - 1;
     const float rad = window_radius(T, q.pred);
     Window& w = q.w;
@@ -568,9 +664,10 @@ __device__ __forceinline__ bool search_front(const KfDesc& kd, const KfView& v, 
     q.nrows = w.r1 - w.r0 + 1;
     // the runs of the first kRowSeg rows (named values, not arrays: an array
     // indexed by a lane-dependent value would be placed in scratch memory)
+    const int idx0 = (int)__umul24(__umul24(w.r0, nb) + q.grp, C), row = nb * C;
     auto run = [&](int j, int c_in, int& b_out, int& c_out) {
         const bool in = j < q.nrows;
-        const int idx = ((in ? w.r0 + j : w.r0) * nb + q.grp) * C;
+        const int idx = idx0 + (in ? j * row : 0);
         const int s0 = cs_at(idx + w.c0), e0 = cs_at(idx + w.c1 + 1);
         b_out = s0 - c_in;
         c_out = c_in + (in ? e0 - s0 : 0);
@@ -753,12 +850,18 @@ __device__ __forceinline__ void search_scan(const KfView& v, int gate, int C, co
 }
 
 // The decision of a searched pair from its best and second.
+// With kp_xy, also the accepted keypoint's position (the two loads together).
 __device__ __forceinline__ void search_back(const KfDesc& kd, int hamming_th, float nn_ratio,
-                                            const int32_t* kp_owner, PairIn& p, PairRes& res) {
+                                            const int32_t* kp_owner, const float* kp_xy, PairIn& p, PairRes& res) {
     if (!accept_match(res.best, hamming_th, nn_ratio)) {
         p.dec = FL_NO_MATCH;
     } else {
-        const int32_t ow = ldg(kp_owner + kd.kp_off + (int32_t)(res.best.key & 0xFFFFu));
+        const int64_t kg = (int64_t)kd.kp_off + (res.best.key & 0xFFFFu);
+        const int32_t ow = ldg(kp_owner + kg);
+        if (kp_xy) {
+            res.ku = ldg(kp_xy + 2 * kg);
+            res.kv = ldg(kp_xy + 2 * kg + 1);
+        }
         if (ow >= 0) {
             p.dec = FL_FUSE;
             res.target = ow;
@@ -768,84 +871,116 @@ __device__ __forceinline__ void search_back(const KfDesc& kd, int hamming_th, fl
     }
 }
 
+// The workgroup's accepted pairs by event: the table entry of the event whose
+// pairs are being searched is written when the next begins (or, event < 0, at
+// the end).  The workgroup's counts are complete when it is called.
+struct MatchSegs {
+    int event;
+    uint32_t m0;   // first staged pair of the event
+    __device__ __forceinline__ void next(const BatchHdr& h, const WgRange& rg, const unsigned long long* s_list,
+                                         int e) {
+        const uint32_t m = (uint32_t)(s_list[0] >> 32);
+        if (threadIdx.x == 0 && event >= 0)
+            h.match_seg[rg.chunk + event] = MatchSeg{(int32_t)(rg.priv_off + m0), (int32_t)(m - m0)};
+        event = e;
+        m0 = m;
+    }
+};
+
 template <int PPL, int MODE, bool STATS>
 __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchHdr* __restrict__ hp) {
     extern __shared__ __align__(16) unsigned char s_mem[];
     const BatchHdr& h = *hp;
     const int tid = threadIdx.x;
     const int lane = wave_lane();
+    __shared__ unsigned long long s_list[1];   // running counts: ADD region (low half), accepted-pair region
+    __shared__ WaveCand s_wc[kWavesPerWG];   // each wave's candidate queue, best and second
+    __shared__ float s_sf[FL_MAX_OCTAVES];
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    constexpr int nw = kWavesPerWG;
+
+    // Every load of the prologue is issued before the first is waited for: a
+    // launch starts with the header, the ranges and the keyframe table in
+    // memory only (the table fetch wrote them), and a trip there is about
+    // 2,000 cycles.  The range and the keyframe table sit at offsets of the
+    // table blob that follow from the grid size, so neither waits for a
+    // pointer, and the range holds what the first keyframe's own loads need.
+    const char* blob = reinterpret_cast<const char*>(hp);
+    const WgRange rg = reinterpret_cast<const WgRange*>(blob + blob_range_offset())[blockIdx.x];
+    const KfDesc* kf_tab = reinterpret_cast<const KfDesc*>(blob + blob_kf_offset((int)gridDim.x));
+    const float sf_lane = h.sf[tid & (FL_MAX_OCTAVES - 1)];
+    OctaveTable T;
+    T.all = s_sf;
+    T.N = uniform_i(h.n_octaves);
+#pragma unroll
+    for (int n = 0; n < kOctReg; ++n) T.sf[n] = uniform_f(h.sf[n]);
+    // header fields read per pair, held in scalar registers (the output
+    // stores below could otherwise be taken to alias the header)
+    const int gate = uniform_i(h.gate), C = uniform_i(h.grid_cols), R = uniform_i(h.grid_rows);
+    const PointEnv points{uniform_p(h.pair_mp), uniform_p(h.mp_id), uniform_p(h.mp_xyz), uniform_p(h.mp_dmax),
+                          uniform_i(h.dense) != 0, gate};
+    const int nb = MODE == kModeGlobal ? 1 : uniform_i(h.oct_buckets);
+    const StageEnv stage{uniform_p(h.kp_xy), uniform_p(h.kp_oct), uniform_p(h.kp_owner), uniform_p(h.kp_desc),
+                         C, R, nb, uniform_i(h.lds_hash_mask)};
+    const int kp_cap = uniform_i(h.lds_kp_cap);
+    const bool want_matches = uniform_i(h.refine_iters) > 0;
+    const int32_t* const kp_owner = stage.own;
+    const float* const kp_xy = stage.xy;
+    const uint8_t* const mp_desc = uniform_p(h.mp_desc);
+    unsigned long long* const claim = uniform_p(h.claim);
+    AddRef* const add_list = uniform_p(h.add_list);
+    MatchRec* const match_stage = uniform_p(h.match_stage);
+    const uint32_t epoch = ldg(h.epoch);   // (a vector register: waited for where it is used)
+    unsigned long long st[4] = {0, 0, 0, 0};
+
     KpRec* s_rec = reinterpret_cast<KpRec*>(s_mem);
     uint4* s_desc = nullptr;
-    uint16_t* s_cs = nullptr;
+    uint4* s_cs = nullptr;
     int32_t* s_hash = nullptr;
     int32_t* s_tmp = nullptr;
-    // running counts of the workgroup's ADD and accepted-pair regions, then
-    // the segment's accepted-pair total and its base in the event's list
-    __shared__ uint32_t s_list[4];
-    __shared__ WaveCand s_wc[kWavesPerWG];   // each wave's candidate queue, best and second
-    const int wid = tid / kWave, nw = (int)(blockDim.x / kWave);
     if (MODE != kModeGlobal) {
-        const size_t slots = (size_t)search_slots(h.lds_kp_cap, h.oct_buckets);
+        const size_t slots = (size_t)search_slots(kp_cap, nb);
         unsigned char* p = s_mem + 16 * slots;
         if (MODE == kModeLdsDesc) {
             s_desc = reinterpret_cast<uint4*>(p);
             p += 32 * slots;
         }
-        s_cs = reinterpret_cast<uint16_t*>(p);
-        p += search_cs_bytes(h.cells, h.oct_buckets);
+        s_cs = reinterpret_cast<uint4*>(p);
+        p += search_cs_bytes(C * R, nb);
         s_hash = reinterpret_cast<int32_t*>(p);
-        p += 4 * (size_t)(h.lds_hash_mask + 1);
+        p += 4 * (size_t)(stage.hmask + 1);
         s_tmp = reinterpret_cast<int32_t*>(p);
-        p += 4 * (size_t)(kSearchBlock / kWave + 4);
     }
-    if (tid == 0) {
-        s_list[0] = 0;
-        s_list[1] = 0;
-    }
-    s_wc[tid / kWave].mark[lane] = -1;
-
-    // the octave scale table in LDS: the octave search and the window radius
-    // index it per lane.  In the LDS modes the barrier that opens the first
-    // keyframe's staging publishes it (and the counters above), so the first
-    // point loads are issued without waiting here.
-    __shared__ float s_sf[FL_MAX_OCTAVES];
-    if (tid < FL_MAX_OCTAVES) s_sf[tid] = h.sf[tid];
+    if (tid == 0) s_list[0] = 0;
+    s_wc[wid].mark[lane] = -1;
+    // the octave scale table in LDS (the octave search and the window radius
+    // index it per lane): published, as the counters above, by the first
+    // keyframe's staging in the LDS modes
+    if (tid < FL_MAX_OCTAVES) s_sf[tid] = sf_lane;
     if (MODE == kModeGlobal) __syncthreads();
-    OctaveTable T;
-    T.all = s_sf;
-    T.N = h.n_octaves;
-#pragma unroll
-    for (int n = 0; n < kOctReg; ++n) T.sf[n] = uniform_f(h.sf[n]);
-    T.N = uniform_i(T.N);
-    const int gate = uniform_i(h.gate), C = uniform_i(h.grid_cols), R = uniform_i(h.grid_rows);
-    const bool dense = uniform_i(h.dense) != 0;
-    const bool want_matches = uniform_i(h.refine_iters) > 0;
-    const unsigned long long tag = (unsigned long long)(uint32_t)uniform_i((int32_t)*h.epoch) << 32;
-    // header fields read per pair, held in scalar registers (the output
-    // stores below could otherwise be taken to alias the header)
-    const int32_t* const kp_owner = uniform_p(h.kp_owner);
-    const float* const kp_xy = uniform_p(h.kp_xy);
-    const uint8_t* const mp_desc = uniform_p(h.mp_desc);
-    unsigned long long* const claim = uniform_p(h.claim);
-    AddRef* const add_list = uniform_p(h.add_list);
-    MatchRec* const match_stage = uniform_p(h.match_stage);
-    unsigned long long st[4] = {0, 0, 0, 0};
 
-    // The range and the keyframe table sit at offsets of the table blob that
-    // follow from the grid size, so neither waits for a pointer.
-    const char* blob = reinterpret_cast<const char*>(hp);
-    const WgRange rg = reinterpret_cast<const WgRange*>(blob + blob_range_offset())[blockIdx.x];
-    const KfDesc* kf_tab = reinterpret_cast<const KfDesc*>(blob + blob_kf_offset((int)gridDim.x));
     int slot = rg.slot;
     int staged = -1;
-    uint32_t seg_m0 = 0;   // first staged accepted pair of the current segment
+    MatchSegs segs{rg.event, 0};
     for (int t = rg.t0; t < rg.t1;) {
-        while (t >= h.tile_prefix[slot + 1]) ++slot;
-        const int k = t == rg.t0 ? rg.kf : h.kf_order[slot];
-        const int tb = h.tile_prefix[slot];
-        const int t_end = min(rg.t1, h.tile_prefix[slot + 1]);
+        const bool first = t == rg.t0;
+        int k = rg.kf, tb = rg.slot_t0, te = rg.slot_t1, pass = rg.pass, key = rg.stage_key;
+        StageKf sk{rg.kp_off, rg.n_kp, rg.invw, rg.invh};
+        if (!first) {
+            while (t >= uniform_i(h.tile_prefix[slot + 1])) ++slot;
+            k = uniform_i(h.kf_order[slot]);
+            tb = uniform_i(h.tile_prefix[slot]);
+            te = uniform_i(h.tile_prefix[slot + 1]);
+            const KfDesc& kn = kf_tab[k];
+            pass = uniform_i(kn.pass);
+            key = uniform_i(kn.stage_key);
+            sk = {uniform_i(kn.kp_off), uniform_i(kn.n_kp), uniform_f(kn.invw), uniform_f(kn.invh)};
+        }
+        StageKp pre[kStagePre];
+        const bool build = MODE != kModeGlobal && staged != key;
+        if (build) stage_load(stage, sk, pre);
         const KfDesc kd = uniform_kf(kf_tab[k]);   // scalar registers, kept across the stores below
-        PassOut po = h.out[kd.pass];
+        PassOut po = h.out[pass];
         po.best_idx = uniform_p(po.best_idx);
         po.best_dist = uniform_p(po.best_dist);
         po.second_dist = uniform_p(po.second_dist);
@@ -853,12 +988,37 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
         po.target = uniform_p(po.target);
         po.hamming_th = uniform_i(po.hamming_th);
         po.nn_ratio = uniform_f(po.nn_ratio);
-        po.r0 = uniform_f(po.r0);
-        T.r0 = po.r0;
+        T.r0 = uniform_f(po.r0);
+        const int t_end = min(rg.t1, te);
         const int64_t kend = kd.pair_off + kd.n_pairs;
         const int64_t sb = kd.pair_off + (int64_t)(t - tb) * kd.tile_pairs;
         const int64_t se = min(kd.pair_off + (int64_t)(t_end - tb) * kd.tile_pairs, kend);
         t = t_end;
+        if (want_matches && kd.event != segs.event) {
+            __syncthreads();   // every pair of the events before is listed
+            segs.next(h, rg, s_list, kd.event);
+            __syncthreads();
+        }
+        // The points of a wave's next chunk are loaded while its current
+        // chunk is evaluated (and the point indices of the one after), those
+        // of its first while the keyframe is staged: their latency overlaps.
+        constexpr int kChunk = kWave * PPL;
+        const int64_t n_chunks = (se - sb + kChunk - 1) / kChunk;
+        // pairs of the 64 from pair o on (any value <= 0: none)
+        auto left = [&](int64_t o) { return (int)min(se - o, (int64_t)kWave); };
+        PairIn pn[PPL];
+        int32_t ln[PPL];
+#pragma unroll
+        for (int r = 0; r < PPL; ++r) {
+            const int64_t o = sb + (int64_t)wid * kChunk + r * kWave;
+            ln[r] = load_index(points, kd, o, left(o));
+        }
+#pragma unroll
+        for (int r = 0; r < PPL; ++r) {
+            const int64_t o = sb + (int64_t)wid * kChunk + r * kWave;
+            load_point(points, kd, ln[r], left(o), pn[r]);
+            ln[r] = load_index(points, kd, o + nw * kChunk, left(o + nw * kChunk));
+        }
 
         KfView v;
         if (MODE == kModeGlobal) {
@@ -873,48 +1033,37 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
             v.hash = h.hash + kd.hash_off;
             v.hash_mask = kd.hash_mask;
         } else {
-            if (staged != kd.stage_key) {
-                __syncthreads();   // every reader of the previous keyframe is done
-                stage_keyframe<MODE == kModeLdsDesc>(h, kd, s_cs, s_rec, s_desc, s_hash, s_tmp);
-                staged = kd.stage_key;
+            if (build) {
+                if (staged >= 0) __syncthreads();   // every reader of the previous keyframe is done
+                stage_build<MODE == kModeLdsDesc>(stage, sk, pre, s_cs, s_rec, s_desc, s_hash, s_tmp);
+                staged = key;
             }
             v.cs = nullptr;
-            v.cs16 = s_cs;
-            v.nb = uniform_i(h.oct_buckets);
+            v.cs16 = reinterpret_cast<const uint16_t*>(s_cs) + kCsFirst;
+            v.nb = nb;
             v.rec = s_rec;
-            v.n_rec = search_slots(uniform_i(h.lds_kp_cap), uniform_i(h.oct_buckets));
+            v.n_rec = search_slots(kp_cap, nb);
             v.desc = MODE == kModeLdsDesc ? s_desc : nullptr;
-            v.desc_orig = h.kp_desc + 32 * (int64_t)kd.kp_off;
+            v.desc_orig = stage.desc + 32 * (int64_t)kd.kp_off;
             v.own = nullptr;
             v.hash = s_hash;
-            v.hash_mask = h.lds_hash_mask;
+            v.hash_mask = stage.hmask;
         }
 
-        constexpr int kChunk = kWave * PPL;
-        const int64_t n_chunks = (se - sb + kChunk - 1) / kChunk;
-        const unsigned long long below = (1ull << lane) - 1ull;
-        // The points of a wave's next chunk are loaded while its current
-        // chunk is evaluated (their latency overlaps the evaluation).
-        PairIn pn[PPL];
-        if (wid < n_chunks) {
-#pragma unroll
-            for (int r = 0; r < PPL; ++r)
-                load_pair(h, kd, dense, gate, sb + wid * kChunk + r * kWave + lane, se, pn[r]);
-        }
         for (int64_t c = wid; c < n_chunks; c += nw) {
             const int64_t cb = sb + c * kChunk;
             PairIn p[PPL];
 #pragma unroll
-            for (int r = 0; r < PPL; ++r) p[r] = pn[r];
-            if (c + nw < n_chunks) {
-#pragma unroll
-                for (int r = 0; r < PPL; ++r)
-                    load_pair(h, kd, dense, gate, cb + nw * kChunk + r * kWave + lane, se, pn[r]);
+            for (int r = 0; r < PPL; ++r) {
+                const int64_t o1 = cb + nw * kChunk + r * kWave, o2 = o1 + nw * kChunk;
+                p[r] = pn[r];
+                load_point(points, kd, ln[r], left(o1), pn[r]);
+                ln[r] = load_index(points, kd, o2, left(o2));
             }
 #pragma unroll
             for (int r = 0; r < PPL; ++r) {
-                const int64_t o = cb + r * kWave + lane;
-                const bool active = o < se;
+                const int64_t o = cb + r * kWave;   // lane 0's pair
+                const bool active = lane < left(o);
                 PairRes res;
                 res.target = -1;
                 res.ku = res.kv = 0.0f;
@@ -924,75 +1073,69 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
                 search_scan<MODE, STATS>(v, gate, C, mp_desc, p[r], sq, wc, st);
                 res.best.key = wc.best[lane];
                 res.best.second = (int)wc.second[lane];
-                if (searching) search_back(kd, po.hamming_th, po.nn_ratio, kp_owner, p[r], res);
+                if (searching)
+                    search_back(kd, po.hamming_th, po.nn_ratio, kp_owner, want_matches ? kp_xy : nullptr, p[r], res);
+                // Stores and loads are counted together, in order: the next
+                // chunk's loads are waited for here (they were issued before
+                // this chunk's scan), not behind the stores below.
+#pragma unroll
+                for (int i = 0; i < PPL; ++i)
+                    asm volatile("" : "+v"(pn[i].x), "+v"(pn[i].y), "+v"(pn[i].z), "+v"(pn[i].dm), "+v"(pn[i].id),
+                                      "+v"(ln[i]));
                 const uint32_t key = res.best.key;
                 const int bidx = key == 0xFFFFFFFFu ? -1 : (int)(key & 0xFFFFu);
                 const int kpg = kd.claim_off + (bidx < 0 ? 0 : bidx);   // claim slot
+                const uint32_t ul = (uint32_t)lane;
                 if (active) {
-                    stg(po.best_idx + o, (int32_t)bidx);
-                    stg(po.best_dist + o, (int16_t)(key == 0xFFFFFFFFu ? FL_NO_DIST : (int)(key >> 16)));
-                    stg(po.second_dist + o, (int16_t)res.best.second);
-                    stg(po.decision + o, p[r].dec);
-                    stg(po.target + o, res.target);
+                    stg(po.best_idx + o + ul, (int32_t)bidx);
+                    stg(po.best_dist + o + ul, (int16_t)(key == 0xFFFFFFFFu ? FL_NO_DIST : (int)(key >> 16)));
+                    stg(po.second_dist + o + ul, (int16_t)res.best.second);
+                    stg(po.decision + o + ul, p[r].dec);
+                    stg(po.target + o + ul, res.target);
                 }
                 const bool is_add = active && p[r].dec == FL_ADD;
                 const bool acc = want_matches && active && (p[r].dec == FL_ADD || p[r].dec == FL_FUSE);
                 if (is_add)
                     __hip_atomic_fetch_min((gmem<unsigned long long>*)(claim + kpg),
-                                           tag | (uint32_t)p[r].gp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                // one LDS reservation per wave and list
+                                           (unsigned long long)epoch << 32 | (uint32_t)p[r].gp, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                // one LDS reservation per wave for both lists
                 const unsigned long long ma = __ballot(is_add), mm = __ballot(acc);
-                uint32_t ba = 0, bm = 0;
-                if (lane == 0) {
-                    if (ma) ba = atomicAdd(&s_list[0], (uint32_t)__popcll(ma));
-                    if (mm) bm = atomicAdd(&s_list[1], (uint32_t)__popcll(mm));
-                }
-                ba = (uint32_t)__shfl((int)ba, 0);
-                bm = (uint32_t)__shfl((int)bm, 0);
+                if ((ma | mm) == 0) continue;
+                unsigned long long at = 0;
+                if (lane == 0)
+                    at = atomicAdd(&s_list[opaque_zero()],
+                                   (unsigned long long)__popcll(mm) << 32 | (unsigned long long)__popcll(ma));
+                const uint32_t ba = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)at);
+                const uint32_t bm = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(at >> 32));
                 if (is_add) {
                     AddRef e;
-                    e.pair = (int32_t)o;
+                    e.pair = (int32_t)(o + lane);
                     e.kp = kpg;
                     e.gp = p[r].gp;
-                    e.pass = kd.pass;
-                    stg_rec(add_list + rg.priv_off + ba + (uint32_t)__popcll(ma & below), e);
+                    e.pass = pass;
+                    stg_rec(add_list + rg.priv_off + ba + __builtin_amdgcn_mbcnt_hi((uint32_t)(ma >> 32),
+                                __builtin_amdgcn_mbcnt_lo((uint32_t)ma, 0u)), e);
                 }
                 if (acc) {
                     // the matched keypoint's observation
-                    const int64_t kg = (int64_t)kd.kp_off + bidx;
                     MatchRec me;
                     me.x = p[r].x;
                     me.y = p[r].y;
                     me.z = p[r].z;
-                    me.u = ldg(kp_xy + 2 * kg);
-                    me.v = ldg(kp_xy + 2 * kg + 1);
+                    me.u = res.ku;
+                    me.v = res.kv;
                     me.kf = k;
                     me.pad0 = me.pad1 = 0;
-                    stg_rec(match_stage + rg.priv_off + bm + (uint32_t)__popcll(mm & below), me);
+                    stg_rec(match_stage + rg.priv_off + bm + __builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32),
+                                __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u)), me);
                 }
             }
         }
-        if (want_matches) {
-            // the segment's accepted pairs join their event's list
-            __syncthreads();
-            if (tid == 0) {
-                const uint32_t tot = s_list[1];
-                s_list[2] = tot;
-                s_list[3] = tot > seg_m0 ? atomicAdd(&h.ev_ctr[kd.event * kEvCtrs + kEvMatch], tot - seg_m0) : 0u;
-            }
-            __syncthreads();
-            const uint32_t tot = s_list[2], base = s_list[3];
-            const EventDesc& ed = h.ev[kd.event];
-            const int32_t list_off = ed.list_off, list_cap = ed.list_cap;
-            for (uint32_t i = seg_m0 + tid; i < tot; i += blockDim.x) {
-                const uint32_t idx = base + (i - seg_m0);
-                if (idx < (uint32_t)list_cap) h.match_list[list_off + idx] = h.match_stage[rg.priv_off + i];
-            }
-            seg_m0 = tot;
-        }
     }
-    __syncthreads();   // every ADD of the workgroup is counted
-    if (tid == 0) h.add_count[blockIdx.x] = s_list[0];
+    __syncthreads();   // every ADD and accepted pair of the workgroup is counted
+    if (tid == 0) h.add_count[blockIdx.x] = (uint32_t)s_list[0];
+    if (want_matches) segs.next(h, rg, s_list, -1);
     if (STATS) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
