@@ -10,7 +10,6 @@
 #include <cstring>
 #include <numeric>
 #include <mutex>
-#include <queue>
 #include <vector>
 
 #include "fastloop.h"
@@ -116,7 +115,7 @@ struct fl_ctx {
     size_t lds_max = 65536;     // dynamic LDS per workgroup the device allows
     DevBuf ws;                  // batched workspace (tables, global grids, lists, partials)
     DevBuf claims;              // ADD claims, 0xFF.. between epochs
-    DevBuf ctrs;                // stats + per-keyframe + per-event counters, zero at rest
+    DevBuf ctrs;                // statistics and epoch, then the ranges' counters
     DevBuf diag;                // sink of the VALU issue-rate probe
     DevBuf plain;               // plain-path workspace
     DevBuf res;                 // residual partials and done counter
@@ -308,6 +307,11 @@ int validate_batch(const fl_batch* B, const fl_params* P, const fl_fuse_out* out
 
 constexpr int kPrepGrid = 512;     // workgroups of the global-grid build
 constexpr int kRefineGrid = 256;   // workgroups of a refinement step
+// Cost of one keyframe's staging in tiles of one pair a lane in an empty image
+// (a tile's cost grows with the keypoint density): 9,000 cycles against about
+// 470 for a tile of 64 pairs at 1,200 keypoints, whose weight is 1.8.
+constexpr float kStageCost = 36.0f;
+constexpr int kLongRange = 64;   // tiles per slot: four rounds of a workgroup's waves
 
 struct Prepared {
     std::vector<char> blob;     // header + tables, uploaded per call
@@ -320,6 +324,7 @@ struct Prepared {
     int refine_iters = 0;
     int refine_variant = 0;           // refinement kernel: bit 0 Levenberg-Marquardt, bit 1 rounds
     bool resolve_in_refine = false;   // the refinement launch resolves the ADD conflicts
+    int n_ctr = 0;                    // ranges whose counters the table fetch clears
 };
 
 template <typename T>
@@ -329,54 +334,102 @@ size_t blob_take(std::vector<char>& blob, size_t n) {
     return off;
 }
 
-// Pairs per tile of every keyframe; returns the number of tiles.  A
-// workgroup runs on one CU and spreads a tile's waves over its four SIMDs,
-// so a tile takes time in proportion to its waves per SIMD.  Full tiles
-// (tile_cap pairs) are the fewest; while they number fewer than the
-// workgroup slots, the spare slots go one at a time to the keyframe whose
-// tiles cost most (pairs times the keypoint density the candidate scan
-// meets), which cuts that keyframe into more, smaller tiles.  A tile of more
-// than 256 pairs is a multiple of 256 (the same waves on every SIMD), a
-// smaller one a multiple of 64.
-int64_t plan_tiles(const std::vector<int64_t>& pairs, const std::vector<int32_t>& kps, int cells, int64_t tile_cap,
-                   int slots, std::vector<int32_t>& tile) {
-    const int n_kf = (int)pairs.size();
-    tile.assign(n_kf, (int32_t)tile_cap);
-    std::vector<int64_t> nt(n_kf, 0), most(n_kf, 0);
-    std::vector<double> cost(n_kf, 0.0);
+// The split of the tiles (in keyframe order) into contiguous ranges, one a
+// workgroup, at most `slots` of them: bound[i] is the first tile of range i.
+// A range costs what its tiles cost (weight[k] for one of keyframe k) and
+// `stage` for every keyframe it touches, whose grid the workgroup builds
+// first.  With more keyframes than slots a range spans several anyway, and
+// past kLongRange tiles one more staging is little (and who is done early
+// helps): the ranges get equal shares of the total.  Otherwise the longest range
+// is what the launch takes, and its least length is searched for: a range that would
+// reach into the next keyframe for a few tiles only pays a second staging (of
+// 20 keyframes over 256 workgroups, ranges of equal tile counts put one in
+// six across two keyframes, and those took 14.2 us where the others took
+// 10.5; twice that where each keyframe is searched in two passes).
+void plan_ranges(const std::vector<int64_t>& tiles, const std::vector<float>& weight, float stage, int slots,
+                 std::vector<int64_t>& bound) {
+    const int n = (int)tiles.size();
     int64_t total = 0;
-    for (int k = 0; k < n_kf; ++k) {
-        const int64_t np = pairs[k];
-        const int n_kp = kps[k];
-        nt[k] = (np + tile_cap - 1) / tile_cap;
-        most[k] = (np + kWave - 1) / kWave;
-        cost[k] = (double)np * (1.0 + 2.0 * n_kp / std::max(1, cells));
-        total += nt[k];
+    double cost = 0.0, longest = 0.0;
+    int used = 0;
+    for (int k = 0; k < n; ++k) {
+        if (tiles[k] <= 0) continue;
+        ++used;
+        total += tiles[k];
+        cost += stage + (double)weight[k] * tiles[k];
+        longest = std::max<double>(longest, stage + weight[k]);
     }
-    if (total < slots) {
-        std::priority_queue<std::pair<double, int>> q;   // (cost per tile, keyframe)
-        for (int k = 0; k < n_kf; ++k)
-            if (nt[k] > 0 && nt[k] < most[k]) q.push({cost[k] / (double)nt[k], k});
-        while (total < slots && !q.empty()) {
-            const int k = q.top().second;
-            q.pop();
-            ++nt[k];
-            ++total;
-            if (nt[k] < most[k]) q.push({cost[k] / (double)nt[k], k});
+    bound.assign(1, 0);
+    if (total <= slots) {   // one tile each
+        for (int64_t t = 1; t < total; ++t) bound.push_back(t);
+    } else if (used > slots || total > (int64_t)kLongRange * slots) {
+        double at = 0.0;
+        int64_t t = 0;
+        int i = 1;
+        for (int k = 0; k < n; ++k) {
+            if (tiles[k] <= 0) continue;
+            at += stage;
+            const double end = at + (double)weight[k] * tiles[k];
+            for (; i < slots && cost * i / slots < end; ++i) {
+                const double j = std::ceil((cost * i / slots - at) / weight[k]);
+                bound.push_back(std::max(bound.back(), t + std::min<int64_t>(std::max<int64_t>((int64_t)j, 0), tiles[k])));
+            }
+            at = end;
+            t += tiles[k];
         }
+    } else {
+        // ranges of cost at most T, in order; their number, and (out) their bounds
+        auto split = [&](double T, std::vector<int64_t>* out) -> int {
+            int count = 0;
+            double acc = 0.0;   // cost of the open range (0: none open)
+            int64_t t = 0;
+            for (int k = 0; k < n; ++k) {
+                int64_t rem = tiles[k];
+                if (rem <= 0) continue;
+                const double w = weight[k];
+                const double per = std::max(1.0, std::floor((T - stage) / w));
+                if (acc > 0.0) {
+                    // the open range reaches into this keyframe if it can take
+                    // all of it or save it a range of its own
+                    const double room = std::floor((T - acc - stage) / w);
+                    const int64_t own = (int64_t)std::ceil(rem / per);
+                    if (room >= rem) {
+                        acc += stage + w * rem;
+                        t += rem;
+                        continue;
+                    }
+                    if (room >= 1.0 && (int64_t)std::ceil((rem - room) / per) < own) {
+                        t += (int64_t)room;
+                        rem -= (int64_t)room;
+                    }
+                    if (out) out->push_back(t);
+                    acc = 0.0;
+                }
+                const int64_t own = (int64_t)std::ceil(rem / per);   // ranges, of like size
+                for (int64_t i = 0; i < own; ++i) {
+                    const int64_t part = rem * (i + 1) / own - rem * i / own;
+                    t += part;
+                    acc = stage + w * part;
+                    ++count;
+                    if (out && i + 1 < own) out->push_back(t);
+                }
+            }
+            return count;
+        };
+        double lo = cost / slots, hi = lo + longest;
+        while (split(hi, nullptr) > slots) hi *= 1.25;
+        for (int i = 0; i < 12 && hi - lo > 0.01 * hi; ++i) {
+            const double mid = 0.5 * (lo + hi);
+            if (split(mid, nullptr) <= slots) hi = mid;
+            else lo = mid;
+        }
+        split(hi, &bound);
     }
-    int64_t n = 0;
-    for (int k = 0; k < n_kf; ++k) {
-        const int64_t np = pairs[k];
-        if (np <= 0) continue;
-        int64_t ts = (np + nt[k] - 1) / nt[k];
-        const int64_t unit = ts > 256 ? 256 : kWave;
-        ts = std::min(tile_cap, (ts + unit - 1) / unit * unit);
-        tile[k] = (int32_t)ts;
-        n += (np + ts - 1) / ts;
-    }
-    return n;
+    bound.push_back(total);
 }
+
+// Ranges a search launch may have, whatever its tuning.
+int max_ranges(const fl_ctx* c) { return 2 * std::max(1, c->n_cu); }
 
 // Choose the staging mode and the octave groups per cell: the most groups
 // (up to one per octave, at most max_nb) whose LDS footprint fits in the
@@ -411,7 +464,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     const int n_vk = n_kf * n_pass;   // descriptors
     if ((int64_t)n_pass * B->n_kp_total > INT32_MAX) return fail(FL_ERANGE, "too many keypoints for %d passes", n_pass);
     const int ppl = c->tune.pairs_per_lane;
-    const int64_t tile_cap = (int64_t)kSearchBlock * ppl;
+    const int64_t tile_pairs = (int64_t)kWave * ppl;
     const bool refine = R && R->n_iters > 0;
     pr.ppl = ppl;
     pr.refine_iters = refine ? R->n_iters : 0;
@@ -429,24 +482,28 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     pr.lds = search_lds_bytes(pr.mode, kp_cap, cells, lds_hash_cap, nb);
     if (graph && pr.mode != kModeGlobal) pr.lds = std::min(c->lds_max, align_up(pr.lds, 16384));
 
-    // workgroups of the search launch (every slot in graph mode, at most one
-    // per tile otherwise)
+    // the workgroups' contiguous, cost-balanced tile ranges (in graph mode the
+    // grid is every slot; the further workgroups get empty ranges)
     const int slots = std::max(1, c->n_cu * std::max(1, c->tune.wg_per_cu));
-    std::vector<int32_t> kf_tile;
-    int64_t n_tiles_all = 0;
+    std::vector<int64_t> bound;
     {
-        std::vector<int64_t> vp(n_vk);
-        std::vector<int32_t> vk(n_vk);
-        for (int v = 0; v < n_vk; ++v) {
-            const int k = v / n_pass;
-            vp[v] = B->pair_offset[k + 1] - B->pair_offset[k];
-            vk[v] = B->kp_offset[k + 1] - B->kp_offset[k];
+        // (the passes of a keyframe follow each other and share its staging)
+        std::vector<int64_t> tiles(n_kf);
+        std::vector<float> weight(n_kf);
+        for (int k = 0; k < n_kf; ++k) {
+            tiles[k] = n_pass * ((B->pair_offset[k + 1] - B->pair_offset[k] + tile_pairs - 1) / tile_pairs);
+            // a pair costs more where keypoints are dense (more candidates scanned)
+            weight[k] = ppl * (1.0f + 2.0f * (B->kp_offset[k + 1] - B->kp_offset[k]) / std::max(1, cells));
         }
-        n_tiles_all = plan_tiles(vp, vk, cells, tile_cap, slots, kf_tile);
+        plan_ranges(tiles, weight, kStageCost, slots, bound);
     }
-    int grid = slots;
-    if (!graph) grid = (int)std::max<int64_t>(1, std::min<int64_t>(grid, n_tiles_all));
+    const int ge = (int)bound.size() - 1;
+    const int grid = graph ? slots : ge;
     pr.grid = grid;
+    // (a graph serves later batches too)
+    pr.n_ctr = graph ? grid : 0;
+    for (int i = 0; i < ge; ++i)
+        if (bound[i + 1] - bound[i] >= kSharedTiles) pr.n_ctr = grid;
 
     // Table blob: header, the workgroups' tile ranges and the keyframe table
     // first, at offsets the kernel derives from its grid size alone.
@@ -465,8 +522,6 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
 
     // keyframes, events, list regions, tiles
     int64_t hash_total = 0;
-    std::vector<double> tile_cost;    // cost of each keyframe's tiles (per tile)
-    tile_cost.resize(n_vk);
     for (int e = 0; e < n_ev; ++e) {
         EventDesc& ed = evd[e];
         const int kb = B->event_kf_offset[e], ke = B->event_kf_offset[e + 1];
@@ -503,13 +558,10 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
                 kd.hash_mask = hsize - 1;
                 kd.pair_off = B->pair_offset[k];
                 kd.n_pairs = B->pair_offset[k + 1] - B->pair_offset[k];
-                kd.tile_pairs = kf_tile[v];
-                kd.n_tiles = (int32_t)((kd.n_pairs + kd.tile_pairs - 1) / kd.tile_pairs);
+                kd.n_tiles = (int32_t)((kd.n_pairs + tile_pairs - 1) / tile_pairs);
                 kd.pass = p;
                 kd.stage_key = k;
                 kd.claim_off = p * B->n_kp_total + kd.kp_off;
-                // a pair costs more where keypoints are dense (more candidates scanned)
-                tile_cost[v] = (double)kd.tile_pairs * (1.0 + 2.0 * kd.n_kp / std::max(1, cells));
             }
         }
     }
@@ -527,11 +579,10 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
         order[k] = k;
         prefix[k] = (int32_t)n_tiles;
         n_tiles += kfd[k].n_tiles;
-        if (n_tiles > INT32_MAX / 2) return fail(FL_ERANGE, "too many tiles");
+        if (n_tiles >= kNoTile) return fail(FL_ERANGE, "too many tiles");
     }
     prefix[n_vk] = (int32_t)n_tiles;
-    if (n_tiles != n_tiles_all) return fail(FL_EINVAL, "internal: tile count mismatch");
-    // the workgroups' contiguous, cost-balanced tile ranges
+    if (n_tiles != bound[ge]) return fail(FL_EINVAL, "internal: tile count mismatch");
     WgRange* wr = (WgRange*)(blob.data() + o_range);
     {
         // first pair of tile t in the list index space (t = n_tiles: its end)
@@ -541,37 +592,8 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
             if (t >= n_tiles) return n_virtual;
             const int s = (int)(std::upper_bound(prefix, prefix + n_vk + 1, (int32_t)t) - prefix) - 1;
             const KfDesc& kd = kfd[order[s]];
-            return vbase[s] + std::min<int64_t>((t - prefix[s]) * (int64_t)kd.tile_pairs, kd.n_pairs);
+            return vbase[s] + std::min<int64_t>((t - prefix[s]) * tile_pairs, kd.n_pairs);
         };
-        // cumulative cost at each tile boundary, by keyframe
-        std::vector<double> kcum(n_vk + 1, 0.0);
-        for (int k = 0; k < n_vk; ++k) kcum[k + 1] = kcum[k] + tile_cost[k] * kfd[k].n_tiles;
-        auto tile_at_cost = [&](double target) -> int64_t {   // first tile whose end cost >= target
-            if (target <= 0.0) return 0;
-            int k = (int)(std::upper_bound(kcum.begin(), kcum.end(), target) - kcum.begin()) - 1;
-            k = std::min(std::max(k, 0), n_vk - 1);
-            const double per = tile_cost[k] > 0 ? tile_cost[k] : 1.0;
-            int64_t j = (int64_t)std::ceil((target - kcum[k]) / per);
-            j = std::min<int64_t>(std::max<int64_t>(j, 0), kfd[k].n_tiles);
-            return prefix[k] + j;
-        };
-        const double total = kcum[n_vk];
-        // The tiles are laid out over ge = min(grid, tiles) workgroups, as an
-        // eager launch has them; a graph's further workgroups (its grid is
-        // fixed) get empty ranges and exit at once.
-        const int ge = (int)std::max<int64_t>(1, std::min<int64_t>(grid, n_tiles));
-        std::vector<int64_t> bound(ge + 1);
-        bound[0] = 0;
-        bound[ge] = n_tiles;
-        if (n_tiles <= 2 * (int64_t)ge) {
-            // at most two tiles per workgroup: equal counts (a single wave of
-            // tiles is latency bound, so a workgroup must not take more)
-            for (int i = 1; i < ge; ++i) bound[i] = n_tiles * i / ge;
-        } else {
-            for (int i = 1; i < ge; ++i) bound[i] = tile_at_cost(total * i / ge);
-        }
-        for (int i = 1; i <= ge; ++i) bound[i] = std::max(bound[i], bound[i - 1]);
-        for (int i = ge - 1; i >= 0; --i) bound[i] = std::min(bound[i], bound[i + 1]);
         // chunk i of the sequence goes to workgroup w(i); with xcd_aware the
         // chunks of one XCD's share are consecutive in the sequence
         std::vector<int> wg_of(ge);
@@ -599,8 +621,13 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
             g.event = t0 < n_tiles ? kfd[order[slot]].event : -1;
             g.slot_t0 = prefix[slot];
             g.slot_t1 = prefix[slot + 1];
+            g.one_event = 0;
+            if (t0 < bound[i + 1]) {
+                const int last = (int)(std::upper_bound(prefix, prefix + n_vk + 1, (int32_t)bound[i + 1] - 1) - prefix) - 1;
+                g.one_event = kfd[order[last]].event == g.event;
+            }
             const KfDesc& kd = kfd[order[slot]];
-            g.pass = kd.pass;
+            g.pass = (int16_t)kd.pass;
             g.stage_key = kd.stage_key;
             g.kp_off = kd.kp_off;
             g.n_kp = kd.n_kp;
@@ -670,7 +697,8 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     rc = c->claims.ensure(sizeof(unsigned long long) * (size_t)std::max(n_pass * B->n_kp_total, 1), 0xFF);
     if (rc) return rc;
     const void* old_ctrs = c->ctrs.p;
-    rc = c->ctrs.ensure(64, 0x00);
+    // the statistics and the epoch, then the ranges' counters (of any tuning)
+    rc = c->ctrs.ensure(sizeof(RangeCtr) * (1 + (size_t)max_ranges(c)), 0x00);
     if (rc) return rc;
     if (c->ctrs.p != old_ctrs && old_ctrs != nullptr) {
         // a fresh counter block restarts the epoch: every stored claim must be reset too
@@ -690,7 +718,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     h.n_kp_total = B->n_kp_total;
     h.n_pairs = B->n_pairs;
     h.n_tiles = (int32_t)n_tiles;
-    h.tile_cap = (int32_t)tile_cap;
+    h.tile_pairs = (int32_t)tile_pairs;
     h.cells = cells;
     h.grid_cols = P->grid_cols;
     h.grid_rows = P->grid_rows;
@@ -723,6 +751,7 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     h.kf_order = (const int32_t*)(base + L_blob + o_order);
     h.tile_prefix = (const int32_t*)(base + L_blob + o_prefix);
     h.wg_range = (const WgRange*)(base + L_blob + o_range);
+    h.range_ctr = (RangeCtr*)(cb + sizeof(RangeCtr));
     h.kp_xy = B->kp_xy;
     h.kp_oct = B->kp_octave;
     h.kp_desc = B->kp_desc;
@@ -808,11 +837,11 @@ int next_epoch(fl_ctx* c, hipStream_t stream) {
     return FL_OK;
 }
 
-void launch_fetch(fl_ctx* c, const void* src, size_t bytes, hipStream_t stream) {
+void launch_fetch(fl_ctx* c, const void* src, size_t bytes, int n_ctr, hipStream_t stream) {
     const int n16 = (int)((bytes + 15) / 16);
     const int grid = std::max(1, std::min((n16 + 255) / 256, 64));
     hipLaunchKernelGGL(fetch_blob_kernel, dim3(grid), dim3(256), 0, stream, (const uint4*)src, (uint4*)c->ws.p, n16,
-                       (uint32_t*)((char*)c->ctrs.p + 32));
+                       (uint32_t*)((char*)c->ctrs.p + 32), (RangeCtr*)c->ctrs.p + 1, n_ctr);
 }
 
 // Eager calls: stage the header and tables in a pinned ring buffer and fetch
@@ -830,7 +859,7 @@ int upload_batch(fl_ctx* c, Prepared& pr, hipStream_t stream) {
         memcpy(pin->p, pr.blob.data(), pr.blob.size());
         pin->used = pr.blob.size();
     }
-    launch_fetch(c, pin->p, pr.blob.size(), stream);
+    launch_fetch(c, pin->p, pr.blob.size(), pr.n_ctr, stream);
     FL_HIP(hipGetLastError());
     c->pin_last = pin;
     return note_fetch(c, *pin, stream);
@@ -1363,7 +1392,7 @@ int fl_search_fuse_graph_launch(fl_ctx* c, const fl_batch* B, const fl_params* P
             FL_HIP(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
             const int saved_prof = c->prof;
             c->prof = 0;
-            launch_fetch(c, c->gpin[gi].p, c->gpin[gi].size, c->cap_stream);
+            launch_fetch(c, c->gpin[gi].p, c->gpin[gi].size, pr.n_ctr, c->cap_stream);
             int lrc = launch_search(c, pr, dh, c->cap_stream, false, false);
             c->prof = saved_prof;
             if (lrc == FL_OK && refine_on)

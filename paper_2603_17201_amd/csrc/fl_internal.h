@@ -34,7 +34,7 @@ struct alignas(16) KfDesc {
     int32_t hash_mask;
     int32_t n_tiles;
     int32_t pad0, pad2;
-    int32_t tile_pairs;  // pairs per tile of this keyframe (a whole number of waves)
+    int32_t pad3;
     int64_t pair_off;
     int64_t n_pairs;
     // A launch may search its batch several times (passes); each (keyframe,
@@ -96,11 +96,31 @@ struct alignas(16) WgRange {
     // of the first keyframe, so that neither its keypoints' loads nor the
     // pass's thresholds wait for its descriptor
     int32_t slot_t0, slot_t1;   // tile_prefix[slot], tile_prefix[slot + 1]
-    int32_t pass, stage_key;
+    int16_t pass;
+    int16_t one_event;          // every tile of the range belongs to `event`
+    int32_t stage_key;
     int32_t kp_off, n_kp;
     float invw, invh;
 };
 static_assert(sizeof(WgRange) == 64, "one cache line");
+
+// The waves of a range's workgroup take its first tiles in turn (tile t0 + w,
+// then every kWavesPerWG-th); those from range_shared() on are claimed one
+// by one, so that workgroups with nothing left can help.  A claim costs some
+// 700 cycles of a tile's 8,000: short ranges, which no one could help in time,
+// have none to claim, longer ones their second half.
+constexpr int kSharedTiles = 96;   // shortest range with tiles to claim
+constexpr int kNoTile = 1 << 30;   // past every tile, with room for a stride on top
+__host__ __device__ constexpr int range_shared(int t0, int t1, int waves) {
+    return t1 - t0 < kSharedTiles ? t1 : t0 + (t1 - t0) / (2 * waves) * waves;
+}
+
+// What has been claimed of a range, and the workgroups that came to help.  A
+// 128-byte line each: device-scope atomics on one line serialise (about 12 ns
+// apiece).  Cleared by the table fetch.
+struct alignas(128) RangeCtr {
+    uint32_t claimed, helpers;   // read together as one 64-bit word
+};
 
 // The accepted pairs one workgroup staged for one event: entries [start,
 // start + count) of the staging list.  Workgroup chunk c and event e meet at
@@ -131,7 +151,7 @@ enum : int { kModeGlobal = 0, kModeLdsRec = 1, kModeLdsDesc = 2 };
 struct alignas(16) BatchHdr {
     int32_t n_events, n_kf, n_mp, n_kp_total;
     int64_t n_pairs;
-    int32_t n_tiles, tile_cap;   // tiles of the batch; the largest tile (workgroup size x pairs per lane)
+    int32_t n_tiles, tile_pairs; // tiles of the batch; pairs per tile (one wave's chunk)
     int32_t cells, grid_cols, grid_rows, n_octaves;
     int32_t n_pass;             // search passes of the launch (1 .. FL_MAX_PASSES)
     int32_t gate;               // 1: point distance invariance given (octave gate on)
@@ -159,6 +179,7 @@ struct alignas(16) BatchHdr {
     const int32_t* kf_order;    // keyframes in tile order
     const int32_t* tile_prefix; // [n_kf+1] first tile of each keyframe in tile order
     const WgRange* wg_range;    // [n_wg] each workgroup's tiles and list regions
+    RangeCtr* range_ctr;        // [n_wg] what has been taken of them
     // inputs (caller-owned)
     const float* kp_xy;
     const int8_t* kp_oct;
@@ -365,41 +386,55 @@ __device__ __forceinline__ T* uniform_p(T* p) {
     return reinterpret_cast<T*>(uniform_l((int64_t)reinterpret_cast<uintptr_t>(p)));
 }
 
-// The search fields of a keyframe descriptor, in scalar registers.
-__device__ __forceinline__ KfDesc uniform_kf(const KfDesc& s) {
+// Tables that no one writes while a kernel runs, read through the constant
+// address space: with a uniform address these are scalar loads, from the
+// scalar cache.  `fresh` hides the pointer's origin, so the loads stay where
+// they are written.  A loop with more uniform values than there are scalar
+// registers reads them where it needs them: hoisted out of it they would be
+// kept in lanes of vector registers, and every use would be a vector
+// instruction.
+template <typename T>
+using cmem = const __attribute__((address_space(4))) T;
+template <typename T>
+__device__ __forceinline__ cmem<T>* fresh(const T* p) {
+    uint64_t a = reinterpret_cast<uint64_t>(p);
+    asm volatile("" : "+s"(a));
+    return (cmem<T>*)a;
+}
+
+// The search fields of a keyframe descriptor.
+__device__ __forceinline__ KfDesc search_kf(cmem<KfDesc>* s) {
     KfDesc k;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) k.A[i] = uniform_f(s.A[i]);
+    for (int i = 0; i < 9; ++i) k.A[i] = s->A[i];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) k.t[i] = uniform_f(s.t[i]);
-    k.inv_s = uniform_f(s.inv_s);
-    k.fx = uniform_f(s.fx);
-    k.fy = uniform_f(s.fy);
-    k.cx = uniform_f(s.cx);
-    k.cy = uniform_f(s.cy);
-    k.W = uniform_f(s.W);
-    k.H = uniform_f(s.H);
-    k.invw = uniform_f(s.invw);
-    k.invh = uniform_f(s.invh);
+    for (int i = 0; i < 3; ++i) k.t[i] = s->t[i];
+    k.inv_s = s->inv_s;
+    k.fx = s->fx;
+    k.fy = s->fy;
+    k.cx = s->cx;
+    k.cy = s->cy;
+    k.W = s->W;
+    k.H = s->H;
+    k.invw = s->invw;
+    k.invh = s->invh;
 #pragma unroll
     for (int i = 0; i < 12; ++i) k.T[i] = 0.0f;   // not used by the search
-    k.kp_off = uniform_i(s.kp_off);
-    k.n_kp = uniform_i(s.n_kp);
-    k.grid_off = uniform_i(s.grid_off);
-    k.event = uniform_i(s.event);
-    k.mp_off = uniform_i(s.mp_off);
-    k.n_mp = uniform_i(s.n_mp);
-    k.hash_off = uniform_i(s.hash_off);
-    k.hash_mask = uniform_i(s.hash_mask);
-    k.n_tiles = uniform_i(s.n_tiles);
-    k.pad0 = k.pad2 = 0;
-    k.tile_pairs = uniform_i(s.tile_pairs);
-    k.pair_off = uniform_l(s.pair_off);
-    k.n_pairs = uniform_l(s.n_pairs);
-    k.pass = uniform_i(s.pass);
-    k.stage_key = uniform_i(s.stage_key);
-    k.claim_off = uniform_i(s.claim_off);
-    k.pad1 = 0;
+    k.kp_off = s->kp_off;
+    k.n_kp = s->n_kp;
+    k.grid_off = s->grid_off;
+    k.event = s->event;
+    k.mp_off = s->mp_off;
+    k.n_mp = s->n_mp;
+    k.hash_off = s->hash_off;
+    k.hash_mask = s->hash_mask;
+    k.n_tiles = s->n_tiles;
+    k.pad0 = k.pad1 = k.pad2 = k.pad3 = 0;
+    k.pair_off = s->pair_off;
+    k.n_pairs = s->n_pairs;
+    k.pass = s->pass;
+    k.stage_key = s->stage_key;
+    k.claim_off = s->claim_off;
     return k;
 }
 

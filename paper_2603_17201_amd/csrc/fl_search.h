@@ -430,11 +430,18 @@ __global__ __launch_bounds__(kPrepBlock) void grid_single_kernel(KfDesc kd, int 
 // copy kernel, in stream order with the kernels that read them).
 
 // It also advances the claim epoch of the launch that follows (counting
-// down, so claims of earlier launches always compare larger).
+// down, so claims of earlier launches always compare larger) and clears the
+// counters of its ranges.
 __global__ __launch_bounds__(256) void fetch_blob_kernel(const uint4* __restrict__ src, uint4* __restrict__ dst,
-                                                       int n16, uint32_t* __restrict__ epoch) {
+                                                       int n16, uint32_t* __restrict__ epoch,
+                                                       RangeCtr* __restrict__ ctr, int n_ctr) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += gridDim.x * blockDim.x) dst[i] = src[i];
-    if (epoch && blockIdx.x == 0 && threadIdx.x == 0) *epoch = *epoch - 1u;
+    if (blockIdx.x != 0) return;
+    for (int i = threadIdx.x; i < n_ctr; i += blockDim.x) {
+        ctr[i].claimed = 0;
+        ctr[i].helpers = 0;
+    }
+    if (threadIdx.x == 0) *epoch = *epoch - 1u;
 }
 
 // ---------------------------------------------------------------------------
@@ -456,20 +463,30 @@ __device__ __forceinline__ void wave_append(bool want, uint32_t* counter, T* lis
 }
 
 // ---------------------------------------------------------------------------
-// Fused batched search.  Each workgroup owns a contiguous, cost-balanced run
-// of tiles (workgroups are dispatched to the 8 XCDs round-robin, and the runs
-// of one XCD are neighbours in the tile order, so the keyframes of an XCD
-// stay in its L2).  The workgroup's consecutive tiles of one keyframe
-// descriptor form a segment.  When a segment's keyframe is not the one in
-// LDS, the workgroup builds that keyframe's grid, records (and descriptors)
-// and owner hash set in LDS; then its waves take the segment's pairs in
-// chunks of 64 x PPL (pair j of a chunk on lane j mod 64), each wave on its
-// own, with no barrier between chunks.  Provisional ADDs and accepted pairs
-// go to the workgroup's own list regions through LDS counters; a table says
-// which of its accepted pairs are whose event's, and the refinement reads them
-// where they are (joining the event's list, with a device-scope reservation
-// and a copy, took 6,000 to 8,000 cycles at the end of every workgroup).  The
-// ADD conflicts are resolved by the next kernel on the stream.
+// Fused batched search.  A tile is one wave's share of a keyframe's pairs (64
+// x PPL, pair j on lane j mod 64).  Each workgroup owns a contiguous,
+// cost-balanced range of tiles (workgroups are dispatched to the 8 XCDs
+// round-robin, and the ranges of one XCD are neighbours in the tile order, so
+// the keyframes of an XCD stay in its L2).  The consecutive tiles of one
+// keyframe descriptor form a segment: if its keyframe is not the one in LDS,
+// the workgroup builds that keyframe's grid, records (and descriptors) and
+// owner hash set in LDS; then its waves search the segment's tiles, each wave
+// on its own, with no barrier between tiles.  What a tile costs is known only
+// once its points are projected, so a long range's second half is claimed tile
+// by tile, and a workgroup whose range is done helps the longest of its XCD
+// (73 keyframes x 97,969 points: the workgroups ended between 92 and 161 us,
+// and the launch takes as long as its last; calls of 224 us became 199).
+// Provisional ADDs and accepted pairs go to the workgroup's own list regions
+// through LDS counters; a table says which of its accepted pairs are whose
+// event's, and the refinement reads them where they are (joining the event's
+// list, with a device-scope reservation and a copy, took 6,000 to 8,000 cycles
+// at the end of every workgroup).  The ADD conflicts are resolved by the next
+// kernel on the stream.
+//
+// Bound: vector instructions, about 400 for a tile of 64 pairs with two scan
+// steps, at four waves a SIMD.  The tables' uniform values are therefore read
+// by scalar loads where they are used (kept across a tile they took 75
+// vector instructions a tile to bring back from spilled lanes).
 
 // Zero in a vector register the compiler cannot see through: an atomic at
 // such an offset is left as written (at an address known to be uniform it is
@@ -531,23 +548,28 @@ struct PointEnv {
 // searched.  First the point's index in its event (-1: no pair), then the
 // point: two dependent loads, in flight during different chunks.  Addresses
 // are a scalar base and the lane.
-__device__ __forceinline__ int32_t load_index(const PointEnv& env, const KfDesc& kd, int64_t o, int n) {
+__device__ __forceinline__ PointEnv point_env(cmem<BatchHdr>* h, int gate) {
+    return {h->pair_mp, h->mp_id, h->mp_xyz, h->mp_dmax, h->dense != 0, gate};
+}
+
+__device__ __forceinline__ int32_t load_index(const PointEnv& env, int64_t pair_off, int64_t o, int n) {
     const uint32_t lane = (uint32_t)wave_lane();
     int32_t lp = -1;
-    if ((int)lane < n) lp = env.dense ? (int32_t)(o - kd.pair_off) + (int32_t)lane : ldg(env.pair_mp + o + lane);
+    if ((int)lane < n) lp = env.dense ? (int32_t)(o - pair_off) + (int32_t)lane : ldg(env.pair_mp + o + lane);
     return lp;
 }
 
 typedef float v3f __attribute__((ext_vector_type(3), aligned(4)));
 
-__device__ __forceinline__ void load_point(const PointEnv& env, const KfDesc& kd, int32_t lp, int n, PairIn& p) {
+__device__ __forceinline__ void load_point(const PointEnv& env, int32_t mp_off, int32_t n_mp, int32_t lp, int n,
+                                           PairIn& p) {
     p.dec = FL_INVALID;
     p.gp = 0;
     p.id = -1;
     p.x = p.y = p.z = p.dm = 0.0f;
-    if (wave_lane() < n && lp >= 0 && lp < kd.n_mp) {
+    if (wave_lane() < n && lp >= 0 && lp < n_mp) {
         p.dec = kDecUndecided;
-        p.gp = kd.mp_off + lp;
+        p.gp = mp_off + lp;
         p.id = env.id ? ldg(env.id + p.gp) : p.gp;
         const v3f x = *(const gmem<v3f>*)(env.xyz + 3 * (int64_t)p.gp);
         p.x = x.x;
@@ -608,7 +630,11 @@ __device__ __forceinline__ float window_radius(const OctaveTable& T, int pred) {
 // second slot; so the second slot ends at the smallest distance of every
 // candidate but the best, whatever the order.  The back (per lane): the
 // fuse / add decision (provisional for ADD).  st: visible pairs, cells
-// scanned, keypoints in them (every octave), candidates.
+// scanned, keypoints in them (every octave), candidates.  The wave takes
+// kRowSeg rows of every window at a time: at 3 pixels few windows have more;
+// at 10 pixels the upper octaves' have up to eight, and walking those by
+// themselves, lane by lane, made a 20-keyframe event with outlier rounds 94 us
+// instead of 89.
 constexpr int kRowSeg = 4;
 static_assert(kRowSeg == 4, "four row runs");
 
@@ -618,6 +644,7 @@ struct PairScan {
     int pred, grp;
     int b0, d1, d2, d3, c1, c2, c3, total;   // slot = m + b0 + (d_j where m >= c_j)
     int nrows;
+    int first;   // entry of the bucket starts of the window's first row, column 0
 };
 
 // Per wave: the candidate queue, each lane's best key and second distance,
@@ -629,6 +656,30 @@ struct WaveCand {
     int32_t mark[kWave];
 };
 constexpr size_t kSearchStaticLds = sizeof(WaveCand) * kWavesPerWG + 1024;   // beside the dynamic LDS
+
+// The runs of the window's rows j0 .. j0 + kRowSeg - 1, and how many records
+// they hold (named values, not arrays: an array indexed by a lane-dependent
+// value would be placed in scratch memory).
+template <int MODE>
+__device__ __forceinline__ void row_runs(const KfView& v, int C, int j0, PairScan& q) {
+    const int row = (MODE == kModeGlobal ? 1 : v.nb) * C;
+    auto cs_at = [&](int j) -> int { return MODE == kModeGlobal ? v.cs[j] : (int)v.cs16[j]; };
+    auto run = [&](int j, int c_in, int& b_out, int& c_out) {
+        const bool in = j0 + j < q.nrows;
+        const int idx = q.first + (in ? (j0 + j) * row : 0);
+        const int s0 = cs_at(idx + q.w.c0), e0 = cs_at(idx + q.w.c1 + 1);
+        b_out = s0 - c_in;
+        c_out = c_in + (in ? e0 - s0 : 0);
+    };
+    int b1, b2, b3;
+    run(0, 0, q.b0, q.c1);
+    run(1, q.c1, b1, q.c2);
+    run(2, q.c2, b2, q.c3);
+    run(3, q.c3, b3, q.total);
+    q.d1 = b1 - q.b0;
+    q.d2 = b2 - b1;
+    q.d3 = b3 - b2;
+}
 
 template <int MODE, bool STATS>
 __device__ __forceinline__ bool search_front(const KfDesc& kd, const KfView& v, const OctaveTable& T, int gate,
@@ -662,24 +713,8 @@ __device__ __forceinline__ bool search_front(const KfDesc& kd, const KfView& v, 
     auto cs_at = [&](int j) -> int { return MODE == kModeGlobal ? v.cs[j] : (int)v.cs16[j]; };
     q.grp = min(q.pred, nb - 1);
     q.nrows = w.r1 - w.r0 + 1;
-    // the runs of the first kRowSeg rows (named values, not arrays: an array
-    // indexed by a lane-dependent value would be placed in scratch memory)
-    const int idx0 = (int)__umul24(__umul24(w.r0, nb) + q.grp, C), row = nb * C;
-    auto run = [&](int j, int c_in, int& b_out, int& c_out) {
-        const bool in = j < q.nrows;
-        const int idx = idx0 + (in ? j * row : 0);
-        const int s0 = cs_at(idx + w.c0), e0 = cs_at(idx + w.c1 + 1);
-        b_out = s0 - c_in;
-        c_out = c_in + (in ? e0 - s0 : 0);
-    };
-    int b1, b2, b3;
-    run(0, 0, q.b0, q.c1);
-    run(1, q.c1, b1, q.c2);
-    run(2, q.c2, b2, q.c3);
-    run(3, q.c3, b3, q.total);
-    q.d1 = b1 - q.b0;
-    q.d2 = b2 - b1;
-    q.d3 = b3 - b2;
+    q.first = (int)__umul24(__umul24(w.r0, nb) + q.grp, C);
+    row_runs<MODE>(v, C, 0, q);
     if (probe) {
         for (int n = 0; n <= v.hash_mask; ++n) {
             if (hv == p.id) {
@@ -771,92 +806,79 @@ __device__ __forceinline__ void drain_queue(WaveCand& wc, int qn, const KfView& 
 // the owner's window and run layout come from the owner lane.
 template <int MODE, bool STATS>
 __device__ __forceinline__ void search_scan(const KfView& v, int gate, int C, const uint8_t* mp_desc,
-                                            const PairIn& p, const PairScan& q, WaveCand& wc,
+                                            const PairIn& p, PairScan& q, WaveCand& wc,
                                             unsigned long long* st) {
     const int lane = wave_lane();
     wc.best[lane] = 0xFFFFFFFFu;
     wc.second[lane] = FL_NO_DIST;
     int qn = 0;
-    const int L = q.total;
-    const int incl = wave_incl_scan(L);
-    const int P = incl - L;
-    const int N = __builtin_amdgcn_readlane(incl, kWave - 1);
-    // item k of this lane (P <= k < P + L) is record slot
-    // k + B + (d1 if k >= A1) + (d2 if k >= A2) + (d3 if k >= A3)
-    const int B = q.b0 - P, A1 = P + q.c1, A2 = P + q.c2, A3 = P + q.c3;
-    const float lx = q.w.lx, hx = q.w.hx, ly = q.w.ly, hy = q.w.hy;
-    int cur = 0;   // owner of the step's first item when no range starts there
-    for (int base = 0; base < N; base += kWave) {
-        // (one wave's LDS accesses complete in order: the read below sees
-        // the marks, and the reset follows the read)
-        if (L > 0 && P >= base && P < base + kWave) wc.mark[P - base] = lane;
-        int mk = wc.mark[lane];
-        wc.mark[lane] = -1;
-        if (lane == 0 && mk < 0) mk = cur;
-        const unsigned long long starts = __ballot(mk >= 0);   // bit 0 always set
-        const unsigned long long upto = lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull);
-        const int pos = 63 - __builtin_clzll(starts & upto);
-        const int o = __shfl(mk, pos);   // owner lane of item base + lane
-        cur = __builtin_amdgcn_readlane(o, kWave - 1);
-        const int k = base + lane;
-        const bool act = k < N;
-        const int oB = __shfl(B, o), oA1 = __shfl(A1, o), oA2 = __shfl(A2, o), oA3 = __shfl(A3, o);
-        const int od1 = __shfl(q.d1, o), od2 = __shfl(q.d2, o), od3 = __shfl(q.d3, o);
-        Window w;
-        w.lx = __shfl(lx, o);
-        w.hx = __shfl(hx, o);
-        w.ly = __shfl(ly, o);
-        w.hy = __shfl(hy, o);
-        const int opred = __shfl(q.pred, o);
-        const int i = k + oB + (od1 & -(int)(k >= oA1)) + (od2 & -(int)(k >= oA2)) + (od3 & -(int)(k >= oA3));
-        KpRec rc{};
-        if (act) rc = v.rec[min((unsigned)i, (unsigned)(v.n_rec - 1))];   // (in range by construction)
-        const bool cand = act && in_window(w, rc.x, rc.y, rc.oct, opred, gate);
-        const unsigned long long cm = __ballot(cand);
-        if (cm) {
-            const int n = __popcll(cm);
-            if (qn + n > kWave) {
-                drain_queue<MODE>(wc, qn, v, mp_desc, p.gp);
-                qn = 0;
+    for (int j0 = 0;;) {
+        const int L = q.total;
+        const int incl = wave_incl_scan(L);
+        const int P = incl - L;
+        const int N = __builtin_amdgcn_readlane(incl, kWave - 1);
+        // item k of this lane (P <= k < P + L) is record slot
+        // k + B + (d1 if k >= A1) + (d2 if k >= A2) + (d3 if k >= A3)
+        const int B = q.b0 - P, A1 = P + q.c1, A2 = P + q.c2, A3 = P + q.c3;
+        const float lx = q.w.lx, hx = q.w.hx, ly = q.w.ly, hy = q.w.hy;
+        int cur = 0;   // owner of the step's first item when no range starts there
+        for (int base = 0; base < N; base += kWave) {
+            // (one wave's LDS accesses complete in order: the read below sees
+            // the marks, and the reset follows the read)
+            if (L > 0 && P >= base && P < base + kWave) wc.mark[P - base] = lane;
+            int mk = wc.mark[lane];
+            wc.mark[lane] = -1;
+            if (lane == 0 && mk < 0) mk = cur;
+            const unsigned long long starts = __ballot(mk >= 0);   // bit 0 always set
+            const unsigned long long upto = lane == kWave - 1 ? ~0ull : ((2ull << lane) - 1ull);
+            const int pos = 63 - __builtin_clzll(starts & upto);
+            const int o = __shfl(mk, pos);   // owner lane of item base + lane
+            cur = __builtin_amdgcn_readlane(o, kWave - 1);
+            const int k = base + lane;
+            const bool act = k < N;
+            const int oB = __shfl(B, o), oA1 = __shfl(A1, o), oA2 = __shfl(A2, o), oA3 = __shfl(A3, o);
+            const int od1 = __shfl(q.d1, o), od2 = __shfl(q.d2, o), od3 = __shfl(q.d3, o);
+            Window w;
+            w.lx = __shfl(lx, o);
+            w.hx = __shfl(hx, o);
+            w.ly = __shfl(ly, o);
+            w.hy = __shfl(hy, o);
+            const int opred = __shfl(q.pred, o);
+            const int i = k + oB + (od1 & -(int)(k >= oA1)) + (od2 & -(int)(k >= oA2)) + (od3 & -(int)(k >= oA3));
+            KpRec rc{};
+            if (act) rc = v.rec[min((unsigned)i, (unsigned)(v.n_rec - 1))];   // (in range by construction)
+            const bool cand = act && in_window(w, rc.x, rc.y, rc.oct, opred, gate);
+            const unsigned long long cm = __ballot(cand);
+            if (cm) {
+                const int n = __popcll(cm);
+                if (qn + n > kWave) {
+                    drain_queue<MODE>(wc, qn, v, mp_desc, p.gp);
+                    qn = 0;
+                }
+                if (cand) {
+                    wc.q[qn + __popcll(cm & ((1ull << lane) - 1ull))] = ((uint32_t)o << 17) | (uint32_t)i;
+                    if (STATS) ++st[3];
+                }
+                qn += n;
             }
-            if (cand) {
-                wc.q[qn + __popcll(cm & ((1ull << lane) - 1ull))] = ((uint32_t)o << 17) | (uint32_t)i;
-                if (STATS) ++st[3];
-            }
-            qn += n;
         }
+        // the next rows, if any lane's window has them
+        j0 += kRowSeg;
+        if (__ballot(q.nrows > j0) == 0ull) break;
+        row_runs<MODE>(v, C, j0, q);
     }
     if (qn) drain_queue<MODE>(wc, qn, v, mp_desc, p.gp);
-    // rows beyond the first kRowSeg (wide windows): each lane its own, the
-    // distances computed on the spot
-    if (q.nrows > kRowSeg) {
-        const int nb = MODE == kModeGlobal ? 1 : v.nb;
-        uint4 a0, a1;
-        load_desc(mp_desc, p.gp, a0, a1);
-        for (int row = q.w.r0 + kRowSeg; row <= q.w.r1; ++row) {
-            const int j = (row * nb + q.grp) * C;
-            const int s0 = MODE == kModeGlobal ? v.cs[j + q.w.c0] : (int)v.cs16[j + q.w.c0];
-            const int e0 = MODE == kModeGlobal ? v.cs[j + q.w.c1 + 1] : (int)v.cs16[j + q.w.c1 + 1];
-            for (int i = s0; i < e0; ++i) {
-                const KpRec rc = v.rec[i];
-                if (!in_window(q.w, rc.x, rc.y, rc.oct, q.pred, gate)) continue;
-                if (STATS) ++st[3];
-                uint4 b0, b1;
-                record_desc<MODE>(v, i, rc.idx, b0, b1);
-                offer_lds(wc, lane, ((uint32_t)hamming(a0, a1, b0, b1) << 16) | (uint32_t)rc.idx);
-            }
-        }
-    }
 }
 
 // The decision of a searched pair from its best and second.
-// With kp_xy, also the accepted keypoint's position (the two loads together).
-__device__ __forceinline__ void search_back(const KfDesc& kd, int hamming_th, float nn_ratio,
-                                            const int32_t* kp_owner, const float* kp_xy, PairIn& p, PairRes& res) {
+// kp_owner and, if given, kp_xy are the keyframe's; with kp_xy, also the
+// accepted keypoint's position (the two loads together).
+__device__ __forceinline__ void search_back(int hamming_th, float nn_ratio, const int32_t* kp_owner,
+                                            const float* kp_xy, PairIn& p, PairRes& res) {
     if (!accept_match(res.best, hamming_th, nn_ratio)) {
         p.dec = FL_NO_MATCH;
     } else {
-        const int64_t kg = (int64_t)kd.kp_off + (res.best.key & 0xFFFFu);
+        const uint32_t kg = res.best.key & 0xFFFFu;
         const int32_t ow = ldg(kp_owner + kg);
         if (kp_xy) {
             res.ku = ldg(kp_xy + 2 * kg);
@@ -887,6 +909,44 @@ struct MatchSegs {
     }
 };
 
+// A range to help with, chosen by one wave for its workgroup, whose own is
+// done: of the ranges all of whose tiles belong to `event` (the workgroup's
+// accepted pairs then stay one run), the one with the most unclaimed tiles per
+// workgroup on it, if they are at least kHelpTiles: staging a keyframe anew
+// costs what two rounds of the sixteen waves do.  The workgroup's list regions
+// must have room for what its waves may hold.  Only the ranges of its own XCD
+// (every kMaxQueues-th workgroup) are looked at: their points are in its L2, and
+// each look goes to memory (with every workgroup reading all 256 counters in
+// the launch's last third, loads took 8,000 cycles).  out: the range (or -1).
+constexpr int kHelpTiles = 32;
+
+__device__ __forceinline__ void pick_range(const BatchHdr& h, RangeCtr* ctr, int event, uint32_t held, int32_t cap,
+                                           unsigned long long used, int* out) {
+    const int lane = wave_lane();
+    int best = -1, best_i = -1;
+    if (max((uint32_t)used, (uint32_t)(used >> 32)) + held <= (uint32_t)cap) {
+        for (int i = (int)(blockIdx.x % kMaxQueues) + lane * kMaxQueues; i < (int)gridDim.x; i += kWave * kMaxQueues) {
+            const WgRange& r = h.wg_range[i];
+            const unsigned long long taken = __hip_atomic_load((gmem<unsigned long long>*)&ctr[i], __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT);
+            const int score = (r.t1 - range_shared(r.t0, r.t1, kWavesPerWG) - (int)(uint32_t)taken) / (1 + (int)(taken >> 32));
+            if (r.event == event && r.one_event && score > best) {
+                best = score;
+                best_i = i;
+            }
+        }
+    }
+    int m = best;
+    for (int off = 32; off > 0; off >>= 1) m = max(m, __shfl_xor(m, off));
+    const unsigned long long who = __ballot(best == m);
+    const int v = __builtin_amdgcn_readlane(best_i, __ffsll((long long)who) - 1);
+    if (lane == 0) {
+        out[0] = m >= kHelpTiles ? v : -1;
+        if (m >= kHelpTiles)
+            __hip_atomic_fetch_add((gmem<uint32_t>*)&ctr[v].helpers, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 template <int PPL, int MODE, bool STATS>
 __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchHdr* __restrict__ hp) {
     extern __shared__ __align__(16) unsigned char s_mem[];
@@ -896,6 +956,7 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
     __shared__ unsigned long long s_list[1];   // running counts: ADD region (low half), accepted-pair region
     __shared__ WaveCand s_wc[kWavesPerWG];   // each wave's candidate queue, best and second
     __shared__ float s_sf[FL_MAX_OCTAVES];
+    __shared__ int s_first[4], s_help[4];
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     constexpr int nw = kWavesPerWG;
 
@@ -909,27 +970,11 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
     const WgRange rg = reinterpret_cast<const WgRange*>(blob + blob_range_offset())[blockIdx.x];
     const KfDesc* kf_tab = reinterpret_cast<const KfDesc*>(blob + blob_kf_offset((int)gridDim.x));
     const float sf_lane = h.sf[tid & (FL_MAX_OCTAVES - 1)];
-    OctaveTable T;
-    T.all = s_sf;
-    T.N = uniform_i(h.n_octaves);
-#pragma unroll
-    for (int n = 0; n < kOctReg; ++n) T.sf[n] = uniform_f(h.sf[n]);
-    // header fields read per pair, held in scalar registers (the output
-    // stores below could otherwise be taken to alias the header)
     const int gate = uniform_i(h.gate), C = uniform_i(h.grid_cols), R = uniform_i(h.grid_rows);
-    const PointEnv points{uniform_p(h.pair_mp), uniform_p(h.mp_id), uniform_p(h.mp_xyz), uniform_p(h.mp_dmax),
-                          uniform_i(h.dense) != 0, gate};
     const int nb = MODE == kModeGlobal ? 1 : uniform_i(h.oct_buckets);
-    const StageEnv stage{uniform_p(h.kp_xy), uniform_p(h.kp_oct), uniform_p(h.kp_owner), uniform_p(h.kp_desc),
-                         C, R, nb, uniform_i(h.lds_hash_mask)};
+    const int hmask = uniform_i(h.lds_hash_mask);
     const int kp_cap = uniform_i(h.lds_kp_cap);
     const bool want_matches = uniform_i(h.refine_iters) > 0;
-    const int32_t* const kp_owner = stage.own;
-    const float* const kp_xy = stage.xy;
-    const uint8_t* const mp_desc = uniform_p(h.mp_desc);
-    unsigned long long* const claim = uniform_p(h.claim);
-    AddRef* const add_list = uniform_p(h.add_list);
-    MatchRec* const match_stage = uniform_p(h.match_stage);
     const uint32_t epoch = ldg(h.epoch);   // (a vector register: waited for where it is used)
     unsigned long long st[4] = {0, 0, 0, 0};
 
@@ -948,9 +993,10 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
         s_cs = reinterpret_cast<uint4*>(p);
         p += search_cs_bytes(C * R, nb);
         s_hash = reinterpret_cast<int32_t*>(p);
-        p += 4 * (size_t)(stage.hmask + 1);
+        p += 4 * (size_t)(hmask + 1);
         s_tmp = reinterpret_cast<int32_t*>(p);
     }
+    if (tid < 4) s_first[tid] = INT32_MAX;
     if (tid == 0) s_list[0] = 0;
     s_wc[wid].mark[lane] = -1;
     // the octave scale table in LDS (the octave search and the window radius
@@ -959,65 +1005,118 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
     if (tid < FL_MAX_OCTAVES) s_sf[tid] = sf_lane;
     if (MODE == kModeGlobal) __syncthreads();
 
+    // The wave's tile ta and the one after it, tb, in the range [.., t1) being
+    // searched, whose tiles from ts on are claimed.
+    int ta = rg.t0 + wid, tb = ta + nw, t1 = rg.t1;
+    int ts = range_shared(rg.t0, rg.t1, nw);
+    int own = (int)blockIdx.x;
+    RangeCtr* const ctr = uniform_p(h.range_ctr);
+    constexpr int kChunk = kWave * PPL;
+    // entries that every tile the waves may hold (one being searched, ta, tb and
+    // one claimed each) could add to the lists
+    constexpr uint32_t kHeld = 4 * nw * kChunk;
+    auto claim_tile = [&]() -> int {   // lane 0's value
+        int v = kNoTile;
+        bool room = true;
+        if (own != (int)blockIdx.x)
+            room = max((uint32_t)s_list[0], (uint32_t)(s_list[0] >> 32)) + kHeld <= (uint32_t)rg.priv_cap;
+        if (room && lane == 0)
+            v = ts + (int)__hip_atomic_fetch_add((gmem<uint32_t>*)&ctr[own].claimed, 1u, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        return v;
+    };
+    // The tile after tb: nw further on, or claimed (tc_v, lane 0's) if that is
+    // one to claim; none after a tile past the end.
+    int tc_v = kNoTile;
+    auto ask_next = [&]() {
+        tc_v = kNoTile;
+        if (tb + nw >= ts && tb < t1 && ts < t1) tc_v = claim_tile();
+    };
+    ask_next();
+
     int slot = rg.slot;
     int staged = -1;
     MatchSegs segs{rg.event, 0};
-    for (int t = rg.t0; t < rg.t1;) {
-        const bool first = t == rg.t0;
-        int k = rg.kf, tb = rg.slot_t0, te = rg.slot_t1, pass = rg.pass, key = rg.stage_key;
+    for (int seg = 0;; ++seg) {
+        int k = rg.kf, tb0 = rg.slot_t0, te = rg.slot_t1, pass = rg.pass, key = rg.stage_key;
         StageKf sk{rg.kp_off, rg.n_kp, rg.invw, rg.invh};
-        if (!first) {
+        if (seg == 0) {
+            if (rg.t0 >= rg.t1) break;
+        } else {
+            // the lowest tile any wave still holds (three minima in turn: one
+            // is cleared a segment after its last reader)
+            if (lane == 0 && ta < t1) atomicMin(&s_first[seg % 3], ta);
+            __syncthreads();   // also: every reader of the keyframe is done, its pairs are listed
+            const int t = uniform_i(s_first[seg % 3]);
+            if (tid == 0) s_first[(seg + 2) % 3] = INT32_MAX;
+            if (t >= t1) {
+                // nothing is left of the range: help another
+                if (wid == 0) pick_range(h, ctr, segs.event, kHeld, rg.priv_cap, s_list[0], s_help);
+                __syncthreads();
+                const int v = uniform_i(s_help[0]);
+                if (v < 0) break;
+                own = v;
+                const WgRange& r = h.wg_range[v];
+                t1 = uniform_i(r.t1);
+                ts = range_shared(uniform_i(r.t0), t1, nw);
+                slot = uniform_i(r.slot);
+                const int a_v = claim_tile(), b_v = claim_tile();
+                ta = uniform_i(a_v);
+                tb = uniform_i(b_v);
+                ask_next();
+                continue;
+            }
             while (t >= uniform_i(h.tile_prefix[slot + 1])) ++slot;
             k = uniform_i(h.kf_order[slot]);
-            tb = uniform_i(h.tile_prefix[slot]);
+            tb0 = uniform_i(h.tile_prefix[slot]);
             te = uniform_i(h.tile_prefix[slot + 1]);
             const KfDesc& kn = kf_tab[k];
             pass = uniform_i(kn.pass);
             key = uniform_i(kn.stage_key);
             sk = {uniform_i(kn.kp_off), uniform_i(kn.n_kp), uniform_f(kn.invw), uniform_f(kn.invh)};
         }
+        te = min(te, t1);
         StageKp pre[kStagePre];
         const bool build = MODE != kModeGlobal && staged != key;
+        cmem<BatchHdr>* const hs = fresh(hp);
+        const StageEnv stage{hs->kp_xy, hs->kp_oct, hs->kp_owner, hs->kp_desc, C, R, nb, hmask};
         if (build) stage_load(stage, sk, pre);
-        const KfDesc kd = uniform_kf(kf_tab[k]);   // scalar registers, kept across the stores below
-        PassOut po = h.out[pass];
-        po.best_idx = uniform_p(po.best_idx);
-        po.best_dist = uniform_p(po.best_dist);
-        po.second_dist = uniform_p(po.second_dist);
-        po.decision = uniform_p(po.decision);
-        po.target = uniform_p(po.target);
-        po.hamming_th = uniform_i(po.hamming_th);
-        po.nn_ratio = uniform_f(po.nn_ratio);
-        T.r0 = uniform_f(po.r0);
-        const int t_end = min(rg.t1, te);
-        const int64_t kend = kd.pair_off + kd.n_pairs;
-        const int64_t sb = kd.pair_off + (int64_t)(t - tb) * kd.tile_pairs;
-        const int64_t se = min(kd.pair_off + (int64_t)(t_end - tb) * kd.tile_pairs, kend);
-        t = t_end;
+        const KfDesc* const kf = kf_tab + k;
+        const KfDesc kd = search_kf(fresh(kf));
+        // A tile is the pairs [first_pair(t), + kChunk) of the keyframe, up to
+        // its last pair se.
+        const int64_t se = kd.pair_off + kd.n_pairs;
+        auto first_pair = [&](int t) { return kd.pair_off + (int64_t)(t - tb0) * kChunk; };
+        // pairs of the 64 from pair o on (any value <= 0: none)
+        auto left = [&](int64_t o) { return (int)min(se - o, (int64_t)kWave); };
         if (want_matches && kd.event != segs.event) {
-            __syncthreads();   // every pair of the events before is listed
+            // (the barrier above: every pair of the events before is listed)
             segs.next(h, rg, s_list, kd.event);
             __syncthreads();
         }
-        // The points of a wave's next chunk are loaded while its current
-        // chunk is evaluated (and the point indices of the one after), those
-        // of its first while the keyframe is staged: their latency overlaps.
-        constexpr int kChunk = kWave * PPL;
-        const int64_t n_chunks = (se - sb + kChunk - 1) / kChunk;
-        // pairs of the 64 from pair o on (any value <= 0: none)
-        auto left = [&](int64_t o) { return (int)min(se - o, (int64_t)kWave); };
+        // The points of a wave's first tile are loaded while the keyframe is
+        // staged, those of its next while its current one is evaluated, and
+        // with them the point indices of the one after, which is claimed
+        // another tile earlier.
         PairIn pn[PPL];
         int32_t ln[PPL];
+        auto indices = [&](const PointEnv& points, int t) {
 #pragma unroll
-        for (int r = 0; r < PPL; ++r) {
-            const int64_t o = sb + (int64_t)wid * kChunk + r * kWave;
-            ln[r] = load_index(points, kd, o, left(o));
-        }
+            for (int r = 0; r < PPL; ++r) {
+                const int64_t o = first_pair(t) + r * kWave;
+                ln[r] = load_index(points, kd.pair_off, o, t < te ? left(o) : 0);
+            }
+        };
+        auto pts = [&](const PointEnv& points, int32_t mp_off, int32_t n_mp, int t) {
 #pragma unroll
-        for (int r = 0; r < PPL; ++r) {
-            const int64_t o = sb + (int64_t)wid * kChunk + r * kWave;
-            load_point(points, kd, ln[r], left(o), pn[r]);
-            ln[r] = load_index(points, kd, o + nw * kChunk, left(o + nw * kChunk));
+            for (int r = 0; r < PPL; ++r)
+                load_point(points, mp_off, n_mp, ln[r], t < te ? left(first_pair(t) + r * kWave) : 0, pn[r]);
+        };
+        {
+            const PointEnv points = point_env(hs, gate);
+            indices(points, ta);
+            pts(points, kd.mp_off, kd.n_mp, ta);
+            indices(points, tb);
         }
 
         KfView v;
@@ -1034,7 +1133,6 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
             v.hash_mask = kd.hash_mask;
         } else {
             if (build) {
-                if (staged >= 0) __syncthreads();   // every reader of the previous keyframe is done
                 stage_build<MODE == kModeLdsDesc>(stage, sk, pre, s_cs, s_rec, s_desc, s_hash, s_tmp);
                 staged = key;
             }
@@ -1044,22 +1142,27 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
             v.rec = s_rec;
             v.n_rec = search_slots(kp_cap, nb);
             v.desc = MODE == kModeLdsDesc ? s_desc : nullptr;
-            v.desc_orig = stage.desc + 32 * (int64_t)kd.kp_off;
+            v.desc_orig = nullptr;   // read where it is used
             v.own = nullptr;
             v.hash = s_hash;
-            v.hash_mask = stage.hmask;
+            v.hash_mask = hmask;
         }
 
-        for (int64_t c = wid; c < n_chunks; c += nw) {
-            const int64_t cb = sb + c * kChunk;
+        while (ta < te) {
+            const int64_t cb = first_pair(ta);
             PairIn p[PPL];
 #pragma unroll
-            for (int r = 0; r < PPL; ++r) {
-                const int64_t o1 = cb + nw * kChunk + r * kWave, o2 = o1 + nw * kChunk;
-                p[r] = pn[r];
-                load_point(points, kd, ln[r], left(o1), pn[r]);
-                ln[r] = load_index(points, kd, o2, left(o2));
+            for (int r = 0; r < PPL; ++r) p[r] = pn[r];
+            const int tc = tb + nw < ts ? tb + nw : uniform_i(tc_v);
+            {
+                cmem<KfDesc>* const kc = fresh(kf);
+                const PointEnv points = point_env(fresh(hp), gate);
+                pts(points, kc->mp_off, kc->n_mp, tb);
+                indices(points, tc);
             }
+            ta = tb;
+            tb = tc;
+            ask_next();
 #pragma unroll
             for (int r = 0; r < PPL; ++r) {
                 const int64_t o = cb + r * kWave;   // lane 0's pair
@@ -1068,35 +1171,52 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
                 res.target = -1;
                 res.ku = res.kv = 0.0f;
                 PairScan sq;
-                const bool searching = search_front<MODE, STATS>(kd, v, T, gate, C, R, p[r], sq, st);
+                bool searching;
+                {
+                    cmem<BatchHdr>* const hc = fresh(hp);
+                    OctaveTable T;
+                    T.all = s_sf;
+                    T.N = hc->n_octaves;
+                    T.r0 = hc->out[pass].r0;
+#pragma unroll
+                    for (int n = 0; n < kOctReg; ++n) T.sf[n] = hc->sf[n];
+                    searching = search_front<MODE, STATS>(search_kf(fresh(kf)), v, T, gate, C, R, p[r], sq, st);
+                }
                 WaveCand& wc = s_wc[wid];
-                search_scan<MODE, STATS>(v, gate, C, mp_desc, p[r], sq, wc, st);
+                cmem<BatchHdr>* const hc = fresh(hp);
+                const int64_t kp_off = fresh(kf)->kp_off;
+                if (MODE == kModeLdsRec) v.desc_orig = hc->kp_desc + 32 * kp_off;
+                search_scan<MODE, STATS>(v, gate, C, hc->mp_desc, p[r], sq, wc, st);
                 res.best.key = wc.best[lane];
                 res.best.second = (int)wc.second[lane];
+                cmem<BatchHdr>* const hb = fresh(hp);
+                cmem<PassOut>* const po = &hb->out[pass];
                 if (searching)
-                    search_back(kd, po.hamming_th, po.nn_ratio, kp_owner, want_matches ? kp_xy : nullptr, p[r], res);
+                    search_back(po->hamming_th, po->nn_ratio, hb->kp_owner + kp_off,
+                                want_matches ? hb->kp_xy + 2 * kp_off : nullptr, p[r], res);
                 // Stores and loads are counted together, in order: the next
-                // chunk's loads are waited for here (they were issued before
-                // this chunk's scan), not behind the stores below.
+                // tiles' loads (and the claim) are waited for here, not behind
+                // the stores below.
 #pragma unroll
                 for (int i = 0; i < PPL; ++i)
                     asm volatile("" : "+v"(pn[i].x), "+v"(pn[i].y), "+v"(pn[i].z), "+v"(pn[i].dm), "+v"(pn[i].id),
                                       "+v"(ln[i]));
+                asm volatile("" : "+v"(tc_v));
                 const uint32_t key = res.best.key;
                 const int bidx = key == 0xFFFFFFFFu ? -1 : (int)(key & 0xFFFFu);
-                const int kpg = kd.claim_off + (bidx < 0 ? 0 : bidx);   // claim slot
+                const int kpg = fresh(kf)->claim_off + (bidx < 0 ? 0 : bidx);   // claim slot
                 const uint32_t ul = (uint32_t)lane;
                 if (active) {
-                    stg(po.best_idx + o + ul, (int32_t)bidx);
-                    stg(po.best_dist + o + ul, (int16_t)(key == 0xFFFFFFFFu ? FL_NO_DIST : (int)(key >> 16)));
-                    stg(po.second_dist + o + ul, (int16_t)res.best.second);
-                    stg(po.decision + o + ul, p[r].dec);
-                    stg(po.target + o + ul, res.target);
+                    stg(po->best_idx + o + ul, (int32_t)bidx);
+                    stg(po->best_dist + o + ul, (int16_t)(key == 0xFFFFFFFFu ? FL_NO_DIST : (int)(key >> 16)));
+                    stg(po->second_dist + o + ul, (int16_t)res.best.second);
+                    stg(po->decision + o + ul, p[r].dec);
+                    stg(po->target + o + ul, res.target);
                 }
                 const bool is_add = active && p[r].dec == FL_ADD;
                 const bool acc = want_matches && active && (p[r].dec == FL_ADD || p[r].dec == FL_FUSE);
                 if (is_add)
-                    __hip_atomic_fetch_min((gmem<unsigned long long>*)(claim + kpg),
+                    __hip_atomic_fetch_min((gmem<unsigned long long>*)(hb->claim + kpg),
                                            (unsigned long long)epoch << 32 | (uint32_t)p[r].gp, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 // one LDS reservation per wave for both lists
@@ -1114,7 +1234,7 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
                     e.kp = kpg;
                     e.gp = p[r].gp;
                     e.pass = pass;
-                    stg_rec(add_list + rg.priv_off + ba + __builtin_amdgcn_mbcnt_hi((uint32_t)(ma >> 32),
+                    stg_rec(hb->add_list + rg.priv_off + ba + __builtin_amdgcn_mbcnt_hi((uint32_t)(ma >> 32),
                                 __builtin_amdgcn_mbcnt_lo((uint32_t)ma, 0u)), e);
                 }
                 if (acc) {
@@ -1127,7 +1247,7 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
                     me.v = res.kv;
                     me.kf = k;
                     me.pad0 = me.pad1 = 0;
-                    stg_rec(match_stage + rg.priv_off + bm + __builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32),
+                    stg_rec(hb->match_stage + rg.priv_off + bm + __builtin_amdgcn_mbcnt_hi((uint32_t)(mm >> 32),
                                 __builtin_amdgcn_mbcnt_lo((uint32_t)mm, 0u)), me);
                 }
             }

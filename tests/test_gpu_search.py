@@ -324,3 +324,61 @@ def test_one_large_keyframe_among_small_ones(ctx, big):
             assert_same(batched(ctx, ev), exp, f"ppl {ppl} mode {mode}")
     finally:
         ctx.set_tuning(saved.pairs_per_lane, saved.lds_mode, saved.wg_per_cu, saved.xcd_aware)
+
+
+@pytest.mark.parametrize("win", [12.0, 25.0, 90.0])
+def test_windows_of_many_rows(ctx, win):
+    # windows of 3 to 65 grid rows (10 pixels each, octaves 0 to 7): the scan
+    # takes four rows at a time, the lanes of a wave with different numbers
+    import dataclasses
+    ev = synth.gen_tiny(41, n_kf=3, n_mp=700, n_kp=(150, 260), skip_frac=0.05)
+    P = dataclasses.replace(ev.params, win_px=win)
+    exp = oracle.search_fuse(ev, params=P)
+    assert_same(plain_per_keyframe(ctx, ev, P), exp, "plain")
+    saved = ctx.get_tuning()
+    try:
+        for ppl, mode in itertools.product((1, 4), (0, 1, 2)):
+            ctx.set_tuning(ppl, mode, 1, 1)
+            assert_same(batched(ctx, ev, params=P), exp, f"ppl {ppl} mode {mode}")
+            assert_same(batched(ctx, ev, params=P, use_dmax=False), oracle.search_fuse(ev, params=P, use_dmax=False),
+                        f"no gate, ppl {ppl} mode {mode}")
+    finally:
+        ctx.set_tuning(saved.pairs_per_lane, saved.lds_mode, saved.wg_per_cu, saved.xcd_aware)
+
+
+@pytest.mark.parametrize("wg_per_cu", [1, 2])
+def test_accepted_pairs_of_every_event_are_counted(ctx, wg_per_cu):
+    # 330 keyframes of 110 events, more than there are workgroups: most
+    # workgroups take several events, large events several workgroups, and
+    # every seventh event accepts nothing; the refinement finds each event's
+    # accepted pairs among the workgroups' lists
+    import paper_2603_17201_amd as fl
+    evs = []
+    for i in range(110):
+        e = synth.gen_tiny(500 + i, n_kf=3, n_mp=2500 if i % 10 == 3 else 70 + 13 * (i % 9), n_kp=(20, 60),
+                           sparse=i % 4 == 2)
+        if i % 7 == 0:
+            e.kp_desc = e.kp_desc ^ np.uint8(0xFF)   # every distance far above the threshold
+        evs.append(e)
+    B = synth.concat_events(evs)
+    exp = oracle.search_fuse(B)
+    accepted = np.isin(exp["decision"], (2, 3))   # ADD, FUSE
+    kf_pairs = np.add.reduceat(np.append(accepted, False), B.pair_offset[:-1].astype(np.int64))
+    kf_pairs[np.diff(B.pair_offset) == 0] = 0
+    n_ref = np.array([kf_pairs[a:b].sum() for a, b in zip(B.event_kf_offset[:-1], B.event_kf_offset[1:])])
+    assert (n_ref == 0).sum() >= 16 and n_ref.max() > 20
+    b = fl.DeviceBatch(B, device=dev())
+    S0 = np.stack([e.S_init for e in evs])
+    saved = ctx.get_tuning()
+    try:
+        ctx.set_tuning(saved.pairs_per_lane, saved.lds_mode, wg_per_cu, saved.xcd_aware)
+        for run in (ctx.search_fuse_batched, ctx.search_fuse_graph):
+            nm = torch.full((110,), -7, dtype=torch.int32, device=dev())
+            got = run(b, B.params, refine=(1, 2.45, t(S0.copy()), None, nm)).numpy()
+            assert_same(got, exp, run.__name__)
+            # a step counts the pairs in front of their keyframe: all accepted ones, or
+            # none (-1) where its system is singular
+            n = nm.cpu().numpy()
+            assert ((n == n_ref) | (n == -1) & (n_ref < 4)).all(), (n[n != n_ref], n_ref[n != n_ref])
+    finally:
+        ctx.set_tuning(saved.pairs_per_lane, saved.lds_mode, saved.wg_per_cu, saved.xcd_aware)
