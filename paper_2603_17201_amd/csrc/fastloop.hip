@@ -1097,7 +1097,7 @@ int fl_build_grid(fl_ctx* c, int32_t n_kp, const float* kp_xy, const fl_pinhole*
     fl_sim3 I{};
     fill_kf_geometry(kd, I, *K, P);
     kd.n_kp = n_kp;
-    hipLaunchKernelGGL(grid_single_kernel, dim3(1), dim3(kPrepBlock), 0, stream, kd,
+    hipLaunchKernelGGL(grid_single_kernel, dim3(1), dim3(kSingleBlock), 0, stream, kd,
                        P->grid_cols * P->grid_rows, P->grid_cols, P->grid_rows, kp_xy, cell_start, cell_kp);
     FL_HIP(hipGetLastError());
     return FL_OK;
@@ -1194,21 +1194,16 @@ int plain_launch(char* base, const PlainLayout& L, int32_t n_mp, const float* mp
     a.second_dist = out->second_dist;
     a.decision = out->decision;
     a.target = out->target;
-    if (kf->cell_start) {
-        a.cell_start = kf->cell_start;
-        a.cell_kp = kf->cell_kp;
-    } else {
-        int32_t* cs = (int32_t*)(base + L.o_cs);
-        int32_t* ck = (int32_t*)(base + L.o_ck);
-        hipLaunchKernelGGL(grid_single_kernel, dim3(1), dim3(kPrepBlock), 0, stream, a.kd, cells, P->grid_cols,
-                           P->grid_rows, kf->kp_xy, cs, ck);
-        a.cell_start = cs;
-        a.cell_kp = ck;
-    }
-    hipLaunchKernelGGL(plain_prep_kernel, dim3(1), dim3(kPrepBlock), 0, stream, n_kp, kf->kp_owner,
-                       (int32_t*)(base + L.o_hash), L.hsize - 1, a.claim, a.counter);
+    int32_t* cs = (int32_t*)(base + L.o_cs);
+    int32_t* ck = (int32_t*)(base + L.o_ck);
+    a.cell_start = kf->cell_start ? kf->cell_start : cs;
+    a.cell_kp = kf->cell_start ? kf->cell_kp : ck;
+    const PlainPrep prep{kf->kp_owner, (int32_t*)(base + L.o_hash), L.hsize - 1, a.claim, a.counter};
+    hipLaunchKernelGGL(plain_prep_kernel, dim3(kf->cell_start ? 1 : 2), dim3(kSingleBlock), 0, stream, a.kd, cells,
+                       P->grid_cols, P->grid_rows, kf->kp_xy, cs, ck, prep);
+    const int64_t search_grid = ((int64_t)n_mp * kPlainLanes + kPlainBlock - 1) / kPlainBlock;
+    hipLaunchKernelGGL(search_plain_kernel, dim3((uint32_t)search_grid), dim3(kPlainBlock), 0, stream, a);
     const int grid = (n_mp + 255) / 256;
-    hipLaunchKernelGGL(search_plain_kernel, dim3(grid), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(resolve_plain_kernel, dim3(std::min(grid, 256)), dim3(256), 0, stream, n_mp,
                        (const uint32_t*)a.counter, (const AddRef*)a.add_list, (int32_t)L.cap,
                        (const int32_t*)a.claim, mp_id, (const int32_t*)out->best_idx, out->decision, out->target);

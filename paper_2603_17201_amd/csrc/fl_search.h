@@ -344,40 +344,55 @@ __device__ __forceinline__ void stage_build(const StageEnv& env, const StageKf& 
 
 constexpr int kPrepBlock = 256;
 
-__device__ void build_grid_global(const KfDesc& kd, int cells, int C, int R, const float* __restrict__ kp_xy,
-                                  int32_t* __restrict__ cs, int32_t* __restrict__ ck, int32_t* s_cnt,
-                                  int32_t* s_tmp) {
+// cs[c] = first entry of cell c in ck (cs[cells] = n), the keypoints of a cell
+// in increasing index order.  s_cnt: cells + 1 ints of LDS.  With s_ck (at
+// least n entries of LDS) the list is put together and sorted there.
+__device__ __forceinline__ void build_grid_global(const KfDesc& kd, int cells, int C, int R,
+                                                  const float* __restrict__ kp_xy, int32_t* __restrict__ cs,
+                                                  int32_t* __restrict__ ck, int32_t* s_cnt, int32_t* s_tmp,
+                                                  uint16_t* s_ck = nullptr) {
     const int tid = threadIdx.x, nb = blockDim.x;
     const int n = kd.n_kp;
     const float* xy = kp_xy + 2 * (int64_t)kd.kp_off;
+    auto cell = [&](int i) { return cell_of(ldg(xy + 2 * i + 1), kd.invh, R) * C + cell_of(ldg(xy + 2 * i), kd.invw, C); };
+    // the cell of the thread's first keypoint is kept for the second pass
+    // (and loaded while the counters are cleared)
+    const int c0 = tid < n ? cell(tid) : 0;
     for (int c = tid; c <= cells; c += nb) s_cnt[c] = 0;
     __syncthreads();
-    for (int i = tid; i < n; i += nb) {
-        const int c = cell_of(xy[2 * i + 1], kd.invh, R) * C + cell_of(xy[2 * i], kd.invw, C);
-        atomicAdd(&s_cnt[c], 1);
-    }
+    for (int i = tid; i < n; i += nb) atomicAdd(&s_cnt[i == tid ? c0 : cell(i)], 1);
     __syncthreads();
     block_exclusive_scan(s_cnt, cells, s_tmp);
     for (int c = tid; c < cells; c += nb) cs[c] = s_cnt[c];
     if (tid == 0) cs[cells] = n;
     __syncthreads();
     for (int i = tid; i < n; i += nb) {
-        const int c = cell_of(xy[2 * i + 1], kd.invh, R) * C + cell_of(xy[2 * i], kd.invw, C);
-        ck[atomicAdd(&s_cnt[c], 1)] = i;
+        const int slot = atomicAdd(&s_cnt[i == tid ? c0 : cell(i)], 1);   // ends as the next cell's first
+        if (s_ck) s_ck[slot] = (uint16_t)i;
+        else ck[slot] = i;
     }
     __syncthreads();
     // keypoints of a cell in increasing index order (deterministic layout)
-    for (int c = tid; c < cells; c += nb) {
-        const int b = cs[c], e = cs[c + 1];
-        for (int a = b + 1; a < e; ++a) {
-            const int v = ck[a];
-            int j = a - 1;
-            while (j >= b && ck[j] > v) {
-                ck[j + 1] = ck[j];
-                --j;
+    auto sort = [&](auto* list) {
+        for (int c = tid; c < cells; c += nb) {
+            const int b = c ? s_cnt[c - 1] : 0, e = s_cnt[c];
+            for (int a = b + 1; a < e; ++a) {
+                const auto v = list[a];
+                int j = a - 1;
+                while (j >= b && list[j] > v) {
+                    list[j + 1] = list[j];
+                    --j;
+                }
+                list[j + 1] = v;
             }
-            ck[j + 1] = v;
         }
+    };
+    if (s_ck) {
+        sort(s_ck);
+        __syncthreads();
+        for (int i = tid; i < n; i += nb) ck[i] = s_ck[i];
+    } else {
+        sort(ck);
     }
     __syncthreads();
 }
@@ -415,14 +430,71 @@ __global__ __launch_bounds__(kPrepBlock) void prep_global_kernel(const BatchHdr*
     }
 }
 
-// Grid of a single keyframe into caller buffers (fl_build_grid).
-__global__ __launch_bounds__(kPrepBlock) void grid_single_kernel(KfDesc kd, int cells, int C, int R,
-                                                               const float* __restrict__ kp_xy,
-                                                               int32_t* __restrict__ cell_start,
-                                                               int32_t* __restrict__ cell_kp) {
+// What a plain search needs of its keyframe before it starts, in one launch:
+// workgroup 0 builds the grid into (caller or scratch) buffers; the other (or
+// the only one, given a grid) makes the owner hash set and resets the claims
+// and the ADD counter.  Both are chains of short steps over some thousand
+// entries, bound by their barriers and round trips: with 1,024 threads a
+// keyframe of 1,000 keypoints takes one or two entries a thread at each
+// (4.8 us; two launches of 256 threads in turn took 10.3 and 5.1).
+constexpr int kSingleBlock = 1024;
+constexpr int kSingleLds = 8192;   // keypoints whose list is sorted in LDS
+
+struct PlainPrep {
+    const int32_t* kp_owner;
+    int32_t* tab;
+    int32_t mask;
+    int32_t* claim;
+    uint32_t* counter;
+};
+
+__device__ __forceinline__ void grid_single(const KfDesc& kd, int cells, int C, int R, const float* kp_xy,
+                                            int32_t* cell_start, int32_t* cell_kp) {
     __shared__ int32_t s_cnt[FL_MAX_CELLS + 1];
-    __shared__ int32_t s_tmp[kPrepBlock / kWave + 1];
-    build_grid_global(kd, cells, C, R, kp_xy, cell_start, cell_kp, s_cnt, s_tmp);
+    __shared__ int32_t s_tmp[kSingleBlock / kWave + 1];
+    __shared__ uint16_t s_ck[kSingleLds];
+    build_grid_global(kd, cells, C, R, kp_xy, cell_start, cell_kp, s_cnt, s_tmp, kd.n_kp <= kSingleLds ? s_ck : nullptr);
+}
+
+// Grid of a single keyframe into caller buffers (fl_build_grid).
+__global__ __launch_bounds__(kSingleBlock) void grid_single_kernel(KfDesc kd, int cells, int C, int R,
+                                                                 const float* __restrict__ kp_xy,
+                                                                 int32_t* __restrict__ cell_start,
+                                                                 int32_t* __restrict__ cell_kp) {
+    grid_single(kd, cells, C, R, kp_xy, cell_start, cell_kp);
+}
+
+__global__ __launch_bounds__(kSingleBlock) void plain_prep_kernel(KfDesc kd, int cells, int C, int R,
+                                                                const float* __restrict__ kp_xy,
+                                                                int32_t* __restrict__ cell_start,
+                                                                int32_t* __restrict__ cell_kp, PlainPrep p) {
+    const int tid = threadIdx.x, n = kd.n_kp;
+    if (blockIdx.x + 1 < gridDim.x) {
+        grid_single(kd, cells, C, R, kp_xy, cell_start, cell_kp);
+        return;
+    }
+    const int32_t own = tid < n ? ldg(p.kp_owner + tid) : -1;
+    for (int i = tid; i < n; i += kSingleBlock) p.claim[i] = 0x7FFFFFFF;
+    if (tid == 0) *p.counter = 0;
+    if (p.mask < 2 * kSingleLds) {
+        // the set in LDS, then copied out
+        __shared__ int32_t s_tab[2 * kSingleLds];
+        for (int s = tid; s <= p.mask; s += kSingleBlock) s_tab[s] = -1;
+        __syncthreads();
+        for (int i = tid; i < n; i += kSingleBlock) {
+            const int32_t o = i == tid ? own : ldg(p.kp_owner + i);
+            if (o >= 0) owner_insert(s_tab, p.mask, o);
+        }
+        __syncthreads();
+        for (int s = tid; s <= p.mask; s += kSingleBlock) p.tab[s] = s_tab[s];
+    } else {
+        for (int s = tid; s <= p.mask; s += kSingleBlock) p.tab[s] = -1;
+        __syncthreads();
+        for (int i = tid; i < n; i += kSingleBlock) {
+            const int32_t o = i == tid ? own : ldg(p.kp_owner + i);
+            if (o >= 0) owner_insert(p.tab, p.mask, o);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1282,22 +1354,6 @@ __global__ __launch_bounds__(kResolveBlock) void resolve_adds_kernel(const Batch
 // gathered through the caller's (or a freshly built) cell_start / cell_kp
 // grid from the keyframe's own arrays.
 
-// Owner hash set and claim reset of a single keyframe (plain path).
-__global__ __launch_bounds__(kPrepBlock) void plain_prep_kernel(int n, const int32_t* __restrict__ kp_owner,
-                                                              int32_t* __restrict__ tab, int32_t mask,
-                                                              int32_t* __restrict__ claim,
-                                                              uint32_t* __restrict__ counter) {
-    const int tid = threadIdx.x;
-    for (int s = tid; s <= mask; s += blockDim.x) tab[s] = -1;
-    for (int i = tid; i < n; i += blockDim.x) claim[i] = 0x7FFFFFFF;
-    if (tid == 0) *counter = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += blockDim.x) {
-        const int32_t o = kp_owner[i];
-        if (o >= 0) owner_insert(tab, mask, o);
-    }
-}
-
 struct PlainArgs {
     KfDesc kd;
     SearchConst sc;
@@ -1324,67 +1380,113 @@ struct PlainArgs {
     int32_t* target;
 };
 
-__global__ __launch_bounds__(256) void search_plain_kernel(PlainArgs a) {
+// The plain search gives each point kPlainLanes neighbouring lanes: with one
+// lane a point, a call of 2,000 points puts 32 waves on the chip, each walking
+// its window's candidates one after the other, four dependent loads apiece.
+// Lane j of a point takes the rows j mod 4, every fourth, and of a row's
+// candidates every second from j / 4 on; the lanes' best and second are put
+// together at the end.  (2,000 points, 1,000 keypoints: 8.0 us, 13.0 with one
+// lane a point.)
+constexpr int kPlainBlock = 256;
+constexpr int kPlainLanes = 8;
+
+// a's and b's candidates together: the better best key; of the other key and
+// the two seconds the smallest distance.
+__device__ __forceinline__ void merge_best(Best& a, uint32_t key, int second) {
+    const uint32_t lose = max(a.key, key);
+    a.key = min(a.key, key);
+    a.second = min(a.second, second);
+    if (lose != 0xFFFFFFFFu) a.second = min(a.second, (int)(lose >> 16));
+}
+
+__global__ __launch_bounds__(kPlainBlock) void search_plain_kernel(PlainArgs a) {
     __shared__ float s_sf[FL_MAX_OCTAVES];
     if (threadIdx.x < FL_MAX_OCTAVES) s_sf[threadIdx.x] = a.sc.sf[threadIdx.x];
-    __syncthreads();
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t o = ((int64_t)blockIdx.x * kPlainBlock + threadIdx.x) / kPlainLanes;
+    const int sub = threadIdx.x % kPlainLanes;
     const bool active = o < a.n_mp;
     const KfDesc& kd = a.kd;
     const SearchConst& sc = a.sc;
     uint8_t dec = active ? kDecUndecided : (uint8_t)0;
     const int32_t gp = (int32_t)o;
-    const int32_t id = active ? (a.mp_id ? a.mp_id[gp] : gp) : 0;
-    if (active && owner_lookup(a.hash, kd.hash_mask, id)) dec = FL_SKIP;
+    // the point's loads together; the owner set's first entry is on its way
+    // while the point is projected
+    int32_t id = 0;
+    float x = 0.0f, y = 0.0f, z = 0.0f, dmax = 0.0f;
+    uint4 a0 = make_uint4(0, 0, 0, 0), a1 = a0;
+    if (active) {
+        id = a.mp_id ? ldg(a.mp_id + gp) : gp;
+        x = ldg(a.mp_xyz + 3 * o);
+        y = ldg(a.mp_xyz + 3 * o + 1);
+        z = ldg(a.mp_xyz + 3 * o + 2);
+        if (sc.gate) dmax = ldg(a.mp_dmax + o);
+        load_desc(a.mp_desc, o, a0, a1);
+    }
+    __syncthreads();
+    const bool probe = active && id >= 0;
+    uint32_t hh = owner_slot(id, kd.hash_mask);
+    int32_t hv = probe ? ldg(a.hash + hh) : -1;
+    Proj p;
+    const bool vis = project(kd, x, y, z, dmax, sc.gate, s_sf, sc.N, p);
     Best best;
     best.init();
     int32_t target = -1;
+    Window w{};
+    if (active && vis) w = make_window(p, kd, s_sf, sc.r0, sc.C, sc.R);
+    for (int n = 0; probe && n <= kd.hash_mask && hv >= 0; ++n) {
+        if (hv == id) {
+            dec = FL_SKIP;
+            break;
+        }
+        hh = (hh + 1) & (uint32_t)kd.hash_mask;
+        hv = ldg(a.hash + hh);
+    }
+    if (dec == kDecUndecided && !vis) dec = FL_NOT_VISIBLE;
     if (dec == kDecUndecided) {
-        const float x = a.mp_xyz[3 * o], y = a.mp_xyz[3 * o + 1], z = a.mp_xyz[3 * o + 2];
-        const float dmax = sc.gate ? a.mp_dmax[o] : 0.0f;
-        Proj p;
-        if (!project(kd, x, y, z, dmax, sc.gate, s_sf, sc.N, p)) {
-            dec = FL_NOT_VISIBLE;
-        } else {
-            uint4 a0, a1;
-            load_desc(a.mp_desc, o, a0, a1);
-            const Window w = make_window(p, kd, s_sf, sc.r0, sc.C, sc.R);
-            for (int row = w.r0; row <= w.r1; ++row) {
-                // a caller-supplied grid is clamped to the keypoint range
-                const int s = max(a.cell_start[row * sc.C + w.c0], 0);
-                const int e = min(a.cell_start[row * sc.C + w.c1 + 1], kd.n_kp);
-                for (int i = s; i < e; ++i) {
-                    const int kp = a.cell_kp[i];
-                    if ((unsigned)kp >= (unsigned)kd.n_kp) continue;
-                    const float kx = a.kp_xy[2 * kp], ky = a.kp_xy[2 * kp + 1];
-                    if (!in_window(w, kx, ky, (int)a.kp_oct[kp], p.pred, sc.gate)) continue;
-                    uint4 b0, b1;
-                    load_desc(a.kp_desc, kp, b0, b1);
-                    best.offer(hamming(a0, a1, b0, b1), kp);
-                }
+        for (int row = w.r0 + sub % 4; row <= w.r1; row += 4) {
+            // a caller-supplied grid is clamped to the keypoint range
+            const int s = max(ldg(a.cell_start + row * sc.C + w.c0), 0);
+            const int e = min(ldg(a.cell_start + row * sc.C + w.c1 + 1), kd.n_kp);
+            for (int i = s + sub / 4; i < e; i += kPlainLanes / 4) {
+                const int kp = ldg(a.cell_kp + i);
+                if ((unsigned)kp >= (unsigned)kd.n_kp) continue;
+                const float kx = ldg(a.kp_xy + 2 * kp), ky = ldg(a.kp_xy + 2 * kp + 1);
+                const int oct = ldg(a.kp_oct + kp);
+                uint4 b0, b1;
+                load_desc(a.kp_desc, kp, b0, b1);
+                if (in_window(w, kx, ky, oct, p.pred, sc.gate)) best.offer(hamming(a0, a1, b0, b1), kp);
             }
-            if (!accept_match(best, sc.th, sc.ratio)) {
-                dec = FL_NO_MATCH;
+        }
+    }
+#pragma unroll
+    for (int off = 1; off < kPlainLanes; off <<= 1) {
+        const uint32_t key = (uint32_t)__shfl_xor((int)best.key, off);
+        const int second = __shfl_xor(best.second, off);
+        merge_best(best, key, second);
+    }
+    if (dec == kDecUndecided) {
+        if (!accept_match(best, sc.th, sc.ratio)) {
+            dec = FL_NO_MATCH;
+        } else {
+            const int32_t ow = ldg(a.kp_owner + (best.key & 0xFFFFu));
+            if (ow >= 0) {
+                dec = FL_FUSE;
+                target = ow;
             } else {
-                const int32_t ow = a.kp_owner[best.key & 0xFFFFu];
-                if (ow >= 0) {
-                    dec = FL_FUSE;
-                    target = ow;
-                } else {
-                    dec = FL_ADD;
-                }
+                dec = FL_ADD;
             }
         }
     }
     const int bidx = best.key == 0xFFFFFFFFu ? -1 : (int)(best.key & 0xFFFFu);
-    if (active) {
+    const bool write = active && sub == 0;
+    if (write) {
         a.best_idx[o] = bidx;
         a.best_dist[o] = (int16_t)(best.key == 0xFFFFFFFFu ? FL_NO_DIST : (int)(best.key >> 16));
         a.second_dist[o] = (int16_t)best.second;
         a.decision[o] = dec;
         a.target[o] = target;
     }
-    const bool is_add = active && dec == FL_ADD;
+    const bool is_add = write && dec == FL_ADD;
     if (is_add) atomicMin(&a.claim[bidx], gp);
     AddRef e;
     e.pair = (int32_t)o;

@@ -382,3 +382,18 @@ def test_accepted_pairs_of_every_event_are_counted(ctx, wg_per_cu):
             assert ((n == n_ref) | (n == -1) & (n_ref < 4)).all(), (n[n != n_ref], n_ref[n != n_ref])
     finally:
         ctx.set_tuning(saved.pairs_per_lane, saved.lds_mode, saved.wg_per_cu, saved.xcd_aware)
+
+
+@pytest.mark.parametrize("n_kp", [1, 1023, 1024, 1025, 8192, 8193])
+def test_plain_search_over_keypoint_counts(ctx, n_kp):
+    # one keypoint a thread, a second one, and the last list that is put
+    # together on the chip; windows of up to eight rows, grid given or not
+    import dataclasses
+    ev = synth.gen_tiny(77, n_kf=1, n_mp=333, n_kp=(n_kp, n_kp), skip_frac=0.1)
+    P = dataclasses.replace(ev.params, win_px=10.0)
+    exp = oracle.search_fuse(ev, params=P)
+    for with_grid in (False, True):
+        assert_same(plain_per_keyframe(ctx, ev, P, with_grid=with_grid), exp, f"grid given: {with_grid}")
+    cs, ck = ctx.build_grid(t(ev.kp_xy), ev.cams[0], P)
+    cs_ref, ck_ref = oracle.build_grid(ev.kp_xy, ev.cams[0], P)
+    assert np.array_equal(cs.cpu().numpy(), cs_ref) and np.array_equal(ck.cpu().numpy(), ck_ref)
