@@ -1158,7 +1158,15 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     const int tid = threadIdx.x;
     const uint32_t epoch = *h.epoch;
     for (int i = tid; i < 16 * kExpTerms; i += blockDim.x) s_cf[i] = kExpTable.v[i];
-    for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
+    // Workgroups of a Gauss-Newton refinement are numbered XCD by XCD (they are
+    // dispatched to the XCDs in turn), so an event of up to 16,384 pairs has its
+    // exchange inside one: 20 keyframes 72.1 -> 69.0 us, 73 keyframes 198.9 ->
+    // 196.6.  The float64 errors of the other kernels' steps make it the other
+    // way round (20 keyframes with outlier rounds 88.5 -> 92.6): theirs are
+    // spread.
+    const int first = LM || ROUNDS ? (int)blockIdx.x
+                                   : (int)(blockIdx.x % kMaxQueues * (gridDim.x / kMaxQueues) + blockIdx.x / kMaxQueues);
+    for (int unit = first; unit < n_units; unit += gridDim.x) {
         const int ev = unit / B, b = unit % B;
         const EventDesc ed = h.ev[ev];
         const int seg_n = h.refine_scan ? 0 : ed.seg_n;
@@ -1515,9 +1523,13 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     // take them while the others iterate.  The refinement reads accepted
     // pairs only, which an ADD and its relabelling as FUSE both are.
     if (h.resolve_in_refine) {
-        const unsigned long long tag = (unsigned long long)(*h.epoch) << 32;
-        for (int r = (int)(gridDim.x - 1 - blockIdx.x); r < h.n_wg; r += (int)gridDim.x)
-            resolve_region_adds(h, r, tag);
+        // by the workgroups that have no share of any event, if that is most of
+        // them: at the end of the others it would come on top of the steps
+        const unsigned long long tag = (unsigned long long)epoch << 32;
+        const int spare = (int)gridDim.x - n_units;
+        const bool spare_only = 2 * spare >= (int)gridDim.x;
+        const int r0 = spare_only ? first - n_units : (int)gridDim.x - 1 - first;
+        for (int r = r0; r >= 0 && r < h.n_wg; r += spare_only ? spare : (int)gridDim.x) resolve_region_adds(h, r, tag);
     }
 }
 
