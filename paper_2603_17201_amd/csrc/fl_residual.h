@@ -1101,6 +1101,11 @@ __device__ __forceinline__ void compose_exp_lanes(const double* d, const Compose
 constexpr int kRefKfLds = 128;   // keyframes of one event whose pose and intrinsics sit in LDS
 constexpr int kRefMaxB = 64;     // workgroups per event
 constexpr int kRefBlock = 512;   // threads of a refinement workgroup: 64 x 512 pairs at one per thread
+// Accepted pairs of a thread in LDS, after the two or three in registers: ten
+// events of 51,000 to 62,000 pairs each have 25 workgroups apiece, four to five
+// pairs a thread.  Looked up in the search's lists again at every
+// step, a step took 17,900 cycles, with them here 15,900.
+constexpr int kRefLds = 2;
 constexpr int kNAccLM = 37;      // the sums plus the Huber loss (slot 36)
 // Each float64 partial travels as two 64-bit words, (high half << 32 | tag)
 // and (low half << 32 | tag): a word is written and read in one piece, so a
@@ -1143,6 +1148,7 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     __shared__ double s_acc[kNAcc];          // LM: g, H and count at S_acc
     __shared__ double s_Sacc[13];            // LM: S_acc
     __shared__ double s_lm[2];               // LM: loss at S_acc, lambda
+    __shared__ float s_more[kRefLds][6][kRefBlock];   // each thread's pairs after those in registers
     __shared__ int s_segx[kRefBlock];        // the event's segments of accepted pairs: the pairs before each,
     __shared__ int s_segp[kRefBlock];        // and its place in the staging list less those
     __shared__ int s_segw[kRefBlock / kWave];
@@ -1257,6 +1263,20 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 ck_[r] = m.kf;
             }
         }
+        // (the next kRefLds in LDS, each thread its own)
+#pragma unroll 1
+        for (int r = 0; use_list && r < kRefLds && b * (int)blockDim.x + (kRefCache + r) * stride < cnt; ++r) {
+            const int i = b * blockDim.x + tid + (kRefCache + r) * stride;
+            if (i < cnt) {
+                const MatchRec m = pair_at(i);
+                s_more[r][0][tid] = m.x;
+                s_more[r][1][tid] = m.y;
+                s_more[r][2][tid] = m.z;
+                s_more[r][3][tid] = m.u;
+                s_more[r][4][tid] = m.v;
+                s_more[r][5][tid] = __int_as_float(m.kf);
+            }
+        }
         // and its first pair of the other direction
         float ix_ = 0.0f, iy_ = 0.0f, iz_ = 0.0f, iu_ = 0.0f, iv_ = 0.0f;
         int ik_ = -1;
@@ -1327,8 +1347,18 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 if (kRefCache > 1 && b * (int)blockDim.x + stride < cnt) cached(std::integral_constant<int, 1>{});
                 if (kRefCache > 2 && b * (int)blockDim.x + 2 * stride < cnt)
                     cached(std::integral_constant<int, kRefCache - 1>{});
-                for (int i = b * blockDim.x + tid + kRefCache * stride; i < cnt; i += stride) {
-                    const MatchRec m = pair_at(i);
+                for (int i = b * blockDim.x + tid + kRefCache * stride, r = 0; i < cnt; i += stride, ++r) {
+                    MatchRec m;
+                    if (r < kRefLds) {
+                        m.x = s_more[r][0][tid];
+                        m.y = s_more[r][1][tid];
+                        m.z = s_more[r][2][tid];
+                        m.u = s_more[r][3][tid];
+                        m.v = s_more[r][4][tid];
+                        m.kf = __float_as_int(s_more[r][5][tid]);
+                    } else {
+                        m = pair_at(i);
+                    }
                     const KfDesc& kd = h.kf[m.kf];
                     double e;
                     if (bounded && !(pair_error64(s_Srs64, kd.T, kd.fx, kd.fy, kd.cx, kd.cy, m.x, m.y, m.z, m.u, m.v,

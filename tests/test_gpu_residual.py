@@ -790,3 +790,44 @@ def test_two_sided_pairs_that_are_not_finite_add_nothing(ctx):
         out.append((S.cpu().numpy()[0], nm.item()))
     assert out[0][1] == out[1][1]
     assert np.linalg.norm(sim3.log(sim3.compose(out[1][0], sim3.inverse(out[0][0])))) < 1e-6
+
+
+@pytest.mark.parametrize("lm", [None, synth.ROBUST_LM_LAMBDA])
+def test_refinement_of_more_pairs_than_the_registers_hold(ctx, lm):
+    """128 events leave two workgroups of 512 threads each: of the three large
+    ones the first has pairs for the registers and the LDS of its threads, the
+    second fills both, the third has pairs beyond them.  Gauss-Newton, and
+    Levenberg-Marquardt in rounds."""
+    import paper_2603_17201_amd as fl
+    big = [synth.gen_c2(seed=241 + n, n_kf=n, n_mp=6000) for n in (4, 6, 8)]
+    evs = big[:1] + [synth.gen_tiny(700 + i, n_kf=2, n_mp=40, n_kp=(8, 14)) for i in range(125)] + big[1:]
+    B = synth.concat_events(evs)
+    P = B.params
+    exp = oracle.search_fuse(B, use_grid=True)
+    at = (0, 126, 127)
+    it, rounds, tau = synth.ROBUST_ITERS, synth.ROBUST_ROUNDS, synth.ROBUST_OUTLIER_PX
+    refs = []
+    for e in at:
+        if lm is None:
+            refs.append(_event_gn(B, exp, e))
+            continue
+        xyz, uv, kfl, T32 = _event_pairs(B, exp, e)
+        refs.append(R.refine_robust(B.events[e].S_init, xyz, uv, kfl, T32, B.cams[int(B.event_kf_offset[e])],
+                                    float(np.float32(2.45)), iters=it, rounds=rounds,
+                                    outlier_px=float(np.float32(tau)), lm_lambda=lm))
+    n_acc = [len(_event_pairs(B, exp, e)[0]) for e in at]
+    assert 3072 < n_acc[0] < 4096 < n_acc[1] < 5120 < n_acc[2], n_acc
+    b = fl.DeviceBatch(B, device=dev())
+    S0 = np.stack([ev.S_init for ev in B.events])
+    for run in (ctx.search_fuse_batched, ctx.search_fuse_graph):
+        S = t(S0.copy())
+        nm = torch.zeros(len(evs), dtype=torch.int32, device=dev())
+        ref = (10, 2.45, S, None, nm) if lm is None else (it, 2.45, S, None, nm, rounds, tau, lm)
+        got = run(b, P, refine=ref).numpy()
+        for k in got:
+            assert np.array_equal(got[k], exp[k]), (run.__name__, k)
+        S_gpu, n_gpu = S.cpu().numpy(), nm.cpu().numpy()
+        for e, (S_ref, n_ref) in zip(at, refs):
+            assert n_gpu[e] == n_ref, (run.__name__, e, n_gpu[e], n_ref)
+            err = np.linalg.norm(sim3.log(sim3.compose(S_gpu[e], sim3.inverse(S_ref))))
+            assert err < 1e-6, (run.__name__, e, err)
