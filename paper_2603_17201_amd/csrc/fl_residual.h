@@ -1452,11 +1452,17 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 for (int jr = 0; jr < kRowsPer; ++jr)
                     if (w + kSeg * jr < Be) pending |= 1u << jr;
                 unsigned spins = 0;
-                // the rows take about 1,600 cycles to arrive, and a load that
-                // is on its way when they do costs as much again: the first is
-                // sent 900 cycles on (C2's loop event: 9,500 cycles to here a
-                // step without the pause, 8,850 with it)
-                __builtin_amdgcn_s_sleep(14);
+                // A row takes 1,200 (its workgroup on the same XCD) to 1,600
+                // cycles to arrive, and a load that is on its way when it does
+                // costs as much again: the first is sent after a pause.  Calls
+                // with pauses of 4, 8, 11, 14 and 18 units (of 64 cycles): up to
+                // 32 rows, on one XCD, 69.7, 66.6, 67.4, 68.1 and 69.2 us (20
+                // keyframes); 64 rows, whose last are later, 88.4, 86.6, 85.3,
+                // 85.4 and 84.4 (60 keyframes); the other kernels, whose rows
+                // come from every XCD, 89.3, 88.5, 88.2, 87.8 and 87.8.
+                if (LM || ROUNDS) __builtin_amdgcn_s_sleep(14);
+                else if (Be * kMaxQueues <= (int)gridDim.x) __builtin_amdgcn_s_sleep(8);
+                else __builtin_amdgcn_s_sleep(18);
                 while (pending) {
                     asm volatile("" ::: "memory");   // the rows change under this loop
 #pragma unroll
