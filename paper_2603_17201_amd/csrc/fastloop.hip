@@ -307,7 +307,6 @@ int validate_batch(const fl_batch* B, const fl_params* P, const fl_fuse_out* out
 
 constexpr int kPrepGrid = 512;     // workgroups of the global-grid build
 constexpr int kRefineGrid = 256;   // workgroups of a refinement step
-static_assert(kRefineGrid % kMaxQueues == 0, "numbered XCD by XCD");
 // Cost of one keyframe's staging in tiles of one pair a lane in an empty image
 // (a tile's cost grows with the keypoint density): 9,000 cycles against about
 // 470 for a tile of 64 pairs at 1,200 keypoints, whose weight is 1.8.

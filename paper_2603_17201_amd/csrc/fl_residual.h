@@ -1164,15 +1164,12 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
     const int tid = threadIdx.x;
     const uint32_t epoch = *h.epoch;
     for (int i = tid; i < 16 * kExpTerms; i += blockDim.x) s_cf[i] = kExpTable.v[i];
-    // Workgroups of a Gauss-Newton refinement are numbered XCD by XCD (they are
-    // dispatched to the XCDs in turn), so an event of up to 16,384 pairs has its
-    // exchange inside one: 20 keyframes 72.1 -> 69.0 us, 73 keyframes 198.9 ->
-    // 196.6.  The float64 errors of the other kernels' steps make it the other
-    // way round (20 keyframes with outlier rounds 88.5 -> 92.6): theirs are
-    // spread.
-    const int first = LM || ROUNDS ? (int)blockIdx.x
-                                   : (int)(blockIdx.x % kMaxQueues * (gridDim.x / kMaxQueues) + blockIdx.x / kMaxQueues);
-    for (int unit = first; unit < n_units; unit += gridDim.x) {
+    // An event's workgroups wait for each other, so they are spread evenly over
+    // the XCDs (workgroup i is dispatched to XCD i mod 8): refinements in flight
+    // together then fit whenever their workgroups do.  With one event's all on
+    // one XCD, whose exchange is shorter (20 keyframes 72.1 -> 69.0 us), two such
+    // launches would each hold CUs the other waits for.
+    for (int unit = blockIdx.x; unit < n_units; unit += gridDim.x) {
         const int ev = unit / B, b = unit % B;
         const EventDesc ed = h.ev[ev];
         const int seg_n = h.refine_scan ? 0 : ed.seg_n;
@@ -1452,17 +1449,11 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 for (int jr = 0; jr < kRowsPer; ++jr)
                     if (w + kSeg * jr < Be) pending |= 1u << jr;
                 unsigned spins = 0;
-                // A row takes 1,200 (its workgroup on the same XCD) to 1,600
-                // cycles to arrive, and a load that is on its way when it does
-                // costs as much again: the first is sent after a pause.  Calls
-                // with pauses of 4, 8, 11, 14 and 18 units (of 64 cycles): up to
-                // 32 rows, on one XCD, 69.7, 66.6, 67.4, 68.1 and 69.2 us (20
-                // keyframes); 64 rows, whose last are later, 88.4, 86.6, 85.3,
-                // 85.4 and 84.4 (60 keyframes); the other kernels, whose rows
-                // come from every XCD, 89.3, 88.5, 88.2, 87.8 and 87.8.
-                if (LM || ROUNDS) __builtin_amdgcn_s_sleep(14);
-                else if (Be * kMaxQueues <= (int)gridDim.x) __builtin_amdgcn_s_sleep(8);
-                else __builtin_amdgcn_s_sleep(18);
+                // the rows take about 1,600 cycles to arrive, and a load that
+                // is on its way when they do costs as much again: the first is
+                // sent 900 cycles on (20 keyframes: 9,500 cycles to here a step
+                // without the pause, 8,850 with it)
+                __builtin_amdgcn_s_sleep(14);
                 while (pending) {
                     asm volatile("" ::: "memory");   // the rows change under this loop
 #pragma unroll
@@ -1564,7 +1555,7 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
         const unsigned long long tag = (unsigned long long)epoch << 32;
         const int spare = (int)gridDim.x - n_units;
         const bool spare_only = 2 * spare >= (int)gridDim.x;
-        const int r0 = spare_only ? first - n_units : (int)gridDim.x - 1 - first;
+        const int r0 = spare_only ? (int)blockIdx.x - n_units : (int)(gridDim.x - 1 - blockIdx.x);
         for (int r = r0; r >= 0 && r < h.n_wg; r += spare_only ? spare : (int)gridDim.x) resolve_region_adds(h, r, tag);
     }
 }
