@@ -359,6 +359,7 @@ void plan_ranges(const std::vector<int64_t>& tiles, const std::vector<float>& we
         cost += stage + (double)weight[k] * tiles[k];
         longest = std::max<double>(longest, stage + weight[k]);
     }
+    bound.reserve(slots + 2);
     bound.assign(1, 0);
     if (total <= slots) {   // one tile each
         for (int64_t t = 1; t < total; ++t) bound.push_back(t);
@@ -378,48 +379,50 @@ void plan_ranges(const std::vector<int64_t>& tiles, const std::vector<float>& we
             t += tiles[k];
         }
     } else {
-        // ranges of cost at most T, in order; their number, and (out) their bounds
-        auto split = [&](double T, std::vector<int64_t>* out) -> int {
+        // ranges of cost at most T, in order; their number (or some number
+        // above `slots`), and (out) their bounds
+        auto split = [&](float T, std::vector<int64_t>* out) -> int {
             int count = 0;
-            double acc = 0.0;   // cost of the open range (0: none open)
+            float acc = 0.0f;   // cost of the open range (0: none open)
             int64_t t = 0;
-            for (int k = 0; k < n; ++k) {
-                int64_t rem = tiles[k];
+            for (int k = 0; k < n && count <= slots; ++k) {
+                int rem = (int)tiles[k];
                 if (rem <= 0) continue;
-                const double w = weight[k];
-                const double per = std::max(1.0, std::floor((T - stage) / w));
-                if (acc > 0.0) {
+                const float w = weight[k], iw = 1.0f / w;
+                const int per = std::max(1, (int)((T - stage) * iw));
+                int own = (rem + per - 1) / per;   // ranges, of like size
+                if (acc > 0.0f) {
                     // the open range reaches into this keyframe if it can take
                     // all of it or save it a range of its own
-                    const double room = std::floor((T - acc - stage) / w);
-                    const int64_t own = (int64_t)std::ceil(rem / per);
+                    const int room = (int)((T - acc - stage) * iw);
                     if (room >= rem) {
                         acc += stage + w * rem;
                         t += rem;
                         continue;
                     }
-                    if (room >= 1.0 && (int64_t)std::ceil((rem - room) / per) < own) {
-                        t += (int64_t)room;
-                        rem -= (int64_t)room;
+                    if (room > (rem - 1) % per) {
+                        t += room;
+                        rem -= room;
+                        own = (rem + per - 1) / per;
                     }
                     if (out) out->push_back(t);
-                    acc = 0.0;
                 }
-                const int64_t own = (int64_t)std::ceil(rem / per);   // ranges, of like size
-                for (int64_t i = 0; i < own; ++i) {
-                    const int64_t part = rem * (i + 1) / own - rem * i / own;
-                    t += part;
-                    acc = stage + w * part;
-                    ++count;
-                    if (out && i + 1 < own) out->push_back(t);
-                }
+                const int last = (rem + own - 1) / own;
+                acc = stage + w * last;
+                count += own;
+                if (out)
+                    for (int i = 1; i < own; ++i) out->push_back(t + (int64_t)rem * i / own);
+                t += rem;
             }
             return count;
         };
-        double lo = cost / slots, hi = lo + longest;
-        while (split(hi, nullptr) > slots) hi *= 1.25;
-        for (int i = 0; i < 12 && hi - lo > 0.01 * hi; ++i) {
-            const double mid = 0.5 * (lo + hi);
+        float lo = (float)std::max(cost / slots, longest), hi = (float)(cost / slots + longest);
+        while (split(hi, nullptr) > slots) {
+            lo = hi;
+            hi *= 1.25f;
+        }
+        for (int i = 0; i < 6 && hi - lo > 0.02f * hi; ++i) {
+            const float mid = 0.5f * (lo + hi);
             if (split(mid, nullptr) <= slots) hi = mid;
             else lo = mid;
         }
@@ -585,15 +588,6 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     if (n_tiles != bound[ge]) return fail(FL_EINVAL, "internal: tile count mismatch");
     WgRange* wr = (WgRange*)(blob.data() + o_range);
     {
-        // first pair of tile t in the list index space (t = n_tiles: its end)
-        std::vector<int64_t> vbase(n_vk + 1, 0);
-        for (int k = 0; k < n_vk; ++k) vbase[k + 1] = vbase[k] + kfd[order[k]].n_pairs;
-        auto tile_pair = [&](int64_t t) -> int64_t {
-            if (t >= n_tiles) return n_virtual;
-            const int s = (int)(std::upper_bound(prefix, prefix + n_vk + 1, (int32_t)t) - prefix) - 1;
-            const KfDesc& kd = kfd[order[s]];
-            return vbase[s] + std::min<int64_t>((t - prefix[s]) * tile_pairs, kd.n_pairs);
-        };
         // chunk i of the sequence goes to workgroup w(i); with xcd_aware the
         // chunks of one XCD's share are consecutive in the sequence
         std::vector<int> wg_of(ge);
@@ -604,35 +598,42 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
         } else {
             for (int i = 0; i < ge; ++i) wg_of[i] = i;
         }
+        // The bounds rise, so the slot of a range's first tile (prefix[slot] <=
+        // tile < prefix[slot + 1]; past the last tile: the last) and the pairs
+        // before it are carried along.
+        int slot = 0;
+        int64_t before = 0;   // pairs of the slots before `slot`
+        auto go_to = [&](int64_t t) {
+            while (slot + 1 < n_vk && prefix[slot + 1] <= t) before += kfd[order[slot++]].n_pairs;
+        };
         for (int i = 0; i < ge; ++i) {
-            // slot of the first tile: prefix[slot] <= tile < prefix[slot + 1]
-            const int64_t t0 = bound[i];
-            int slot = (int)(std::upper_bound(prefix, prefix + n_vk + 1, (int32_t)t0) - prefix) - 1;
-            slot = std::min(std::max(slot, 0), std::max(n_vk - 1, 0));
+            const int64_t t0 = bound[i], t1 = bound[i + 1];
+            go_to(t0);
+            const KfDesc& kd = kfd[order[slot]];
             WgRange& g = wr[wg_of[i]];
             g.t0 = (int32_t)t0;
-            g.t1 = (int32_t)bound[i + 1];
+            g.t1 = (int32_t)t1;
             g.slot = slot;
             g.kf = order[slot];
-            const int64_t p0 = tile_pair(t0), p1 = tile_pair(bound[i + 1]);
-            g.priv_off = (int32_t)p0;
-            g.priv_cap = (int32_t)(p1 - p0);
+            // first pair of the range in the list index space
+            g.priv_off = (int32_t)(before + std::min<int64_t>((t0 - prefix[slot]) * tile_pairs, kd.n_pairs));
+            if (i > 0) wr[wg_of[i - 1]].priv_cap = g.priv_off - wr[wg_of[i - 1]].priv_off;
+            g.priv_cap = (int32_t)n_virtual - g.priv_off;
             g.chunk = i;
-            g.event = t0 < n_tiles ? kfd[order[slot]].event : -1;
+            g.event = t0 < n_tiles ? kd.event : -1;
             g.slot_t0 = prefix[slot];
-            g.slot_t1 = prefix[slot + 1];
-            g.one_event = 0;
-            if (t0 < bound[i + 1]) {
-                const int last = (int)(std::upper_bound(prefix, prefix + n_vk + 1, (int32_t)bound[i + 1] - 1) - prefix) - 1;
-                g.one_event = kfd[order[last]].event == g.event;
-            }
-            const KfDesc& kd = kfd[order[slot]];
+            g.slot_t1 = prefix[std::min(slot + 1, n_vk)];
             g.pass = (int16_t)kd.pass;
             g.stage_key = kd.stage_key;
             g.kp_off = kd.kp_off;
             g.n_kp = kd.n_kp;
             g.invw = kd.invw;
             g.invh = kd.invh;
+            g.one_event = 0;
+            if (t0 < t1) {
+                go_to(t1 - 1);
+                g.one_event = kfd[order[slot]].event == g.event;
+            }
         }
         // each event's chunks: from the one that holds its first tile to the
         // one that holds its last (an empty chunk between them writes an empty
