@@ -1809,7 +1809,7 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     // Every iteration enqueues the same kernels: the damping, the decision
     // and whether to relinearise are read from the device state.
     const int edge_grid = std::max(1, (E + kPgoBlock - 1) / kPgoBlock);
-    const int jac_grid = std::max(1, (E + kPgoJacBlock - 1) / kPgoJacBlock);
+    const int jac_grid = std::max(1, (E + kPgoJacEdges - 1) / kPgoJacEdges);
     const int node_grid = std::max(1, (int)((13 * (int64_t)N + kPgoBlock - 1) / kPgoBlock));
     hipLaunchKernelGGL(pgo_edge_cost_kernel, dim3(edge_grid), dim3(kPgoBlock), 0, stream, a, (const double*)a.S);
     hipLaunchKernelGGL(pgo_init_kernel, dim3(1), dim3(kPgoBlock), 0, stream, a, P->lambda);

@@ -15,7 +15,7 @@
 // live in device memory, so the host enqueues the same kernels every
 // iteration and never waits.
 //
-// Per iteration pgo_jacobian_kernel runs one thread per edge (it exits at
+// Per iteration pgo_jacobian_kernel runs two threads per edge (it exits at
 // once after a refusal), then one of three solves writes the candidate:
 //  - direct (the paper's is a direct LDL^T), with the free nodes renumbered
 //    so that every edge spans at most b positions (reverse Cuthill-McKee on
@@ -47,7 +47,8 @@
 namespace fl {
 
 constexpr int kPgoBlock = 256;      // threads of a solve workgroup (one per CU, all co-resident)
-constexpr int kPgoJacBlock = 64;    // threads (edges) of a Jacobian workgroup: one wave, so that a graph fills more CUs
+constexpr int kPgoJacEdges = 64;    // edges of a Jacobian workgroup, each taken by one thread of two waves (J_i and J_j)
+constexpr int kPgoJacBlock = 2 * kPgoJacEdges;
 constexpr int kBandBlock = 512;     // threads of the band assembly and of the one band-solve workgroup
 constexpr int kBandLdsNodes = 12;   // widest band, in keyframes, whose window the LDS holds
 constexpr int kBandMaxW = 7 * kBandLdsNodes;   // widest band row of the LDS-window solve, in scalars
@@ -233,33 +234,39 @@ __device__ inline void jl_inv_adjoint(const double* K11, const double* K21, cons
 }
 
 // One Jacobian (7 x 7 row-major) of edge k, this thread's, into a.J.  The
-// edge-major layout goes through LDS, so that the wave's stores are of
-// consecutive addresses (written by each thread at its own stride they took
-// 23 us against 11 for 3,002 edges).
+// edge-major layout goes through LDS (s_P: the wave's), so that the wave's
+// stores are of consecutive addresses (written by each thread at its own stride
+// they took 23 us against 11 for 3,002 edges).
 __device__ inline void pgo_store_jacobian(const PgoArgs& a, int side, int k, const double* P, double* s_P) {
     double* J = a.J + side * a.J_s;
     if (a.J_q != 1) {
         for (int q = 0; q < 49; ++q) J[q * a.J_q + k * a.J_k] = P[q];
         return;
     }
-    for (int q = 0; q < 49; ++q) s_P[threadIdx.x * 49 + q] = P[q];
+    const int l = wave_lane();
+    for (int q = 0; q < 49; ++q) s_P[l * 49 + q] = P[q];
     // one wave: its LDS accesses are in order; lanes past the last edge are not here
-    const int k0 = blockIdx.x * kPgoJacBlock, n = min(kPgoJacBlock, a.n_edges - k0);
-    for (int i = threadIdx.x; i < n * 49; i += n) J[(k0 + i / 49) * a.J_k + i % 49] = s_P[i];
+    const int k0 = blockIdx.x * kPgoJacEdges, n = min(kPgoJacEdges, a.n_edges - k0);
+    for (int i = l; i < n * 49; i += n) J[(k0 + i / 49) * a.J_k + i % 49] = s_P[i];
 }
 
-// e and the exact J_i, J_j of edge k (one thread per edge); nothing after a
-// refused step (the linearisation at the accepted poses is kept).
+// e and the exact J_i, J_j of each edge; nothing after a refused step (the
+// linearisation at the accepted poses is kept).  A chain of float64 operations,
+// bound by one wave's issue: the first wave of a workgroup makes J_i, the second
+// J_j, both the error and J_l^-1 they share (14.0 us for 3,002 edges; one wave
+// making both took 17.6).
 __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
-    __shared__ double s_P[kPgoJacBlock * 49];
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double s_P[2][kPgoJacEdges * 49];
+    const int side = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int k = blockIdx.x * kPgoJacEdges + wave_lane();
     if (k >= a.n_edges || a.lm[kLmRelin] == 0.0) return;
     const int i = a.edges[2 * k], j = a.edges[2 * k + 1];
     const Sim3d Minv = sim3_inv(sim3_load(a.M + 13 * (int64_t)k));
     const Sim3d Ed = sim3_mul(Minv, sim3_mul(sim3_load(a.S + 13 * (int64_t)j), sim3_inv(sim3_load(a.S + 13 * (int64_t)i))));
     double e[7];
     sim3_log(Ed, e);
-    for (int r = 0; r < 7; ++r) a.e[r * a.e_q + k * a.e_k] = e[r];
+    if (side == 0)
+        for (int r = 0; r < 7; ++r) a.e[r * a.e_q + k * a.e_k] = e[r];
     const LeftJac J = sim3_left_jacobian(e);
     double K11[9], K22[9], K21[9], k23[3], A[9];
     inv33(J.J11, K11);
@@ -269,10 +276,9 @@ __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
     for (int q = 0; q < 9; ++q) K21[q] = -K21[q];
     for (int r = 0; r < 3; ++r) k23[r] = -fma(K22[3 * r], J.j23[0], fma(K22[3 * r + 1], J.j23[1], K22[3 * r + 2] * J.j23[2]));
     double P[49];
-    jl_inv_adjoint(K11, K21, K22, k23, Ed, -1.0, P);   // J_i = -J_l^-1 Ad(E)
-    pgo_store_jacobian(a, 0, k, P, s_P);
-    jl_inv_adjoint(K11, K21, K22, k23, Minv, 1.0, P);  // J_j = J_l^-1 Ad(M^-1)
-    pgo_store_jacobian(a, 1, k, P, s_P);
+    // J_i = -J_l^-1 Ad(E), J_j = J_l^-1 Ad(M^-1)
+    jl_inv_adjoint(K11, K21, K22, k23, side ? Minv : Ed, side ? 1.0 : -1.0, P);
+    pgo_store_jacobian(a, side, k, P, s_P[side]);
 }
 
 // y += J^T v with J's entry 7 r + c at J[(7 r + c) st] and v's entry r at
