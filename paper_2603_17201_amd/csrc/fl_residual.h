@@ -893,32 +893,32 @@ constexpr unsigned kSpinLimit = 1u << 22;
 // and sums took 250: two waves a SIMD issue them for 0.9 us a step instead of
 // 1.3).  INV as in pair_term: A, t are S^-1's, the pair is a point of the
 // current side.
-// No branch: a pair that is not there (has false) or not in front of its
-// keyframe adds zeros.  FIRST: acc is written, not added to.
+// No branch: a pair that is not there (has false) or whose depth is not positive
+// adds zeros, whatever it holds: its residual, point and rows of the Jacobian
+// are selected to zero, since an observation, a pose or an intrinsic that is
+// not finite times a zero weight is not zero.  FIRST: acc is written, not
+// added to.
 template <bool INV, bool FIRST = false>
 __device__ __forceinline__ void refine_pair_f32(const float* A, const float* t, const float* T, float fx, float fy,
                                                 float cx, float cy, float x, float y, float z, float uo, float vo,
                                                 float delta, float* acc, bool has = true) {
-    float p0 = fmaf(A[0], x, fmaf(A[1], y, fmaf(A[2], z, t[0])));
-    float p1 = fmaf(A[3], x, fmaf(A[4], y, fmaf(A[5], z, t[1])));
-    float p2 = fmaf(A[6], x, fmaf(A[7], y, fmaf(A[8], z, t[2])));
-    float q0 = fmaf(T[0], p0, fmaf(T[1], p1, fmaf(T[2], p2, T[9])));
-    float q1 = fmaf(T[3], p0, fmaf(T[4], p1, fmaf(T[5], p2, T[10])));
+    const float p0 = fmaf(A[0], x, fmaf(A[1], y, fmaf(A[2], z, t[0])));
+    const float p1 = fmaf(A[3], x, fmaf(A[4], y, fmaf(A[5], z, t[1])));
+    const float p2 = fmaf(A[6], x, fmaf(A[7], y, fmaf(A[8], z, t[2])));
+    const float q0 = fmaf(T[0], p0, fmaf(T[1], p1, fmaf(T[2], p2, T[9])));
+    const float q1 = fmaf(T[3], p0, fmaf(T[4], p1, fmaf(T[5], p2, T[10])));
     const float q2 = fmaf(T[6], p0, fmaf(T[7], p1, fmaf(T[8], p2, T[11])));
     const bool in = has && q2 > 0.0f;
-    // zeros in place of a point that is not finite, so that its terms are
-    p0 = in ? p0 : 0.0f;
-    p1 = in ? p1 : 0.0f;
-    p2 = in ? p2 : 0.0f;
-    q0 = in ? q0 : 0.0f;
-    q1 = in ? q1 : 0.0f;
-    const float iz = in ? __builtin_amdgcn_rcpf(q2) : 0.0f;   // within 1 ulp
+    const auto keep = [in](float v) { return in ? v : 0.0f; };
+    const float iz = __builtin_amdgcn_rcpf(q2);   // within 1 ulp
     const float a0 = fx * iz, b1 = fy * iz;
-    const float r0 = fmaf(a0, q0, cx) - uo;
-    const float r1 = fmaf(b1, q1, cy) - vo;
+    const float r0 = keep(fmaf(a0, q0, cx) - uo);
+    const float r1 = keep(fmaf(b1, q1, cy) - vo);
     const float e2 = fmaf(r0, r0, r1 * r1);
-    const float w = !in ? 0.0f : e2 <= delta * delta ? 1.0f : delta * __builtin_amdgcn_rsqf(e2);   // within 1 ulp
+    const float w = keep(e2 <= delta * delta ? 1.0f : delta * __builtin_amdgcn_rsqf(e2));   // within 1 ulp
     const float a2 = -a0 * (q0 * iz), b2 = -b1 * (q1 * iz);
+    // the point the perturbation acts on
+    const float x0 = keep(INV ? x : p0), x1 = keep(INV ? y : p1), x2 = keep(INV ? z : p2);
     float J[2][7], W[2][7];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -926,7 +926,6 @@ __device__ __forceinline__ void refine_pair_f32(const float* A, const float* t, 
         float m0 = fmaf(d2, T[6], d0 * T[3 * r]);
         float m1 = fmaf(d2, T[7], d0 * T[3 * r + 1]);
         float m2 = fmaf(d2, T[8], d0 * T[3 * r + 2]);
-        float x0 = p0, x1 = p1, x2 = p2;   // the point the perturbation acts on
         if (INV) {
             const float i0 = -fmaf(m0, A[0], fmaf(m1, A[3], m2 * A[6]));
             const float i1 = -fmaf(m0, A[1], fmaf(m1, A[4], m2 * A[7]));
@@ -934,10 +933,10 @@ __device__ __forceinline__ void refine_pair_f32(const float* A, const float* t, 
             m0 = i0;
             m1 = i1;
             m2 = i2;
-            x0 = in ? x : 0.0f;
-            x1 = in ? y : 0.0f;
-            x2 = in ? z : 0.0f;
         }
+        m0 = keep(m0);
+        m1 = keep(m1);
+        m2 = keep(m2);
         J[r][0] = fmaf(x1, m2, -(x2 * m1));
         J[r][1] = fmaf(x2, m0, -(x0 * m2));
         J[r][2] = fmaf(x0, m1, -(x1 * m0));
@@ -956,7 +955,7 @@ __device__ __forceinline__ void refine_pair_f32(const float* A, const float* t, 
         for (int j = i; j < 7; ++j, ++k)
             acc[k] = fmaf(W[0][i], J[0][j], FIRST ? W[1][i] * J[1][j] : fmaf(W[1][i], J[1][j], acc[k]));
     }
-    const float one = in ? 1.0f : 0.0f;
+    const float one = keep(1.0f);
     acc[35] = FIRST ? one : acc[35] + one;
 }
 

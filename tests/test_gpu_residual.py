@@ -831,3 +831,105 @@ def test_refinement_of_more_pairs_than_the_registers_hold(ctx, lm):
             assert n_gpu[e] == n_ref, (run.__name__, e, n_gpu[e], n_ref)
             err = np.linalg.norm(sim3.log(sim3.compose(S_gpu[e], sim3.inverse(S_ref))))
             assert err < 1e-6, (run.__name__, e, err)
+
+
+NOT_FINITE = [np.nan, np.inf, -np.inf]
+
+
+@pytest.mark.parametrize("bad", NOT_FINITE)
+@pytest.mark.parametrize("what", ["padding", "observation", "pose", "intrinsics"])
+def test_excluded_pairs_of_the_other_direction_add_nothing_whatever_they_hold(ctx, what, bad):
+    """Pairs of the other direction whose depth is not positive, or whose point
+    and observation are both not finite, with a value that is not finite in
+    their observation, keyframe pose or intrinsics: the count and the Sim3 of
+    the launch without them (another order of the float32 sums of a quad at
+    most), in each launch that refines."""
+    import paper_2603_17201_amd as fl
+    ev = synth.gen_c2(seed=213, n_kf=4, n_mp=2000, n_kp=500)
+    xyz, uv, kf, T = synth.gen_inverse_pairs(ev.S_true, 700, seed=9)
+    T = np.asarray(T, np.float32)
+    cam = np.tile(np.array(synth.CAM_752[:4], np.float32), (len(T), 1))
+    # a further keyframe, with every point far behind it
+    extra_T = np.array([[1, 0, 0, 0, 1, 0, 0, 0, 1, 0, 0, -1e6]], np.float32)
+    extra_cam, m = cam[:1].copy(), 70
+    x_bad, u_bad = xyz[:m].copy(), uv[:m].copy()
+    if what == "padding":
+        x_bad[:], u_bad[:] = bad, bad
+        extra_T[0, 6:9] = 0.0   # zero times the point: a depth that is not a number
+    elif what == "observation":
+        u_bad[:] = bad
+    elif what == "pose":
+        extra_T[0, [0, 4, 9, 10]] = bad
+    else:
+        extra_cam[:] = bad
+    n_T = len(T)
+    b = fl.DeviceBatch(ev, device=dev())
+    res = ctx.search_fuse_graph(b, ev.params)
+    out = {}
+    for extra in (False, True):
+        x, u, k = (np.concatenate([xyz, x_bad]), np.concatenate([uv, u_bad]),
+                   np.concatenate([kf, np.full(m, n_T, np.int32)])) if extra else (xyz, uv, kf)
+        inv = fl.InversePairs([0, len(x)], t(x), t(u), t(k.astype(np.int32)), t(np.concatenate([T, extra_T])),
+                              t(np.concatenate([cam, extra_cam])))
+        for mode in ("batched", "graph", "scan"):
+            S = t(ev.S_init.reshape(1, 13).copy())
+            nm = torch.zeros(1, dtype=torch.int32, device=dev())
+            ref = (6, 2.45, S, None, nm, 0, 0.0, 0.0, inv)
+            if mode == "scan":
+                ctx.refine_events(b, res, ref)
+            else:
+                (ctx.search_fuse_batched if mode == "batched" else ctx.search_fuse_graph)(b, ev.params, refine=ref)
+            out[mode, extra] = (S.cpu().numpy()[0], nm.item())
+    for mode in ("batched", "graph", "scan"):
+        (S0, n0), (S1, n1) = out[mode, False], out[mode, True]
+        assert n0 == n1 > 700, (mode, n0, n1)
+        assert not np.array_equal(S0, ev.S_init), mode
+        err = np.linalg.norm(sim3.log(sim3.compose(S1, sim3.inverse(S0))))
+        assert err < 1e-6, (mode, err)
+
+
+@pytest.mark.parametrize("bad", NOT_FINITE)
+@pytest.mark.parametrize("lm", [None, synth.ROBUST_LM_LAMBDA])
+@pytest.mark.parametrize("matched", [False, True])
+def test_keyframe_poses_that_are_not_finite_add_nothing(ctx, matched, lm, bad):
+    """An event whose first keyframe's pose is not finite (every depth not a
+    number or negative, the image rows any of the three): the accepted pairs of
+    the other keyframes alone are refined, whether the first keyframe has some
+    (left out, float64 reference on the rest) or none (threads without a pair
+    read that pose)."""
+    import paper_2603_17201_amd as fl
+    ev = synth.gen_c2(seed=214, n_kf=4, n_mp=3000, n_kp=600)
+    n0 = int(ev.kp_offset[1])
+    if not matched:
+        ev.kp_desc[:n0] ^= np.uint8(0xFF)   # every distance far above the threshold
+    B = synth.concat_events([ev])
+    exp = oracle.search_fuse(B, use_grid=True)
+    xyz, uv, kfl, T32 = _event_pairs(B, exp, 0)
+    assert (np.count_nonzero(kfl == 0) > 100) == matched
+    rest = kfl != 0
+    B.kf_T = np.array(B.kf_T, np.float32)
+    T0 = B.kf_T.reshape(-1, 12)[0]
+    T0[:] = [bad, 0, 0, 0, bad, 0, 0, 0, 1, bad, bad, -np.inf if bad == -np.inf else -1e6]
+    if np.isnan(bad):
+        T0[6:9] = bad
+    it, rounds, tau = synth.ROBUST_ITERS, synth.ROBUST_ROUNDS, synth.ROBUST_OUTLIER_PX
+    if lm is None:
+        S_ref = R.gauss_newton(ev.S_init, xyz[rest], uv[rest], kfl[rest], T32, B.cams[0], 2.45, iters=10)
+        n_ref = int(rest.sum())
+    else:
+        S_ref, n_ref = R.refine_robust(ev.S_init, xyz[rest], uv[rest], kfl[rest], T32, B.cams[0],
+                                       float(np.float32(2.45)), iters=it, rounds=rounds,
+                                       outlier_px=float(np.float32(tau)), lm_lambda=lm)
+    b = fl.DeviceBatch(B, device=dev())
+    res = ctx.search_fuse_graph(b, B.params)
+    for mode in ("batched", "graph", "scan"):
+        S = t(ev.S_init.reshape(1, 13).copy())
+        nm = torch.zeros(1, dtype=torch.int32, device=dev())
+        ref = (10, 2.45, S, None, nm) if lm is None else (it, 2.45, S, None, nm, rounds, tau, lm)
+        if mode == "scan":
+            ctx.refine_events(b, res, ref)
+        else:
+            (ctx.search_fuse_batched if mode == "batched" else ctx.search_fuse_graph)(b, B.params, refine=ref)
+        assert nm.item() == n_ref, (mode, nm.item(), n_ref)
+        err = np.linalg.norm(sim3.log(sim3.compose(S.cpu().numpy()[0], sim3.inverse(S_ref))))
+        assert err < 1e-6, (mode, err)
