@@ -1183,6 +1183,9 @@ __global__ __launch_bounds__(kRefBlock) void refine_kernel(const BatchHdr* __res
                 const int f = i & 15;
                 s_kf[i] = f < 12 ? kd.T[f] : f == 12 ? kd.fx : f == 13 ? kd.fy : f == 14 ? kd.cx : kd.cy;
             }
+            // (threads without a pair read the first entry, which an event
+            // without keyframes does not have)
+            if (n_kf_ev == 0 && tid < 16) s_kf[tid] = 0.0f;
         }
         // two-sided refinement (Gauss-Newton only): the event's pairs of the
         // other direction and their keyframes

@@ -933,3 +933,64 @@ def test_keyframe_poses_that_are_not_finite_add_nothing(ctx, matched, lm, bad):
         assert nm.item() == n_ref, (mode, nm.item(), n_ref)
         err = np.linalg.norm(sim3.log(sim3.compose(S.cpu().numpy()[0], sim3.inverse(S_ref))))
         assert err < 1e-6, (mode, err)
+
+
+def test_events_without_keyframes_are_refined_from_the_other_direction(ctx):
+    """The first, the third and the last of four events have no keyframe and no
+    point, the first and the last some hundred pairs of the other direction
+    (one workgroup, and two): float64 two-sided Gauss-Newton on those; the third
+    is left as it was."""
+    import paper_2603_17201_amd as fl
+    ev = synth.gen_c2(seed=215, n_kf=3, n_mp=2000, n_kp=500)
+    B = synth.concat_events([ev])
+    exp = oracle.search_fuse(B, use_grid=True)
+    fx = _event_pairs(B, exp, 0)
+    B.event_kf_offset = np.array([0, 0, 3, 3, 3], np.int32)
+    B.event_mp_offset = np.array([0, 0, ev.n_mp, ev.n_mp, ev.n_mp], np.int32)
+    sets = [synth.gen_inverse_pairs(ev.S_true, 300, seed=31), None, None, synth.gen_inverse_pairs(ev.S_true, 900, seed=32)]
+    cam_bwd = np.array(list(synth.CAM_752) + [0.0, 0.0], np.float32)
+    inv = _inverse_set(fl, sets, [cam_bwd] * 4)
+    none = tuple(a[:0] for a in fx[:3]) + (fx[3],)
+    refs = [(ev.S_init, 0) if st is None else
+            (R.gauss_newton_bidir(ev.S_init, none, st[:3] + (st[3].astype(np.float64),), cam_bwd, 2.45, iters=10,
+                                  cam_bwd=cam_bwd), len(st[0])) for st in sets]
+    refs[1] = (R.gauss_newton(ev.S_init, *fx, B.cams[0], 2.45, iters=10), len(fx[0]))
+    b = fl.DeviceBatch(B, device=dev())
+    for run in (ctx.search_fuse_batched, ctx.search_fuse_graph):
+        S = t(np.stack([ev.S_init] * 4))
+        nm = torch.zeros(4, dtype=torch.int32, device=dev())
+        got = run(b, B.params, refine=(10, 2.45, S, None, nm, 0, 0.0, 0.0, inv)).numpy()
+        for k in got:
+            assert np.array_equal(got[k], exp[k]), (run.__name__, k)
+        for e, (S_ref, n_ref) in enumerate(refs):
+            assert nm[e].item() == n_ref, (run.__name__, e, nm[e].item(), n_ref)
+            err = np.linalg.norm(sim3.log(sim3.compose(S[e].cpu().numpy(), sim3.inverse(S_ref))))
+            assert err < 1e-6, (run.__name__, e, err)
+
+
+def test_event_without_keyframes_after_one_whose_pose_is_not_a_number(ctx):
+    """257 events: the workgroup of event 0, whose keyframes' poses are not a
+    number, goes on to event 256, which has no keyframe and is refined from the
+    other direction alone; the ones between have neither."""
+    import paper_2603_17201_amd as fl
+    ev = synth.gen_tiny(216, n_kf=2, n_mp=60, n_kp=(20, 30))
+    B = synth.concat_events([ev])
+    B.kf_T = np.full_like(np.asarray(B.kf_T, np.float32), np.nan)
+    n = 257
+    B.event_kf_offset = np.array([0] + [2] * n, np.int32)
+    B.event_mp_offset = np.array([0] + [ev.n_mp] * n, np.int32)
+    st = synth.gen_inverse_pairs(ev.S_true, 300, seed=33)
+    cam = np.array(list(synth.CAM_752) + [0.0, 0.0], np.float32)
+    inv = _inverse_set(fl, [None] * (n - 1) + [st], [cam] * n)
+    none = (np.zeros((0, 3)), np.zeros((0, 2)), np.zeros(0, np.int32), np.zeros((2, 12)))
+    S_ref = R.gauss_newton_bidir(ev.S_init, none, st[:3] + (st[3].astype(np.float64),), cam, 2.45, iters=10, cam_bwd=cam)
+    b = fl.DeviceBatch(B, device=dev())
+    for run in (ctx.search_fuse_batched, ctx.search_fuse_graph):
+        S = t(np.stack([ev.S_init] * n))
+        nm = torch.zeros(n, dtype=torch.int32, device=dev())
+        run(b, B.params, refine=(10, 2.45, S, None, nm, 0, 0.0, 0.0, inv))
+        S = S.cpu().numpy()
+        assert nm.cpu().tolist() == [0] * (n - 1) + [len(st[0])], run.__name__
+        assert all(np.array_equal(S[e], ev.S_init) for e in range(n - 1)), run.__name__
+        err = np.linalg.norm(sim3.log(sim3.compose(S[-1], sim3.inverse(S_ref))))
+        assert err < 1e-6, (run.__name__, err)
