@@ -1202,8 +1202,12 @@ int plain_launch(char* base, const PlainLayout& L, int32_t n_mp, const float* mp
     const PlainPrep prep{kf->kp_owner, (int32_t*)(base + L.o_hash), L.hsize - 1, a.claim, a.counter};
     hipLaunchKernelGGL(plain_prep_kernel, dim3(kf->cell_start ? 1 : 2), dim3(kSingleBlock), 0, stream, a.kd, cells,
                        P->grid_cols, P->grid_rows, kf->kp_xy, cs, ck, prep);
-    const int64_t search_grid = ((int64_t)n_mp * kPlainLanes + kPlainBlock - 1) / kPlainBlock;
-    hipLaunchKernelGGL(search_plain_kernel, dim3((uint32_t)search_grid), dim3(kPlainBlock), 0, stream, a);
+    for (int64_t first = 0; first < n_mp; first += kPlainSlice) {
+        a.first = (int32_t)first;
+        const int64_t lanes = std::min<int64_t>(n_mp - first, kPlainSlice) * kPlainLanes;
+        hipLaunchKernelGGL(search_plain_kernel, dim3((uint32_t)((lanes + kPlainBlock - 1) / kPlainBlock)),
+                           dim3(kPlainBlock), 0, stream, a);
+    }
     const int grid = (n_mp + 255) / 256;
     hipLaunchKernelGGL(resolve_plain_kernel, dim3(std::min(grid, 256)), dim3(256), 0, stream, n_mp,
                        (const uint32_t*)a.counter, (const AddRef*)a.add_list, (int32_t)L.cap,

@@ -1357,6 +1357,7 @@ __global__ __launch_bounds__(kResolveBlock) void resolve_adds_kernel(const Batch
 struct PlainArgs {
     KfDesc kd;
     SearchConst sc;
+    int32_t first;   // the launch's first point
     int32_t n_mp;
     int32_t add_cap;
     const float* mp_xyz;
@@ -1389,6 +1390,7 @@ struct PlainArgs {
 // lane a point.)
 constexpr int kPlainBlock = 256;
 constexpr int kPlainLanes = 8;
+constexpr int kPlainSlice = 1 << 28;   // points a launch takes: one may have up to 2^32 - 1 threads
 
 // a's and b's candidates together: the better best key; of the other key and
 // the two seconds the smallest distance.
@@ -1402,7 +1404,7 @@ __device__ __forceinline__ void merge_best(Best& a, uint32_t key, int second) {
 __global__ __launch_bounds__(kPlainBlock) void search_plain_kernel(PlainArgs a) {
     __shared__ float s_sf[FL_MAX_OCTAVES];
     if (threadIdx.x < FL_MAX_OCTAVES) s_sf[threadIdx.x] = a.sc.sf[threadIdx.x];
-    const int64_t o = ((int64_t)blockIdx.x * kPlainBlock + threadIdx.x) / kPlainLanes;
+    const int64_t o = a.first + ((int64_t)blockIdx.x * kPlainBlock + threadIdx.x) / kPlainLanes;
     const int sub = threadIdx.x % kPlainLanes;
     const bool active = o < a.n_mp;
     const KfDesc& kd = a.kd;

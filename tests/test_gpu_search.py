@@ -397,3 +397,41 @@ def test_plain_search_over_keypoint_counts(ctx, n_kp):
     cs, ck = ctx.build_grid(t(ev.kp_xy), ev.cams[0], P)
     cs_ref, ck_ref = oracle.build_grid(ev.kp_xy, ev.cams[0], P)
     assert np.array_equal(cs.cpu().numpy(), cs_ref) and np.array_equal(ck.cpu().numpy(), ck_ref)
+
+
+def test_plain_search_of_more_points_than_a_launch_has_lanes_for(ctx):
+    """2^29 + 300 points, eight lanes each, are more threads than one launch
+    may have: the event's points at both ends and across the 2^28th and the
+    2^29th, all others behind the keyframe, against the search of those points
+    alone (the claims of one keypoint from both ends among them)."""
+    import paper_2603_17201_amd as fl
+    n = (1 << 29) + 300
+    if torch.cuda.mem_get_info(dev())[0] < 80 << 30:
+        pytest.skip("needs 40 GB of device memory")
+    ev = synth.gen_c2(seed=311, n_kf=1, n_mp=2000, n_kp=800)
+    at = [(0, 500), ((1 << 28) - 250, (1 << 28) + 250), ((1 << 29) - 250, n)]
+    m = sum(b - a for a, b in at)
+    # every point twice, at two of the places
+    pick = np.concatenate([np.arange(m // 2), np.arange(m - m // 2)])
+    x, d = np.ascontiguousarray(ev.mp_xyz[pick]), np.ascontiguousarray(ev.mp_desc[pick])
+    rest = (t(ev.kp_xy), t(ev.kp_oct), t(ev.kp_desc), t(ev.kp_owner), ev.kf_sim3[0], ev.cams[0], ev.params)
+    ids = np.arange(m, dtype=np.int32) + 10 ** 9
+    exp = ctx.search_fuse(t(x), t(d), None, t(ids), *rest).numpy()
+    assert (exp["decision"] == oracle.ADD).sum() > 50
+    # the others behind the keyframe
+    A, c = np.float64(ev.kf_sim3[0][:9]).reshape(3, 3), np.float64(ev.kf_sim3[0][9:12])
+    X = t(np.linalg.solve(A, np.array([0.0, 0.0, -5.0]) - c).astype(np.float32)).repeat(n, 1)
+    D = torch.zeros((n, 32), dtype=torch.uint8, device=dev())
+    I = torch.full((n,), -1, dtype=torch.int32, device=dev())
+    o = 0
+    for a, b in at:
+        X[a:b], D[a:b], I[a:b] = t(x[o:o + b - a]), t(d[o:o + b - a]), t(ids[o:o + b - a])
+        o += b - a
+    out = ctx.search_fuse(X, D, None, I, *rest)
+    none = dict(best_idx=-1, best_dist=0x7FFF, second_dist=0x7FFF, decision=oracle.NOT_VISIBLE, target=-1)
+    for f in FIELDS:
+        got = getattr(out, f)
+        assert np.array_equal(np.concatenate([got[a:b].cpu().numpy() for a, b in at]), exp[f]), f
+        for a, b in at:
+            got[a:b] = none[f]
+        assert bool((got == none[f]).all()), f
