@@ -424,10 +424,10 @@ int fl_gn_step(fl_ctx* ctx, const double* g, const double* H, double lambda, dou
  *    exactly (cg_used = 0; a pivot that is not positive reports -1 and
  *    refuses that iteration's candidate).  FL_PGO_SOLVER_AUTO factors bands
  *    of at most 37 keyframes by block cyclic reduction (a nested-dissection
- *    order) over the whole GPU;
+ *    order) over the whole GPU, with up to 1 GiB of workspace;
  *  - the band solves, one workgroup (wider bands, graphs of fewer than 4 or
- *    more than about 87,000 free keyframes, and FL_PGO_SOLVER_DIRECT[_WIDE]).  A band
- *    of at most 12 keyframes is factored through a window of rows in LDS,
+ *    more than about 87,000 free keyframes, a device without that much free
+ *    memory, and FL_PGO_SOLVER_DIRECT[_WIDE]).  A band of at most 12 keyframes is factored through a window of rows in LDS,
  *    a wider one (several loops, for instance) with the band itself in
  *    device memory as the window; both take the same floating-point steps
  *    in the same order and give identical results where both apply;
@@ -528,6 +528,10 @@ int fl_valu_rate(fl_ctx* ctx, int32_t iters, double* lane_ops_per_s /* host */, 
  * entries (0 restores the default) so that their overflow paths, full scans
  * of the pair outputs, run.  Results are unchanged. */
 int fl_debug_set_list_cap(fl_ctx* ctx, int32_t cap);
+
+/* Test hook: an essential-graph workspace of more than `bytes` cannot be
+ * allocated (0 restores the default, what the device has free). */
+int fl_debug_set_pgo_cap(fl_ctx* ctx, int64_t bytes);
 
 /* Test hooks of the refinement's tagged partial sums (host-only, no GPU
  * needed): the 32-bit tag a launch with device epoch `epoch` gives step

@@ -431,8 +431,8 @@ class Context:
         damping lam; lam = 0: Gauss-Newton): S device float64 [n, 13],
         M device float64 [E, 13], edges host int32 [E, 2], fixed host bool
         [n] or None (node 0 held); solver 0 (direct when the reordered band
-        fits, by block cyclic reduction where the band allows, else conjugate
-        gradients), 1 (conjugate gradients), 2 (the band solve) or 3 (the band
+        fits, by block cyclic reduction where the band and the free memory
+        allow, else conjugate gradients), 1 (conjugate gradients), 2 (the band solve) or 3 (the band
         solve through the device-memory window, which wider bands take
         anyway).  Returns (cost [iters + 1], cg_used [iters], 0 for a
         direct solve) as device tensors, and with history=True also
@@ -543,6 +543,9 @@ class Context:
 
     def debug_set_list_cap(self, cap: int):
         _check(self._lib.fl_debug_set_list_cap(self._h, int(cap)), "fl_debug_set_list_cap")
+
+    def debug_set_pgo_cap(self, n_bytes: int):
+        _check(self._lib.fl_debug_set_pgo_cap(self._h, int(n_bytes)), "fl_debug_set_pgo_cap")
 
 
 def search_fuse_noalloc(mp_xyz, mp_desc, mp_dmax, mp_id, kp_xy, kp_oct, kp_desc, kp_owner, sim3_16, cam8, params,

@@ -52,9 +52,11 @@ struct DevBuf {
     void* p = nullptr;
     size_t size = 0;
     // Grow to at least `need` bytes; a new allocation is filled with `fill`
-    // (-1: left uninitialised).
-    int ensure(size_t need, int fill = -1) {
-        if (need <= size) return FL_OK;
+    // (-1: left uninitialised).  With `cap`, a need beyond it asks for more
+    // than any device has, and fails as on a full one.
+    int ensure(size_t need, int fill = -1, size_t cap = 0) {
+        const bool over = cap && need > cap;
+        if (need <= size && !over) return FL_OK;
         if (p) {
             hipDeviceSynchronize();   // work queued on any stream may still use the old buffer
             hipFree(p);
@@ -62,9 +64,10 @@ struct DevBuf {
         p = nullptr;
         size = 0;
         size_t n = std::max(need, (size_t)1 << 20);
-        n = align_up(n + n / 4, 4096);
+        n = over ? (size_t)1 << 60 : align_up(n + n / 4, 4096);
         if (hipMalloc(&p, n) != hipSuccess) {
             p = nullptr;
+            (void)hipGetLastError();   // reported here, not by the next launch's check
             return fail(FL_ENOMEM, "hipMalloc of %zu bytes failed", n);
         }
         size = n;
@@ -132,6 +135,7 @@ struct fl_ctx {
     Pinned* pin_last = nullptr; // ring buffer of the last eager upload
     int stats = 0;
     int add_cap_override = 0;   // test hook: >0 forces small accepted-pair (and plain-path ADD) list capacities
+    size_t pgo_cap = 0;         // test hook: >0 fails larger pose-graph workspaces
     int prof = 0;               // record events around eager search and refinement kernels
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_ev[2];   // by FL_PROF_* class
     std::vector<hipEvent_t> ev_pool;   // events of read profiles, reused (no event creation per launch)
@@ -1719,39 +1723,50 @@ int fl_pose_graph_optimize(fl_ctx* c, const fl_pose_graph* G, const fl_pgo_param
     const int band_w = 7 * (bw + 1);
     const int64_t band_vs = 7 * (int64_t)nf;
     const size_t tab_bytes = sizeof(int32_t) * tab.size();
-    // The automatic choice takes the block cyclic reduction where its shape
-    // allows; a solver asked for by name is the band solve.
-    CrArgs cr{};
-    const int cr_nt = direct && P->solver == FL_PGO_SOLVER_AUTO ? cr_shape(bw, nf, cr) : 0;
     // co-resident solve workgroups: enough threads for every edge and node,
     // at most one per CU (each grid barrier costs every workgroup a fence)
     const int solve_grid = (int)std::max<int64_t>(
         1, std::min<int64_t>(c->n_cu, (std::max(E, N) + (int64_t)kPgoBlock - 1) / kPgoBlock));
-    size_t off_b = 0;
-    auto take = [&](size_t bytes) {
-        const size_t o = off_b;
-        off_b = align_up(off_b + std::max<size_t>(bytes, 16), 256);
-        return o;
-    };
-    const size_t L_tab = take(tab_bytes);
-    const size_t L_fix = take((size_t)N);
-    const size_t L_e = take(sizeof(double) * 7 * (size_t)E);
-    const size_t L_J = take(sizeof(double) * 98 * (size_t)E);
-    const size_t L_u = take(direct ? 0 : sizeof(double) * 7 * (size_t)E);
-    const size_t L_vec = take(direct ? 0 : sizeof(double) * 6 * 7 * (size_t)N);
-    const size_t L_D = take(direct ? 0 : sizeof(double) * 49 * (size_t)N);
-    const size_t L_bar = take(sizeof(uint32_t));
-    const size_t L_red = take(sizeof(double) * 2 * 4 * (size_t)solve_grid);
-    const size_t L_lm = take(sizeof(double) * kLmWords);
-    const size_t L_Sc = take(sizeof(double) * 13 * (size_t)N);
-    const size_t L_ec = take(sizeof(double) * (size_t)E);
-    const bool band = direct && cr_nt == 0;
-    const size_t L_band = take(band ? sizeof(double) * (size_t)band_vs * band_w : 0);
-    const size_t L_rhs = take(band ? sizeof(double) * (size_t)band_vs : 0);
-    const size_t L_xs = take(band ? sizeof(double) * (size_t)band_vs : 0);
-    const size_t cr_mat = sizeof(double) * (size_t)cr.n_blocks * cr.m * cr.m, cr_vec = sizeof(double) * (size_t)cr.n_blocks * cr.m;
-    const size_t L_cr = take(4 * cr_mat + 2 * cr_vec);
-    int rc = c->pgo.ensure(off_b);
+    // The automatic choice takes the block cyclic reduction where its shape
+    // allows and its blocks, up to 1 GiB, can be allocated (several times what
+    // the band solve needs, which serves the graph otherwise); a solver asked
+    // for by name is the band solve.
+    CrArgs cr{};
+    int cr_nt = direct && P->solver == FL_PGO_SOLVER_AUTO ? cr_shape(bw, nf, cr) : 0;
+    size_t L_tab, L_fix, L_e, L_J, L_u, L_vec, L_D, L_bar, L_red, L_lm, L_Sc, L_ec, L_band, L_rhs, L_xs, L_cr;
+    size_t cr_mat, cr_vec;
+    int rc;
+    for (;;) {
+        size_t off_b = 0;
+        auto take = [&](size_t bytes) {
+            const size_t o = off_b;
+            off_b = align_up(off_b + std::max<size_t>(bytes, 16), 256);
+            return o;
+        };
+        L_tab = take(tab_bytes);
+        L_fix = take((size_t)N);
+        L_e = take(sizeof(double) * 7 * (size_t)E);
+        L_J = take(sizeof(double) * 98 * (size_t)E);
+        L_u = take(direct ? 0 : sizeof(double) * 7 * (size_t)E);
+        L_vec = take(direct ? 0 : sizeof(double) * 6 * 7 * (size_t)N);
+        L_D = take(direct ? 0 : sizeof(double) * 49 * (size_t)N);
+        L_bar = take(sizeof(uint32_t));
+        L_red = take(sizeof(double) * 2 * 4 * (size_t)solve_grid);
+        L_lm = take(sizeof(double) * kLmWords);
+        L_Sc = take(sizeof(double) * 13 * (size_t)N);
+        L_ec = take(sizeof(double) * (size_t)E);
+        const bool band = direct && cr_nt == 0;
+        L_band = take(band ? sizeof(double) * (size_t)band_vs * band_w : 0);
+        L_rhs = take(band ? sizeof(double) * (size_t)band_vs : 0);
+        L_xs = take(band ? sizeof(double) * (size_t)band_vs : 0);
+        cr_mat = sizeof(double) * (size_t)cr.n_blocks * cr.m * cr.m;
+        cr_vec = sizeof(double) * (size_t)cr.n_blocks * cr.m;
+        L_cr = take(4 * cr_mat + 2 * cr_vec);
+        rc = c->pgo.ensure(off_b, -1, c->pgo_cap);
+        if (rc != FL_ENOMEM || cr_nt == 0) break;
+        cr_nt = 0;
+        cr = CrArgs{};
+    }
     if (rc) return rc;
     char* base = (char*)c->pgo.p;
     // tables and fixed flags through the pinned ring (node 0 held when no flags are given)
@@ -2070,6 +2085,12 @@ int fl_debug_refine_rows_cleared(uint32_t launches) { return refine_rows_cleared
 int fl_debug_set_list_cap(fl_ctx* c, int32_t cap) {
     if (!c || cap < 0) return fail(FL_EINVAL, "bad argument");
     c->add_cap_override = cap;
+    return FL_OK;
+}
+
+int fl_debug_set_pgo_cap(fl_ctx* c, int64_t bytes) {
+    if (!c || bytes < 0) return fail(FL_EINVAL, "bad argument");
+    c->pgo_cap = (size_t)bytes;
     return FL_OK;
 }
 

@@ -310,3 +310,27 @@ def test_cyclic_reduction_reports_a_failed_pivot(ctx):
         S, _, used, _, acc = _run(ctx, d, iters=1, solver=solver)
         assert list(used) == [-1] and list(acc) == [0]
         assert np.array_equal(S, d["S0"])
+
+
+def test_band_solve_when_the_blocks_cannot_be_allocated(ctx):
+    """1,000 keyframes on one lap need 12 MB for the reduction's blocks and 3 MB
+    for the band, beside 3 MB for both: with 12 MB to be had the automatic
+    choice is the band solve, to the bit; with 4 MB there is none; afterwards
+    the reduction again, to the bit what it was."""
+    import paper_2603_17201_amd as fl
+    from paper_2603_17201_amd import _abi
+    d = synth.gen_pose_graph(n=1000, seed=41)
+    auto, band = _run(ctx, d, iters=2), _run(ctx, d, iters=2, solver=DIRECT)
+    assert _err(auto[0], band[0]) < 1e-9 and not np.array_equal(auto[0], band[0])
+    try:
+        ctx.debug_set_pgo_cap(12 << 20)
+        for a, b in zip(_run(ctx, d, iters=2), band):
+            assert np.array_equal(a, b)
+        ctx.debug_set_pgo_cap(4 << 20)
+        with pytest.raises(fl.FlError) as e:
+            _run(ctx, d, iters=2)
+        assert e.value.code == _abi.FL_ENOMEM
+    finally:
+        ctx.debug_set_pgo_cap(0)
+    for a, b in zip(_run(ctx, d, iters=2), auto):
+        assert np.array_equal(a, b)
