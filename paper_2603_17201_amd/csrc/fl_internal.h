@@ -342,6 +342,15 @@ __host__ __device__ constexpr bool refine_rows_cleared_before(uint32_t launches)
 
 __device__ __forceinline__ int wave_lane() { return threadIdx.x & (kWave - 1); }
 
+// Between a wave's LDS stores and its lanes' loads of each other's values (or
+// such loads and the next stores): one wave's LDS accesses complete in order,
+// so no instruction is needed, but the compiler must keep theirs, which it
+// otherwise only does while it cannot tell the addresses apart.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Global-memory accesses through the global address space: the compiler
 // then issues global (not flat) loads and stores, with a scalar base where
 // it can.

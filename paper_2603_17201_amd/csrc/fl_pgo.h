@@ -245,7 +245,7 @@ __device__ inline void pgo_store_jacobian(const PgoArgs& a, int side, int k, con
     }
     const int l = wave_lane();
     for (int q = 0; q < 49; ++q) s_P[l * 49 + q] = P[q];
-    // one wave: its LDS accesses are in order; lanes past the last edge are not here
+    wave_lds_sync();   // lanes past the last edge are not here
     const int k0 = blockIdx.x * kPgoJacEdges, n = min(kPgoJacEdges, a.n_edges - k0);
     for (int i = l; i < n * 49; i += n) J[(k0 + i / 49) * a.J_k + i % 49] = s_P[i];
 }

@@ -97,6 +97,7 @@ __device__ __forceinline__ bool cr_factor_tile(v4d c, double* sD, double* sX, do
             sD[(lr + 4 * r) * 17 + lc] = c[r];
             sX[(lr + 4 * r) * 17 + lc] = X[r];
         }
+        wave_lds_sync();
         const double* a = sD + 4 * s * 18;   // the diagonal block, rows of 17
         double d[4], x[4];
 #pragma unroll
@@ -127,6 +128,7 @@ __device__ __forceinline__ bool cr_factor_tile(v4d c, double* sD, double* sX, do
         if (s < 3) {
             c = __builtin_amdgcn_mfma_f64_16x16x4f64(-P, P, c, 0, 0, 0);
             X = __builtin_amdgcn_mfma_f64_16x16x4f64(-Q, P, X, 0, 0, 0);
+            wave_lds_sync();
         }
     }
     return ok;
@@ -239,10 +241,12 @@ __global__ __launch_bounds__(kCrWaves * 64) void cr_eliminate_kernel(CrArgs a, i
     // a panel tile times L_kk^-T: through LDS into the left operand's layout
     auto panel = [&](const v4d& v, double* t, const double* Mk) {
         put(t, v);
+        wave_lds_sync();
         v4d c = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk)
             c = __builtin_amdgcn_mfma_f64_16x16x4f64(t[oa + 4 * kk], Mk[op + 4 * 17 * kk], c, 0, 0, 0);
+        wave_lds_sync();
         put(t, c);
         return c;
     };
@@ -278,6 +282,7 @@ __global__ __launch_bounds__(kCrWaves * 64) void cr_eliminate_kernel(CrArgs a, i
                 if (kd == 3) {
                     if (lr == 0) a.b[mb * M + 16 * k + lc] = c[0];
                 } else if (kd == 2) {   // transposed
+                    wave_lds_sync();
                     double* d = a.LI + mb * MM + 16 * k * M + 16 * row;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) d[og + 4 * r * M] = sP[i * kCrTile + oa + 4 * r];
