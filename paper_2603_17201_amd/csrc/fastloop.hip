@@ -722,8 +722,6 @@ int prepare_batch(fl_ctx* c, const fl_batch* B, const fl_params* P, const fl_fus
     h.n_mp = B->n_mp;
     h.n_kp_total = B->n_kp_total;
     h.n_pairs = B->n_pairs;
-    h.n_tiles = (int32_t)n_tiles;
-    h.tile_pairs = (int32_t)tile_pairs;
     h.cells = cells;
     h.grid_cols = P->grid_cols;
     h.grid_rows = P->grid_rows;

@@ -151,13 +151,11 @@ enum : int { kModeGlobal = 0, kModeLdsRec = 1, kModeLdsDesc = 2 };
 struct alignas(16) BatchHdr {
     int32_t n_events, n_kf, n_mp, n_kp_total;
     int64_t n_pairs;
-    int32_t n_tiles, tile_pairs; // tiles of the batch; pairs per tile (one wave's chunk)
     int32_t cells, grid_cols, grid_rows, n_octaves;
     int32_t n_pass;             // search passes of the launch (1 .. FL_MAX_PASSES)
     int32_t gate;               // 1: point distance invariance given (octave gate on)
     int32_t dense;
     int32_t stats;              // 1: count visible / cells / keypoints / candidates
-    uint32_t pad_epoch;
     int32_t lds_hash_mask;      // owner hash capacity - 1 in the LDS modes
     int32_t n_wg;               // workgroups of the search launch
     int32_t refine_iters;       // evaluations per round
@@ -310,19 +308,6 @@ struct Best {
 
 __device__ __forceinline__ uint32_t hash_id(int32_t id) {
     return (uint32_t)id * 0x9E3779B1u;
-}
-
-// Is `id` among the owners stored in a keyframe's open-addressing table?
-__device__ __forceinline__ bool owner_lookup(const int32_t* __restrict__ table, int32_t mask, int32_t id) {
-    if (id < 0) return false;
-    uint32_t h = (hash_id(id) >> 7) & (uint32_t)mask;
-    for (int probe = 0; probe <= mask; ++probe) {
-        const int32_t v = table[h];
-        if (v == id) return true;
-        if (v < 0) return false;
-        h = (h + 1) & (uint32_t)mask;
-    }
-    return false;
 }
 
 // Tag of the refinement's partial-sum words: the low kTagEpochBits bits of

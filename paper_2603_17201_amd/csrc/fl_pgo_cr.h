@@ -49,7 +49,7 @@ struct CrArgs {
     double* LI;         // [N][m][m] L^-1 of an eliminated block (the transpose of L^-T)
     double* b;          // [N][m] right-hand sides, then y
     double* x;          // [N][m]
-    double* lm;         // Levenberg-Marquardt state (kLmFail, kLmUsed)
+    double* lm;         // Levenberg-Marquardt state (kLmFail; kLmUsed stays the 0 it is set to at the start)
 };
 
 constexpr int kCrWaves = 8;            // waves of an elimination workgroup
@@ -317,7 +317,6 @@ __global__ __launch_bounds__(kCrWaves * 64) void cr_eliminate_kernel(CrArgs a, i
         __syncthreads();
     }
     if (!ok && l == 0) a.lm[kLmFail] = 1.0;
-    if (last && grp == 0 && threadIdx.x == 0) a.lm[kLmUsed] = 0.0;
 }
 
 // Sum over k of P_i[row][k] P_j[col][k] for 16 x 16 entries, P_i and P_j 16

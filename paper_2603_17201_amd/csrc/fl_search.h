@@ -576,7 +576,6 @@ struct KfView {
     const KpRec* rec;
     const uint4* desc;          // cell-ordered descriptors (LDS or workspace), or null
     const uint8_t* desc_orig;   // keypoint descriptors by original index (when desc is null)
-    const int32_t* own;         // unused: the owner of the best keypoint is read from kp_owner
     const int32_t* hash;
     int32_t hash_mask;
     int32_t n_rec;              // records (slots) in rec
@@ -818,12 +817,6 @@ __device__ __forceinline__ bool search_front(const KfDesc& kd, const KfView& v, 
         }
     }
     return true;
-}
-
-__device__ __forceinline__ int scan_slot(const PairScan& q, int m) {
-    // masks, not a chain of selects, which the compiler would turn into a
-    // table in scratch memory
-    return m + q.b0 + (q.d1 & -(int)(m >= q.c1)) + (q.d2 & -(int)(m >= q.c2)) + (q.d3 & -(int)(m >= q.c3));
 }
 
 // Descriptor of record slot i (keypoint index idx).
@@ -1200,7 +1193,6 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
             v.n_rec = max(kd.n_kp, 1);
             v.desc = h.desc_sorted + 2 * (int64_t)kd.kp_off;
             v.desc_orig = nullptr;
-            v.own = nullptr;
             v.hash = h.hash + kd.hash_off;
             v.hash_mask = kd.hash_mask;
         } else {
@@ -1215,7 +1207,6 @@ __global__ __launch_bounds__(kSearchBlock) void search_fused_kernel(const BatchH
             v.n_rec = search_slots(kp_cap, nb);
             v.desc = MODE == kModeLdsDesc ? s_desc : nullptr;
             v.desc_orig = nullptr;   // read where it is used
-            v.own = nullptr;
             v.hash = s_hash;
             v.hash_mask = hmask;
         }
