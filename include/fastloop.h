@@ -533,6 +533,14 @@ int fl_debug_set_list_cap(fl_ctx* ctx, int32_t cap);
  * allocated (0 restores the default, what the device has free). */
 int fl_debug_set_pgo_cap(fl_ctx* ctx, int64_t bytes);
 
+/* Test hook (host-only, no GPU needed): the split of n keyframes' tiles into
+ * at most `slots` contiguous ranges, as a batched search plans it: tiles [n]
+ * of each keyframe, weight [n] of one of its tiles, the cost `stage` of
+ * staging a keyframe.  bound [slots + 1] receives the first tile of each range
+ * and the number of tiles; the number of ranges is returned. */
+int fl_debug_plan_ranges(int32_t n, const int64_t* tiles, const float* weight, float stage, int32_t slots,
+                         int64_t* bound);
+
 /* Test hooks of the refinement's tagged partial sums (host-only, no GPU
  * needed): the 32-bit tag a launch with device epoch `epoch` gives step
  * `step` (0 <= step < 1000; the epoch is decremented by every table fetch,

@@ -148,6 +148,7 @@ SIGNATURES = [
     ("fl_valu_rate", c_int32, [c_void_p, c_int32, ctypes.POINTER(c_double), c_void_p]),
     ("fl_debug_set_list_cap", c_int32, [c_void_p, c_int32]),
     ("fl_debug_set_pgo_cap", c_int32, [c_void_p, c_int64]),
+    ("fl_debug_plan_ranges", c_int32, [c_int32, c_void_p, c_void_p, c_float, c_int32, c_void_p]),
     ("fl_debug_refine_tag", ctypes.c_uint32, [ctypes.c_uint32, c_int32]),
     ("fl_debug_refine_rows_cleared", c_int32, [ctypes.c_uint32]),
 ]

@@ -2086,6 +2086,16 @@ int fl_debug_set_list_cap(fl_ctx* c, int32_t cap) {
     return FL_OK;
 }
 
+int fl_debug_plan_ranges(int32_t n, const int64_t* tiles, const float* weight, float stage, int32_t slots,
+                         int64_t* bound) {
+    if (n < 0 || slots < 1 || (n > 0 && (!tiles || !weight)) || !bound) return fail(FL_EINVAL, "bad argument");
+    std::vector<int64_t> b;
+    plan_ranges(std::vector<int64_t>(tiles, tiles + n), std::vector<float>(weight, weight + n), stage, slots, b);
+    if ((int64_t)b.size() > (int64_t)slots + 1) return fail(FL_ERANGE, "%zu ranges for %d slots", b.size() - 1, slots);
+    std::copy(b.begin(), b.end(), bound);
+    return (int)b.size() - 1;
+}
+
 int fl_debug_set_pgo_cap(fl_ctx* c, int64_t bytes) {
     if (!c || bytes < 0) return fail(FL_EINVAL, "bad argument");
     c->pgo_cap = (size_t)bytes;

@@ -208,3 +208,63 @@ def test_noalloc_search_rejects_what_its_scratch_cannot_hold(lib):
     rc = lib.fl_search_fuse_noalloc(10, fake, fake, None, None, ctypes.byref(kf), ctypes.byref(S), ctypes.byref(K),
                                     ctypes.byref(P), ctypes.byref(o), None)
     assert rc == _abi.FL_EINVAL
+
+
+def _plan(lib, tiles, weight, stage, slots):
+    t = np.asarray(tiles, np.int64)
+    w = np.asarray(weight, np.float32)
+    bound = np.full(slots + 1, -1, np.int64)
+    n = lib.fl_debug_plan_ranges(len(t), t.ctypes.data, w.ctypes.data, stage, slots, bound.ctypes.data)
+    assert 1 <= n <= slots, (n, fl.last_error())
+    return bound[:n + 1]
+
+
+def _range_costs(bound, tiles, weight, stage):
+    """Cost of each range: its tiles' weights, and `stage` for each keyframe it has tiles of."""
+    first = np.concatenate([[0], np.cumsum(tiles)])
+    lo = np.maximum(bound[:-1, None], first[None, :-1])
+    hi = np.minimum(bound[1:, None], first[None, 1:])
+    share = np.maximum(hi - lo, 0)
+    return (share * np.asarray(weight)[None, :]).sum(1) + stage * (share > 0).sum(1)
+
+
+def test_ranges_of_a_plan_cover_the_tiles_and_share_their_cost(lib):
+    # No keyframe, keyframes without tiles, one tile a slot, as many keyframes
+    # as slots and more, few and many tiles a slot, one dense keyframe among
+    # sparse ones.  Every tile is in one range and the ranges rise.  Where the
+    # longest range is minimised (no more keyframes than slots, at most 64
+    # tiles a slot), it is at most the even share and the dearest keyframe's
+    # staging and tile, or the 1.25 times that which is tried next.  Otherwise
+    # a range costs at most one tile and the staging of the keyframe it begins
+    # in more than the even share.
+    stage = 36.0
+    rng = np.random.default_rng(5)
+    cases = [([], [], 256), ([0, 0], [2, 2], 256), ([1], [1.8], 256), ([256], [1.8], 256), ([257], [1.8], 256),
+             ([5] * 256, [1.8] * 256, 256), ([5] * 257, [1.8] * 257, 256), ([3, 0, 70000, 2], [1.8, 9, 1.8, 40.0], 512),
+             ([16384], [1.8], 256), ([16385], [1.8], 256), ([235] * 20, [1.8] * 20, 256), ([1] * 3, [1e3, 1, 1], 2),
+             ([7], [1.8], 1), ([0, 7, 3], [1.8] * 3, 1)]
+    for _ in range(400):
+        n = int(rng.integers(1, 400))
+        tiles = np.floor(np.exp(rng.uniform(0, rng.uniform(1, 8), n))).astype(np.int64) * (rng.random(n) > 0.1)
+        cases.append((tiles, 1 + rng.exponential(2.0, n).astype(np.float32) * rng.choice([1, 10], n, p=[0.95, 0.05]),
+                      int(rng.choice([1, 2, 7, 64, 256, 512]))))
+    for tiles, weight, slots in cases:
+        tiles = np.asarray(tiles, np.int64)
+        weight = np.asarray(weight, np.float32).astype(np.float64)
+        b = _plan(lib, tiles, weight, stage, slots)
+        total, used = int(tiles.sum()), int((tiles > 0).sum())
+        what = (used, total, slots)
+        assert b[0] == 0 and b[-1] == total and np.all(np.diff(b) >= 0), what
+        if total == 0:
+            assert len(b) == 2, what
+            continue
+        if total <= slots:
+            assert len(b) == total + 1 and np.all(np.diff(b) == 1), what
+            continue
+        cost = _range_costs(b, tiles, weight, stage)
+        even = (stage * used + (tiles * weight).sum()) / slots
+        top = stage + weight[tiles > 0].max()
+        if used > slots or total > 64 * slots:
+            assert cost.max() <= even * (1 + 1e-5) + top, what
+        else:
+            assert np.all(np.diff(b) > 0) and cost.max() <= 1.25 * (even + top) * (1 + 1e-5), what

@@ -435,3 +435,29 @@ def test_plain_search_of_more_points_than_a_launch_has_lanes_for(ctx):
         for a, b in at:
             got[a:b] = none[f]
         assert bool((got == none[f]).all()), f
+
+
+def test_claimed_and_helped_tiles_of_several_events_and_passes(ctx):
+    # 27,000 tiles of four events over 256 workgroups: ranges long enough that
+    # their second half is claimed, some within one event (others help with
+    # them) and some across two or three; eager with refinement, and in two
+    # passes (twice the tiles), the second with windows of several rows
+    import paper_2603_17201_amd as fl
+    B = synth.concat_events([synth.gen_c2(seed=231, n_kf=2, n_mp=400), synth.gen_c2(seed=232, n_kf=5, n_mp=200000),
+                             synth.gen_c2(seed=233, n_kf=3, n_mp=2000), synth.gen_c2(seed=234, n_kf=4, n_mp=180000)])
+    exp = oracle.search_fuse(B, use_grid=True)
+    accepted = np.isin(exp["decision"], (oracle.ADD, oracle.FUSE))
+    n_ref = [int(accepted[int(B.pair_offset[a]):int(B.pair_offset[z])].sum())
+             for a, z in zip(B.event_kf_offset[:-1], B.event_kf_offset[1:])]
+    b = fl.DeviceBatch(B, device=dev())
+    assert b.n_pairs / 64 / 256 > 96
+    for run in (ctx.search_fuse_batched, ctx.search_fuse_graph):
+        S = t(np.stack([e.S_init for e in B.events]))
+        nm = torch.zeros(4, dtype=torch.int32, device=dev())
+        assert_same(run(b, B.params, refine=(1, 2.45, S, None, nm)).numpy(), exp, run.__name__)
+        assert nm.cpu().tolist() == n_ref, run.__name__
+    P2 = synth.verification_params()
+    exp2 = oracle.search_fuse(B, params=P2, use_grid=True)
+    outs = ctx.search_fuse_passes(b, [(B.params, None, None), (P2, None, None)])
+    for o, e in zip(outs, (exp, exp2)):
+        assert_same(o.numpy(), e, "passes")
