@@ -541,8 +541,9 @@ class Bench:
     def essential_graph(self, steps):
         """Essential-graph optimisation of a loop of 1,000 keyframes (about
         3,000 odometry, covisibility and loop edges) from its drifted start:
-        10 outer steps, each solved directly (banded Cholesky under a reverse
-        Cuthill-McKee order) and, for comparison, by block-Jacobi conjugate
+        10 outer steps, each solved as the library chooses (block cyclic
+        reduction under a reverse Cuthill-McKee order) and, for comparison, by
+        the one-workgroup banded Cholesky and by block-Jacobi conjugate
         gradients (at most 500 iterations, to 1e-10)."""
         import synth
         torch, fl, ctx = self.torch, self.fl, self.ctx
@@ -556,7 +557,8 @@ class Bench:
             return dict(deg=max(x[0] for x in e), m=max(x[1] for x in e), log_scale=max(x[2] for x in e))
         res = dict(n_nodes=int(S.shape[0]), n_edges=int(d["edges"].shape[0]), iters=10,
                    worst_node_error_start=worst(d["S0"]))
-        for name, solver in (("direct", fl._abi.PGO_SOLVER_DIRECT), ("conjugate_gradients", fl._abi.PGO_SOLVER_CG)):
+        for name, solver in (("automatic", fl._abi.PGO_SOLVER_AUTO), ("direct", fl._abi.PGO_SOLVER_DIRECT),
+                             ("conjugate_gradients", fl._abi.PGO_SOLVER_CG)):
             out = {}
 
             def run():
@@ -579,12 +581,12 @@ class Bench:
     def pose_graph_by_size(self, steps, graphs=((100, 1), (250, 1), (500, 1), (1000, 1), (2000, 1), (1000, 2),
                                                 (1000, 3), (1000, 4))):
         """One Levenberg-Marquardt step of the essential graph on the device
-        (edge Jacobians, banded assembly, direct solve, candidate cost) across
-        graph sizes (n keyframes, laps of the trajectory: one loop, or
-        several whose keyframes are joined to the lap before, 3 each), beside
-        the CPU baseline of the linear solve alone: the same damped system,
-        assembled on the host from the oracle's edge Jacobians (untimed),
-        solved by LAPACK's banded Cholesky under a reverse Cuthill-McKee order
+        (edge Jacobians, assembly, direct solve, as the library chooses and by
+        the band solve, candidate cost) across graph sizes (n keyframes, laps
+        of the trajectory: one loop, or several whose keyframes are joined to
+        the lap before, 3 each), beside the CPU baseline of the linear solve
+        alone: the same damped system, assembled on the host from the
+        oracle's edge Jacobians (untimed), solved by LAPACK's banded Cholesky under a reverse Cuthill-McKee order
         and by SuperLU on the sparse matrix."""
         import synth
         import scipy.linalg
@@ -602,9 +604,12 @@ class Bench:
 
             def step():
                 S.copy_(S0)
-                ctx.pose_graph_optimize(S, M, d["edges"], None, iters=1, solver=fl._abi.PGO_SOLVER_DIRECT)
+                ctx.pose_graph_optimize(S, M, d["edges"], None, iters=1, solver=solver)
             gc.collect()
             gc.disable()
+            solver = fl._abi.PGO_SOLVER_AUTO
+            auto_ms = self.events_time(step, max(3, steps // 3), 2)
+            solver = fl._abi.PGO_SOLVER_DIRECT
             dev_ms = self.events_time(step, max(3, steps // 3), 2)
             gc.enable()
             # the host system at the start poses, node 0 held
@@ -648,12 +653,14 @@ class Bench:
             Hc = H.tocsc()
             lu_ms = t_ms(lambda: scipy.sparse.linalg.spsolve(Hc, -g))
             out.append(dict(n_keyframes=n, laps=laps, n_edges=int(d["edges"].shape[0]), unknowns=N, band_width=w,
-                            device_lm_step_ms=dev_ms, cpu_banded_cholesky_solve_ms=chol_ms,
-                            cpu_sparse_lu_solve_ms=lu_ms))
-            log(f"essential graph, {n} keyframes, {laps} lap(s): device LM step {dev_ms:.3f} ms; CPU solve alone: banded "
-                f"Cholesky {chol_ms:.3f} ms, sparse LU {lu_ms:.3f} ms (band {w} of {N} unknowns)")
-        return dict(note="device: one whole Levenberg-Marquardt step (Jacobians, assembly, banded solve, candidate "
-                         "cost); CPU: the linear solve alone in the benchmark process (LAPACK and SuperLU "
+                            device_lm_step_ms=dev_ms, device_lm_step_automatic_ms=auto_ms,
+                            cpu_banded_cholesky_solve_ms=chol_ms, cpu_sparse_lu_solve_ms=lu_ms))
+            log(f"essential graph, {n} keyframes, {laps} lap(s): device LM step {auto_ms:.3f} ms as the library "
+                f"chooses, {dev_ms:.3f} ms by band solve; CPU solve alone: banded Cholesky {chol_ms:.3f} ms, sparse LU "
+                f"{lu_ms:.3f} ms (band {w} of {N} unknowns)")
+        return dict(note="device: one whole Levenberg-Marquardt step (Jacobians, assembly, solve, candidate cost; "
+                         "device_lm_step_ms by the band solve, device_lm_step_automatic_ms as the library "
+                         "chooses); CPU: the linear solve alone in the benchmark process (LAPACK and SuperLU "
                          "with the process's BLAS threads), assembly excluded", sizes=out)
 
     def residual(self):

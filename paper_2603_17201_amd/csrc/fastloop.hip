@@ -1563,10 +1563,11 @@ namespace {
 // whose edges span at most bw band positions: 16 x 16 tiles a side of a
 // block, 0: the band solves.  Ten iterations, band solve against cyclic
 // reduction: 2 free keyframes 344 / 384 us, 4: 507 / 431, 59 (bands of 4, 13,
-// 18 keyframes) 3.0 / 1.2, 7.4 / 2.8, 6.7 / 2.2 ms, 999 36.5 / 2.3 ms (band
-// of 7) and 97 / 6.7 ms (band of 24).  Blocks of more than 36 keyframes would
-// not fit the registers, and graphs beyond kCrMaxEntries (87,000 keyframes at
-// a band of 7) would take over 1 GiB of workspace.
+// 18 keyframes) 3.0 / 1.2, 7.4 / 2.8, 6.7 / 2.2 ms, 299 (bands of 34 and 37,
+// whose blocks of 36 the registers no longer hold whole) 48 / 9.0 and 54 / 8.7
+// ms, 999 36.5 / 2.2 ms (band of 7) and 97 / 6.6 ms (band of 24).  Wider blocks
+// would spill most of their tiles, and graphs beyond kCrMaxEntries (87,000
+// keyframes at a band of 7) would take over 1 GiB of workspace.
 int cr_shape(int bw, int nf, CrArgs& cr) {
     if (nf < 4) return 0;
     for (const int nt : {3, 4, 6, 8, 11, 14, 16}) {

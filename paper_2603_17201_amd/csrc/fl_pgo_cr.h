@@ -62,8 +62,10 @@ constexpr int64_t kCrMaxEntries = 1 << 25;   // entries of one of the four block
 // Tile rows of [Y_l; Y_r; I; b] a workgroup carries beside the triangle of
 // A_mm, which every workgroup of a block factors for itself (that costs no
 // time, the triangle's chain is the same in all, and no exchange is needed).
-// Every tile lives in registers for the whole elimination: with 8 waves a
-// thread holds (NT (NT + 1) / 2 + XR NT) / 8 tiles of 4 doubles.
+// A wave keeps its tiles in registers for the whole elimination: with 8 waves a
+// thread holds (NT (NT + 1) / 2 + XR NT) / 8 tiles of 4 doubles, which fills
+// the 256 registers at NT = 11.  Of the two widest shapes the compiler spills
+// 6 (NT = 14) and 93 of them (NT = 16).
 constexpr int cr_rows(int nt) { return nt >= 14 ? 2 : nt >= 11 ? 4 : 5; }
 constexpr int cr_groups(int nt) { return (3 * nt + 1 + cr_rows(nt) - 1) / cr_rows(nt); }
 
@@ -82,8 +84,9 @@ __device__ __forceinline__ double cr_rsqrt(double d) {
 // which is both operands' layout of the one matrix instruction that updates
 // the rest.  Identity rows taken along come out as the rows of L^-T, in sM.
 // (4,000 to 5,000 cycles a tile; column by column, with the values passed
-// between lanes by readlane, it took 5,000 to 14,000, two thirds of a step.)  Entries above the diagonal
-// are never used.  Returns whether every pivot was positive.
+// between lanes by readlane, it took 5,000 to 14,000, two thirds of a step.)
+// Entries above the diagonal are never used.  Returns whether every pivot was
+// positive.
 __device__ __forceinline__ bool cr_factor_tile(v4d c, double* sD, double* sX, double* sM) {
     const int l = wave_lane(), lr = l >> 4, lc = l & 15;
     v4d X;

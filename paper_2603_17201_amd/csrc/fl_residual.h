@@ -889,10 +889,13 @@ constexpr unsigned kSpinLimit = 1u << 22;
 // acc when the pair is in front of its keyframe: acc[0..6] w J^T r, acc[7..34]
 // w J^T J (upper, row by row), acc[35] the pairs added.  The arithmetic of
 // pair_term with fused multiply-adds throughout, the weight from the squared
-// error and w J formed once (150 instructions a pair where separate products
-// and sums took 250: two waves a SIMD issue them for 0.9 us a step instead of
-// 1.3).  INV as in pair_term: A, t are S^-1's, the pair is a point of the
-// current side.
+// error and w J formed once (some 150 instructions a pair where separate
+// products and sums took 250: two waves a SIMD issue them for 0.9 us a step
+// instead of 1.3).  Both round at the size of the observation, which bounds the
+// result: against float64 refinements of the same pairs the pose is off by 1.8
+// to 3.0e-8 (relative, geometric means of 15 to 60 inputs of six kinds of
+// event), with separate products it was by 1.9 to 3.3e-8.  INV as in
+// pair_term: A, t are S^-1's, the pair is a point of the current side.
 // No branch: a pair that is not there (has false) or whose depth is not positive
 // adds zeros, whatever it holds: its residual, point and rows of the Jacobian
 // are selected to zero, since an observation, a pose or an intrinsic that is

@@ -555,10 +555,13 @@ __device__ __forceinline__ void wave_append(bool want, uint32_t* counter, T* lis
 // at the end of every workgroup).  The ADD conflicts are resolved by the next
 // kernel on the stream.
 //
-// Bound: vector instructions, about 400 for a tile of 64 pairs with two scan
-// steps, at four waves a SIMD.  The tables' uniform values are therefore read
-// by scalar loads where they are used (kept across a tile they took 75
-// vector instructions a tile to bring back from spilled lanes).
+// Bound: instruction issue and LDS latency at four waves a SIMD.  A tile of 64
+// pairs with two scan steps takes about 400 vector and 40 LDS instructions; the
+// vector ones keep a SIMD busy for 63% of a workgroup's time, and 42 fewer of
+// them left a call as it was: the chain of dependent operations waits.  The
+// tables' uniform values are read by scalar loads where they are used (kept
+// across a tile they took 75 vector instructions a tile to bring back from
+// spilled lanes).
 
 // Zero in a vector register the compiler cannot see through: an atomic at
 // such an offset is left as written (at an address known to be uniform it is
