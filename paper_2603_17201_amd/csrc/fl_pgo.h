@@ -253,8 +253,9 @@ __device__ inline void pgo_store_jacobian(const PgoArgs& a, int side, int k, con
 // e and the exact J_i, J_j of each edge; nothing after a refused step (the
 // linearisation at the accepted poses is kept).  A chain of float64 operations,
 // bound by one wave's issue: the first wave of a workgroup makes J_i, the second
-// J_j, both the error and J_l^-1 they share (14.0 us for 3,002 edges; one wave
-// making both took 17.6).
+// J_j, both the error and J_l^-1 they share (3,002 edges: 14.0 us, one wave
+// making both took 17.6; of ten iterations the first, whose large errors take
+// the long series, 33, the last 13).
 __global__ __launch_bounds__(kPgoJacBlock) void pgo_jacobian_kernel(PgoArgs a) {
     __shared__ double s_P[2][kPgoJacEdges * 49];
     const int side = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));

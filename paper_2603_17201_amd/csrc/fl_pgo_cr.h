@@ -25,8 +25,8 @@
 // panel steps of 16 columns; the arithmetic (about 6 m^3 fused multiply-adds
 // per block, on the float64 matrix instructions) is a few microseconds.  On
 // 1,000 keyframes, per level: one lap (N = 167 blocks of 48, 8 levels)
-// eliminate 10.7, update 4.4, back 4.6 us, three laps (40 blocks of 176, 6
-// levels) 60, 12.4 and 13.4 us; a whole iteration 0.23 and 0.67 ms, where the
+// eliminate 9.9, update 4.8, back 4.4 us, three laps (40 blocks of 176, 6
+// levels) 57, 12.4 and 13.3 us; a whole iteration 0.22 and 0.65 ms, where the
 // band solves took 3.65 and 9.7 ms.
 #pragma once
 
